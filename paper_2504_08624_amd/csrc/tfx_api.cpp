@@ -68,8 +68,8 @@ tfx_status check_ws(void *ws, size_t ws_bytes, size_t need) {
 }
 
 // Default fp32 FIR path by tap count: direct up to 48 taps, one 4096-point
-// FFT per 3072-sample block up to 1025, one 16384-point FFT per 8192-sample
-// block up to 8193, partitioned 4096-point FFTs beyond.
+// FFT per 3072-sample block up to 1025, one 16384-point FFT per block
+// up to 8193, partitioned 4096-point FFTs beyond.
 int32_t auto_fir_mode(int32_t M) {
     if (M <= 48) return tfx::FIR_DIRECT;
     if (M > tfx::FFT_PART && M <= tfx::FFT16_MAX_TAPS) return tfx::FIR_FFT16;
@@ -135,6 +135,19 @@ tfx_status gather(const tfx_stage *stages, int32_t nstages, Gathered &g) {
     }
     if (g.S > tfx::MAX_SECTIONS) return fail(TFX_E_UNSUPPORTED, "more than %d sections in one chain", tfx::MAX_SECTIONS);
     if (g.Mtot > tfx::MAX_TAPS) return fail(TFX_E_UNSUPPORTED, "merged FIR longer than %d taps", tfx::MAX_TAPS);
+    return TFX_OK;
+}
+
+// Workspace layout of a chain call.
+tfx_status chain_layout(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
+                        tfx::WsLayout &lay) {
+    if (C < 1 || N < 0) return fail(TFX_E_INVALID_ARG, "bad shape");
+    Gathered g;
+    tfx_status s = gather(stages, nstages, g);
+    if (s) return s;
+    int32_t mode = tfx::FIR_NONE;
+    if (g.firs.n > 0 && (s = check_fir_mode(g.Mtot, cmp, TFX_FIR_AUTO, &mode, C, N, g.S == 0))) return s;
+    lay = tfx::ws_layout(C, N, g.S, g.Mtot, g.firs.n, mode);
     return TFX_OK;
 }
 
@@ -323,6 +336,15 @@ tfx_status set_error(tfx_status s, const char *msg) {
     g_last_error = msg;
     return s;
 }
+
+tfx_status chain_workspace_least(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
+                                 size_t *bytes) {
+    WsLayout lay{};
+    const tfx_status s = chain_layout(C, N, stages, nstages, cmp, lay);
+    if (s) return s;
+    *bytes = lay.total;
+    return ok();
+}
 }  // namespace tfx
 
 extern "C" {
@@ -399,13 +421,10 @@ tfx_status tfx_sos_workspace_size(int64_t C, int64_t N, int32_t S, size_t *bytes
 tfx_status tfx_chain_workspace_size(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages,
                                     tfx_compute cmp, size_t *bytes) {
     if (!bytes) return fail(TFX_E_INVALID_ARG, "bytes is NULL");
-    if (C < 1 || N < 0) return fail(TFX_E_INVALID_ARG, "bad shape");
-    Gathered g;
-    tfx_status s = gather(stages, nstages, g);
+    tfx::WsLayout lay{};
+    const tfx_status s = chain_layout(C, N, stages, nstages, cmp, lay);
     if (s) return s;
-    int32_t mode = tfx::FIR_NONE;
-    if (g.firs.n > 0 && (s = check_fir_mode(g.Mtot, cmp, TFX_FIR_AUTO, &mode, C, N, g.S == 0))) return s;
-    *bytes = tfx::ws_layout(C, N, g.S, g.Mtot, g.firs.n, mode).total;
+    *bytes = lay.total_short;
     return ok();
 }
 

@@ -623,6 +623,7 @@ static size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode) {
     BwdLayout b{};
     b.fwd = ws_layout(C, N, S, M_merged, n_fir, fir_mode);
+    b.fwd.short_shape = false;
     const int64_t ntiles = b.fwd.ntiles, cpad = b.fwd.cpad, npairs = cpad / 2;
     // the forward layout ends with a 256-aligned total (or 0 when it needs nothing)
     size_t off = b.fwd.total ? b.fwd.total : 256;
@@ -694,9 +695,6 @@ hipError_t launch_backward(const BwdPlan &bp) {
                              : nullptr;
     // tables, merged taps, spectrum; clears the look-back records
     if ((e = launch_tables(p, lay.fwd, h, M)) != hipSuccess) return e;
-    if (has_fir && p.fir_mode == FIR_FFT16 &&
-        (e = launch_fft16k_prepare(h, M, ws + lay.fwd.f16, st)) != hipSuccess)
-        return e;
     // the cascade input f and the gradient of the cascade input gf
     const float *f = p.x;
     int64_t ldf = p.ldx;

@@ -111,6 +111,7 @@ struct KArgs {
     const float *hist;    // streaming: the M - 1 FIR inputs before the block, [C][M - 1] (null = zeros)
     int64_t ldh;          // M - 1
     uint32_t xcd_ks;      // block order: xcd_order's log2 K (0 = block ids in order)
+    int32_t after_short;  // the short-memory kernel ran before this one: nothing to do if it did the work
 };
 
 // FIR input x[ch][n] of the block, n < N, with the streaming history for
@@ -617,6 +618,7 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
     // for both)
     float2 *s_twl = reinterpret_cast<float2 *>(s_dyn);
 
+    if (HAS_SOS && a.after_short && short_done(a.hdr)) return;
     if (HAS_SOS && (a.hdr[HDR_HIQ] != 0u) != HIQ) {  // the other variant runs
         advance_epoch(a.hdr);
         return;
@@ -810,6 +812,7 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
     __shared__ __align__(16) float lds[mc_lds_floats<FIRM>()];
     __shared__ uint32_t s_epoch;
     __shared__ __align__(16) float2 s_twl[FIRM == FIR_FFT ? TWL_ENTRIES : 2];  // the transforms' twiddles
+    if (a.after_short && short_done(a.hdr)) return;
     if (a.hdr[HDR_HIQ] != 0u) {  // the FP64-carry variant runs
         advance_epoch(a.hdr);
         return;
@@ -922,7 +925,11 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
     if (fir_mode == FIR_TOEPLITZ) off += al256(toeplitz_table_bytes(M_merged, 3));  // largest (split) table
     w.f16 = off;
     if (fir_mode == FIR_FFT16) off += al256(fft16k_table_bytes());
+    w.short_shape = S > 0 && S <= CASC_MAX && M_merged <= FFT16_MAX_TAPS && C * N * S >= SHORT_MIN_WORK &&
+                    ((fir_mode == FIR_FFT && fft_parts(M_merged) == 1) || fir_mode == FIR_FFT16);
+    w.sh = off;
     w.total = (S > 0 || n_fir > 1 || fir_mode == FIR_FFT || fir_mode == FIR_TOEPLITZ || fir_mode == FIR_FFT16) ? off : 0;
+    w.total_short = w.total + (w.short_shape ? al256(fft16k_table_bytes() + sizeof(ShortTab)) : 0);
     return w;
 }
 
@@ -1000,8 +1007,6 @@ hipError_t launch_prepare(const ChainPlan &p) {
     const WsLayout lay = ws_layout(p.C, p.N, p.S, Mtot, p.firs.n, p.fir_mode);
     hipError_t e = launch_tables(p, lay, taps_ptr(p, lay), Mtot);
     if (e != hipSuccess) return e;
-    if (Mtot > 0 && p.fir_mode == FIR_FFT16)
-        return launch_fft16k_prepare(taps_ptr(p, lay), Mtot, static_cast<char *>(p.ws) + lay.f16, p.stream);
     if (p.fir_mode != FIR_TOEPLITZ) return e;
     return launch_toeplitz_prepare(taps_ptr(p, lay), Mtot, p.cmp, static_cast<char *>(p.ws) + lay.ttab, p.stream);
 }
@@ -1043,10 +1048,22 @@ hipError_t launch_run(const ChainPlan &p) {
     // into the chain kernel (the split-bf16 form and a FIR alone run the
     // stand-alone Toeplitz kernel)
     const bool tz_fused = Mtot > 0 && p.fir_mode == FIR_TOEPLITZ && p.S > 0 && (p.cmp == TZ_BF16 || p.cmp == TZ_F16);
+    uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
+    // a chain that may be a short-memory one, with nothing asked for that only
+    // the scan gives (checkpoints, registers, a stream's history)
+    const bool short_try = lay.short_shape && p.ws_bytes >= lay.total_short && !p.n_layout && !p.ckpt && !p.state_in &&
+                           !p.state_out && !p.hist_in && !p.hist_out;
+    if (short_try) {
+        const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot, ws + lay.sh,
+                                             ws + (p.fir_mode == FIR_FFT16 ? lay.f16 : lay.sh), hdr, p.stream);
+        if (e != hipSuccess) return e;
+        k.after_short = 1;
+    }
     if (Mtot > 0 && p.fir_mode == FIR_FFT16) {
         // 16384-point FFT FIR into y, then the cascade in place over y (each
         // tile of the cascade kernel reads only the samples it writes)
-        hipError_t e = launch_fft16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot, ws + lay.f16, false, p.hist_in, p.stream);
+        hipError_t e = launch_fft16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot, ws + lay.f16, false, p.hist_in,
+                                     short_try ? hdr : nullptr, p.stream);
         if (e != hipSuccess || p.S == 0) return e;
         k.x = p.y;
         k.ldx = p.ldy;
@@ -1075,7 +1092,7 @@ hipError_t launch_run(const ChainPlan &p) {
     k.ckpt = p.ckpt;
     k.ntiles = (p.N + T - 1) / T;  // the block's tiles (streaming: the layout may be for a longer block)
     k.cpad = lay.cpad;
-    k.hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
+    k.hdr = hdr;
     k.tab = reinterpret_cast<const SecTab *>(ws + lay.tab);
     k.recs = reinterpret_cast<uint64_t *>(ws + lay.recs);
     k.vec = ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.y)) % 16 == 0 && p.ldx % 4 == 0 &&
@@ -1117,7 +1134,8 @@ hipError_t launch_fir_pass(const ChainPlan &p, const WsLayout &lay, const float 
     if (p.N == 0 || Mtot == 0) return hipSuccess;
     char *ws = static_cast<char *>(p.ws);
     if (p.fir_mode == FIR_FFT16)
-        return launch_fft16k(in, out, p.C, p.N, ldin, ldout, Mtot, ws + lay.f16, correlate, nullptr, p.stream);
+        return launch_fft16k(in, out, p.C, p.N, ldin, ldout, Mtot, ws + lay.f16, correlate, nullptr, nullptr,
+                             p.stream);
     KArgs k{};
     k.x = in;
     k.y = out;

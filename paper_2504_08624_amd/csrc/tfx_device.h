@@ -43,6 +43,13 @@ __device__ __forceinline__ void advance_epoch(uint32_t *hdr) {
     }
 }
 
+// Whether the short-memory kernel has done this run's work: the chain is a
+// short-memory one and no value of this run was not finite (then the general
+// kernels run, and a non-finite sample travels as in any other chain).
+__device__ __forceinline__ bool short_done(const uint32_t *hdr) {
+    return hdr[HDR_SHORT] != 0u && hdr[HDR_BAD] != hdr[HDR_EPOCH];
+}
+
 // Logical block id of block b for L2 reuse across the chip's 8 XCDs, which
 // take block ids round robin (block b runs on XCD b % 8) and each have their
 // own L2.  Within every window of 8 K block ids (K = 2^ks), XCD x takes the

@@ -35,11 +35,13 @@ struct F16Args {
     const float *hist;  // streaming: [C][hlen] inputs before the block (convolution only), or null
     int64_t hlen;
     int32_t correlate;
+    const uint32_t *gate;  // workspace header of a chain whose short-memory kernel ran before, or null
 };
 
 __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     __shared__ __align__(16) float P[PLANE];
     __shared__ __align__(16) float2 twl[TW_FLOAT2];
+    if (a.gate && short_done(a.gate)) return;
     const int t = threadIdx.x;
     tw_stage(twl, a.tw, t);
     const uint32_t u = xcd_unit(blockIdx.x, a.nunits);
@@ -61,66 +63,84 @@ __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
 }
 
-// Twiddle rows and tap spectrum / 16384, in FP64 and rounded once.  A block of
-// 256 threads covers 16 bins: lane (kk, jj) sums the taps j = jj (mod 16) of
-// bin k = 16 blk + kk by Horner's rule in w^16, the 16 partial sums are added
-// by a fixed shuffle tree.  The taps are real: bins 0..8192 are computed, the
-// others are their conjugates.  (Per prepare of an 8191-tap filter this spreads
-// over the chip what one workgroup's fp32 transform did in 17 us.)
-__global__ __launch_bounds__(256) void fft16k_prepare_kernel(const float *h, int32_t M, float2 *tw, float2 *hs) {
-    extern __shared__ double ht[];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const int steps = (M + 15) / 16;
-    for (int j = tid; j < 16 * steps; j += 256) ht[j] = j < M ? (double)h[j] : 0.0;
-    const int i = b * 256 + tid;
-    if (i < TW_FLOAT2) {
-        const int row = i / TWS, k = i % TWS;
-        const int m = k < R ? ((row < 32 ? 16 * row : row - 32) * k) & (NB - 1) : 0;
-        double s, c;
-        sincospi(-2.0 * (double)m / NB, &s, &c);
-        tw[i] = k < R ? make_float2((float)c, (float)s) : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    const int kk = tid >> 4, jj = tid & 15;
-    const int k = 16 * b + kk;
-    double wr, wi, pr, pi;
-    sincospi(-2.0 * (double)((16 * k) & (NB - 1)) / NB, &wi, &wr);
-    sincospi(-2.0 * (double)((jj * k) & (NB - 1)) / NB, &pi, &pr);
-    double ar = 0.0, ai = 0.0;
-#pragma unroll 4
-    for (int m = steps - 1; m >= 0; --m) {
-        const double nr = fma(ar, wr, fma(-ai, wi, ht[jj + 16 * m]));
-        ai = fma(ar, wi, ai * wr);
-        ar = nr;
-    }
-    double hr = ar * pr - ai * pi, hi = fma(ar, pi, ai * pr);
+// Memory V of the chain of an M-tap FIR and the cascade (M - 1 and the length of
+// the cascade's response that the decay sums prove, rounded up to 64), or 0
+// when the sums prove none up to FFT16_MEM.  By a whole wave, the same in each.
+__device__ __forceinline__ int short_memory(const ShortTab *st, int32_t M, int lane) {
+    const int j = lane & 3;
+    const double lam = st->lam[j];
+    double s = st->sum[lane >> 2][j];
 #pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) {
-        hr += __shfl_xor(hr, d);
-        hi += __shfl_xor(hi, d);
+    for (int d = 4; d < 64; d <<= 1) s += __shfl_xor(s, d);
+    const double unit = __shfl(s, 0);
+    // (false for a NaN, for an unstable cascade and for one with FP64 carry)
+    float len = 1e9f;
+    if (lam < 0.0 && unit < 1e300 && s < 1e300) {
+        const float r = (float)(unit / s);
+        if (r > 0.f) len = fmaxf((SHORT_LOG2_EPS + 0.5f * log2f(r)) / (float)lam, 0.f);
+        else if (unit == 0.0) len = 0.f;
     }
-    if (jj == 0 && k <= NB / 2) {
-        const float2 v = make_float2((float)(hr / NB), (float)(hi / NB));
-        hs[spec_at(k)] = v;
-        if (k > 0 && k < NB / 2) hs[spec_at(NB - k)] = make_float2(v.x, -v.y);
-    }
+#pragma unroll
+    for (int d = 1; d < 4; d <<= 1) len = fminf(len, __shfl_xor(len, d));
+    if (!(len <= (float)FFT16_MEM)) return 0;
+    const int V = (M - 1 + (int)len + 1 + 63) & ~63;
+    return __builtin_amdgcn_readfirstlane(V <= FFT16_MEM ? V : 0);
 }
-constexpr int PREP_BLOCKS = NB / 2 / 16 + 1;
-static_assert(PREP_BLOCKS * 256 >= TW_FLOAT2, "the prepare grid covers the twiddle rows");
+
+// A short-memory chain (FIR and cascade as one filter of memory V; the grid is
+// sized for the longest memory).  The same two
+// transforms a block as above.  A value that is not finite marks the run, and
+// the general kernels behind this one do it again.
+struct ShortArgs {
+    const float *x;
+    float *y;
+    int64_t C, N, ldx, ldy;
+    const float2 *tw, *hs;
+    const ShortTab *st;
+    uint32_t *hdr;
+    int32_t M;
+};
+
+__global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
+    __shared__ __align__(16) float P[PLANE];
+    __shared__ __align__(16) float2 twl[TW_FLOAT2];
+    const int V = short_memory(a.st, a.M, threadIdx.x & 63), T = NB - V;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
+    if (V == 0) return;
+    const uint32_t per_ch = (uint32_t)((a.N + 2 * T - 1) / (2 * T));
+    const uint32_t nunits = (uint32_t)a.C * per_ch;
+    if (blockIdx.x >= nunits) return;
+    const int t = threadIdx.x;
+    tw_stage(twl, a.tw, t);
+    const uint32_t u = xcd_unit(blockIdx.x, nunits);
+    const int64_t ch = u / per_ch;
+    const int64_t n0 = (int64_t)(u - (uint32_t)ch * per_ch) * 2 * T, n1 = n0 + T;
+    const float *xc = a.x + ch * a.ldx;
+    float zr[R], zi[R];
+    load_block(zr, xc, n0 - V, a.N, nullptr, 0, t);
+    load_block(zi, xc, n1 - V, a.N, nullptr, 0, t);
+    __syncthreads();  // the twiddle rows
+    forward(zr, zi, P, twl, t);
+    spec_mul(zr, zi, a.hs, t, 1.f);
+    inverse(zr, zi, P, twl, t);
+    float *yc = a.y + ch * a.ldy;
+    store_block(zr, yc, n0, V, T, a.N, t);
+    if (n1 < a.N) store_block(zi, yc, n1, V, T, a.N, t);
+    // a NaN or an infinity in a block's input reaches every output as a NaN;
+    // an overflow in the last pass may be in any one of them
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
+    if (!(m < INFINITY) || zr[0] != zr[0] || zi[0] != zi[0])
+        __hip_atomic_store(a.hdr + HDR_BAD, a.hdr[HDR_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 }  // namespace
 
 size_t fft16k_table_bytes() { return (size_t)TW_FLOAT2 * sizeof(float2) + (size_t)NB * sizeof(float2); }
 
-hipError_t launch_fft16k_prepare(const float *h, int32_t M, void *tab, hipStream_t st) {
-    float2 *tw = static_cast<float2 *>(tab);
-    hipLaunchKernelGGL(fft16k_prepare_kernel, dim3(PREP_BLOCKS), dim3(256), (size_t)((M + 15) / 16 * 16) * sizeof(double),
-                       st, h, M, tw, tw + TW_FLOAT2);
-    return hipGetLastError();
-}
-
 hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                         const void *tab, bool correlate, const float *hist, hipStream_t st) {
+                         const void *tab, bool correlate, const float *hist, const uint32_t *hdr, hipStream_t st) {
     if (N == 0) return hipSuccess;
     F16Args a{};
     a.x = x;
@@ -138,7 +158,27 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
     a.hist = (!correlate && M > 1) ? hist : nullptr;
     a.hlen = M > 1 ? M - 1 : 0;
     a.correlate = correlate ? 1 : 0;
+    a.gate = hdr;
     hipLaunchKernelGGL(fir16k_kernel, dim3(a.nunits), dim3(WGB), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
+                           const void *tab, const void *tw, uint32_t *hdr, hipStream_t st) {
+    ShortArgs a{};
+    a.x = x;
+    a.y = y;
+    a.C = C;
+    a.N = N;
+    a.ldx = ldx;
+    a.ldy = ldy;
+    a.tw = static_cast<const float2 *>(tw);
+    a.hs = static_cast<const float2 *>(tab) + TW_FLOAT2;
+    a.st = reinterpret_cast<const ShortTab *>(static_cast<const char *>(tab) + fft16k_table_bytes());
+    a.hdr = hdr;
+    a.M = M;
+    const int64_t T2 = 2 * (int64_t)(NB - FFT16_MEM);  // the shortest tiles: the most blocks
+    hipLaunchKernelGGL(short16k_kernel, dim3((unsigned)(C * ((N + T2 - 1) / T2))), dim3(WGB), 0, st, a);
     return hipGetLastError();
 }
 

@@ -37,11 +37,11 @@ constexpr int TWL_S = 18, TWL_ROWS = 32, TWL_ENTRIES = TWL_ROWS * TWL_S;
 // The fp32 twiddle region of the workspace holds TWL alone (float2 entries).
 constexpr int TWID_ENTRIES = TWL_ENTRIES;
 __host__ __device__ constexpr int fft_parts(int M) { return (M + FFT_PART - 1) / FFT_PART; }
-// One 16384-point FFT per block of 8192 outputs (tfx_fft16k.hip): filters of
-// up to 8193 taps.
+// One 16384-point FFT per block (tfx_fft16k.hip): filters with a memory of up
+// to 8192 samples, whose blocks give at least 8192 outputs.
 constexpr int FFT16_POINTS = 16384;
-constexpr int FFT16_HOP = 8192;
-constexpr int FFT16_MAX_TAPS = FFT16_HOP + 1;
+constexpr int FFT16_MEM = 8192;
+constexpr int FFT16_MAX_TAPS = FFT16_MEM + 1;
 
 constexpr int MAX_STAGES = 64;
 constexpr int MAX_SECTIONS = 256;
@@ -165,25 +165,44 @@ struct alignas(16) McTab {
     float Fsr[16][16];
 };
 
-// Header words of a workspace: look-back error bit, look-back epoch, and
+// Header words of a workspace: look-back error bit, look-back epoch,
 // whether any section needs the FP64 carry (the filter kernels come in two
-// variants; the one that does not match this word exits at once).
-enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3 };
+// variants; the one that does not match this word exits at once), the memory
+// of a short-memory chain (V | 1, V a multiple of 64; 0: none), and the epoch of
+// the last run in which its kernel met a value that is not finite.
+enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5 };
 
-// Pole radius of 1 + a1 z^-1 + a2 z^-2 above 0.999: the section's carry
-// runs in FP64.
-__host__ __device__ inline bool section_hiq(double a1, double a2) {
+// Short-memory chains: an FFT FIR with a cascade of up to CASC_MAX sections
+// whose impulse response has died out within FFT16_MEM samples is one FIR, and
+// runs as one (short16k_kernel) instead of a FIR and a scan.  Whether a chain is
+// one is found out on the device: the prepare step leaves the sums below, and
+// the kernel takes as the response's length the smallest L that a circle
+// proves: rho^L (sum / sum of the unit circle)^(1/2) <= SHORT_EPS.  The response
+// beyond it has 2^-31 of the whole's 2-norm: a hundredth of an fp32 rounding of
+// the output, and a few hundredths where a resonance alone is heard.
+constexpr float SHORT_LOG2_EPS = -31.f;
+constexpr int CIRC_BLOCKS = 16;
+struct ShortTab {
+    double lam[4];               // log2 rho_j (rho_0 = 1; all 0: a section wants the FP64 carry)
+    double sum[CIRC_BLOCKS][4];  // shares of the sum of |H|^2 on circle j
+};
+// Samples times sections from which a short-memory chain is worth its 16384-
+// point blocks; below, the scan's 3072-sample tiles fill the chip better.  Per
+// call, scan against blocks: 2 sections (101 taps) 2 x 0.48 M samples 30 / 36 us,
+// 8 x 0.5 M 36 / 38, 8 x 1 M 52 / 43; 6 sections (1023 taps) 2 x 0.48 M 37 / 37,
+// 8 x 0.5 M 46 / 39, 8 x 5.76 M 252 / 147.
+constexpr int64_t SHORT_MIN_WORK = 10000000;
+
+// Larger pole radius of 1 + a1 z^-1 + a2 z^-2.
+__host__ __device__ inline double section_radius(double a1, double a2) {
     const double disc = a1 * a1 - 4.0 * a2;
-    double r;
-    if (disc < 0.0) {
-        r = sqrt(a2);
-    } else {
-        const double sq = sqrt(disc);
-        const double r1 = fabs(0.5 * (-a1 + sq)), r2 = fabs(0.5 * (-a1 - sq));
-        r = r1 > r2 ? r1 : r2;
-    }
-    return r > 0.999;
+    if (disc < 0.0) return sqrt(a2);
+    const double sq = sqrt(disc);
+    const double r1 = fabs(0.5 * (-a1 + sq)), r2 = fabs(0.5 * (-a1 - sq));
+    return r1 > r2 ? r1 : r2;
 }
+// Above 0.999 the section's carry runs in FP64.
+__host__ __device__ inline bool section_hiq(double a1, double a2) { return section_radius(a1, a2) > 0.999; }
 
 struct StageList {
     const float *ptr[MAX_STAGES];
@@ -214,6 +233,10 @@ struct ChainPlan {
 // Workspace layout of a chain/SOS/FIR call.
 struct WsLayout {
     size_t hdr, tab, recs, casc, zir, mc, taps, merge, twid, hspec, tw64, ttab, f16, total;
+    // a chain that may be a short-memory one also wants its combined spectrum
+    // at sh (total_short bytes in all); without that room it runs as any other
+    size_t sh, total_short;
+    bool short_shape;
     int64_t ntiles, cpad;
 };
 WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode);
@@ -221,6 +244,10 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
 // Sets the calling thread's tfx_last_error message and returns s (for entry
 // points defined outside tfx_api.cpp).
 tfx_status set_error(tfx_status s, const char *msg);
+// The workspace a chain call cannot do without (tfx_chain_workspace_size may
+// ask for more).
+tfx_status chain_workspace_least(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
+                                 size_t *bytes);
 
 // The FIR form tfx_fir_autotune recorded for an fp32 call of this shape
 // (false when there is none).
@@ -257,13 +284,20 @@ hipError_t launch_toeplitz(const float *x, float *y, int64_t C, int64_t N, int64
                            int32_t cmp, const void *tab, hipStream_t st, const float *hist = nullptr);
 
 // ---- overlap-save FIR with 16384-point FFTs (tfx_fft16k.hip) --------------------
-// Twiddle tables and tap spectrum of the 16384-point path.
+// Twiddle rows and one spectrum of the 16384-point path (written by the
+// prepare step).
 size_t fft16k_table_bytes();
-hipError_t launch_fft16k_prepare(const float *h, int32_t M, void *tab, hipStream_t st);
 // FIR (or, with correlate, its adjoint correlation) x -> y; hist: streaming
-// history [C][M - 1] before the block (convolution only), or null.
+// history [C][M - 1] before the block (convolution only), or null; hdr: the
+// workspace header when the short-memory kernel may have done the work
+// already (then this one does nothing), or null.
 hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                         const void *tab, bool correlate, const float *hist, hipStream_t st);
+                         const void *tab, bool correlate, const float *hist, const uint32_t *hdr, hipStream_t st);
+// Chain x -> y with the combined spectrum and decay sums of tab and the twiddle
+// rows tw (the prepare step writes them once, in front of its first spectrum),
+// if it is a short-memory one (which the kernel leaves in the header).
+hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
+                           const void *tab, const void *tw, uint32_t *hdr, hipStream_t st);
 
 // ---- batched ragged clips (tfx_batched.hip) -------------------------------------
 // Device descriptor of one clip, in processing order.  Blocks of the single

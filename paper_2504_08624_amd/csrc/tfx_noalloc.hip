@@ -51,7 +51,7 @@ tfx_status tfx_chain_noalloc(const float *x, float *y, int64_t C, int64_t N, int
                              const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt, uint32_t *flags,
                              void *stream) {
     size_t need = 0;
-    tfx_status s = tfx_chain_workspace_size(C, N, stages, nstages, cmp, &need);
+    tfx_status s = tfx::chain_workspace_least(C, N, stages, nstages, cmp, &need);
     if (s) return s;
     if (need > SCRATCH_BYTES) {
         char msg[256];

@@ -5,9 +5,19 @@
 // kernel (tfx_chain.hip) only reads what they leave in the workspace.
 #include <hip/hip_runtime.h>
 
+#include "tfx_fft16k.h"
 #include "tfx_internal.h"
 
 namespace tfx {
+
+// The table builders below run one per block, in one kernel: each lays its
+// arrays over the block's one LDS buffer.
+constexpr int PREP_LDS = 20 * 1024;
+template <class Sh>
+__device__ __forceinline__ Sh &lds_as(char *raw) {
+    static_assert(sizeof(Sh) <= PREP_LDS, "fits the block's LDS buffer");
+    return *reinterpret_cast<Sh *>(raw);
+}
 
 __device__ void mat2_mul(const double *A, const double *B, double *C) {
     const double c0 = A[0] * B[0] + A[1] * B[2];
@@ -131,9 +141,14 @@ __device__ double block_maxabs(const double (*M)[16], int i, int j, int tid) {
 
 // co(s, k): coefficient k of section s; Lc: the chunk length (tile 128 Lc).
 template <class Co>
-__device__ void casc_table_block(Co co_at, int32_t S, int Lc, CascTab *out, int tid) {
-    __shared__ double co[CASC_MAX][5];
-    __shared__ double M0[16][16], M1[16][16], Pw[7][16][16];
+__device__ void casc_table_block(char *raw, Co co_at, int32_t S, int Lc, CascTab *out, int tid) {
+    struct Sh {
+        double co[CASC_MAX][5], M0[16][16], M1[16][16], Pw[7][16][16];
+    };
+    Sh &sh = lds_as<Sh>(raw);
+    auto &co = sh.co;
+    auto &M0 = sh.M0, &M1 = sh.M1;
+    auto &Pw = sh.Pw;
     const int i = tid >> 4, j = tid & 15;
     if (tid < S * 5) co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
     __syncthreads();
@@ -185,10 +200,14 @@ __device__ void casc_table_block(Co co_at, int32_t S, int Lc, CascTab *out, int 
 // section s reaches the output through the b0 of every later section) and
 // c[2s+1] = 0.
 template <class Co>
-__device__ void zir_block(Co co_at, int32_t S, int Lc, int k, CascZir *out, int tid) {
-    __shared__ double co[CASC_MAX][5];
-    __shared__ double Fm[16][16], P[16][16];
-    __shared__ double g[16];
+__device__ void zir_block(char *raw, Co co_at, int32_t S, int Lc, int k, CascZir *out, int tid) {
+    struct Sh {
+        double co[CASC_MAX][5], Fm[16][16], P[16][16], g[16];
+    };
+    Sh &sh = lds_as<Sh>(raw);
+    auto &co = sh.co;
+    auto &Fm = sh.Fm, &P = sh.P;
+    auto &g = sh.g;
     const int i = tid >> 4, j = tid & 15;
     if (tid < S * 5) co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
     __syncthreads();
@@ -232,12 +251,18 @@ __device__ void zir_block(Co co_at, int32_t S, int Lc, int k, CascZir *out, int 
 // output rows c F^r, the chunk transition Fc = F^32 and the segment
 // transition Fc^12, each laid out as the kernel's operands.
 template <class Co>
-__device__ void mc_block(Co co_at, int32_t S, McTab *out, int tid) {
-    __shared__ double co[CASC_MAX][5];
-    __shared__ double Pw[16][16], Q[16][16];
-    __shared__ double V[MC_LC][16];   // F^m b
-    __shared__ double Gm[MC_LC][16];  // c F^r
-    __shared__ double hh[MC_LC];
+__device__ void mc_block(char *raw, Co co_at, int32_t S, McTab *out, int tid) {
+    struct Sh {
+        double co[CASC_MAX][5], Pw[16][16], Q[16][16];
+        double V[MC_LC][16];   // F^m b
+        double Gm[MC_LC][16];  // c F^r
+        double hh[MC_LC];
+    };
+    Sh &sh = lds_as<Sh>(raw);
+    auto &co = sh.co;
+    auto &Pw = sh.Pw, &Q = sh.Q;
+    auto &V = sh.V, &Gm = sh.Gm;
+    auto &hh = sh.hh;
     const int i = tid >> 4, j = tid & 15;
     if (tid < S * 5) co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
     __syncthreads();
@@ -372,8 +397,12 @@ __global__ void fft_twiddle_kernel(float2 *twid, double2 *tw64) {
 // 65 steps from an exact start, so the FP64 twiddle error stays near
 // 1e-14, far below the fp32 rounding of the result); the 16 partial sums
 // are added by a fixed shuffle tree.
-__device__ void spectrum_block(const float *h_all, int32_t M_all, int part, int blk, float2 *hspec_all, int tid) {
-    __shared__ float hs[FFT_PART + 15];
+__device__ void spectrum_block(char *raw, const float *h_all, int32_t M_all, int part, int blk, float2 *hspec_all,
+                               int tid) {
+    struct Sh {
+        float hs[FFT_PART + 15];
+    };
+    auto &hs = lds_as<Sh>(raw).hs;
     const int kk = tid >> 4, jj = tid & 15;
     const int k = blk * 16 + kk;
     const float *h = h_all + (int64_t)part * FFT_PART;
@@ -403,6 +432,161 @@ __device__ void spectrum_block(const float *h_all, int32_t M_all, int part, int 
         hspec_all[(int64_t)part * NFFT + 16 * (k & 255) + (k >> 8)] = make_float2((float)(hr / NFFT), (float)(hi / NFFT));
 }
 
+// Spectra of the 16384-point path, in FP64 and rounded once, each / 16384 in
+// the transform's output order: the taps' (hs), and the taps' times the
+// cascade's (ht); with hf the taps' spectrum also stays in FP64 (bin k at
+// hf[k], unscaled).  With n = 128 n1 + n2 and k = k1 + 128 k2, block k1 forms
+// A[n2] = W^(n2 k1) sum_n1 h[n] W_128^(n1 k1) and from it its 128 bins
+// sum_n2 A[n2] W_128^(n2 k2), two threads a bin; everything is real in time, so
+// blocks k1 <= 64 give the others' bins as conjugates.  The first blocks also
+// write the twiddle rows.  (A direct sum per bin took 29 us of a prepare with
+// 1023 taps, one workgroup's fp32 transform 17; this form takes none of its
+// critical path.)
+constexpr int SPEC16_BLOCKS = 65;
+static_assert(SPEC16_BLOCKS * 256 >= f16k::TW_FLOAT2, "the spectrum blocks cover the twiddle rows");
+__device__ __forceinline__ double2 cmul64(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+template <class Co>
+__device__ void spec16_block(char *raw, const float *h, int32_t M, Co co_at, int32_t S, int k1, float2 *tw, float2 *hs, float2 *ht,
+                             double2 *hf, int tid) {
+    constexpr int NB = FFT16_POINTS;
+    struct Sh {
+        double2 w128[128], wq[128], A[128], part[128];
+        double cs[CASC_MAX][5];
+    };
+    Sh &sh = lds_as<Sh>(raw);
+    auto &w128 = sh.w128, &wq = sh.wq, &A = sh.A, &part = sh.part;
+    auto &cs = sh.cs;
+    const int q = tid & 127, hf2 = tid >> 7;
+    if (ht && tid < S * 5) cs[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
+    // W_128^q (threads < 128), W^(q k1) (the others), then the twiddle row entry:
+    // one loop, so that the sine's code is there once
+    const int i = k1 * 256 + tid, row = i / f16k::TWS, kr = i % f16k::TWS;
+    const int mr = kr < f16k::R ? (row < 32 ? 16 * row : row - 32) * kr : 0;
+#pragma unroll 1
+    for (int r = 0; r < (i < f16k::TW_FLOAT2 ? 2 : 1); ++r) {
+        const int m = r == 0 ? (hf2 == 0 ? 128 * q : q * k1) : mr;
+        double s, c;
+        sincospi(-2.0 * (double)(m & (NB - 1)) / NB, &s, &c);
+        if (r == 1) tw[i] = kr < f16k::R ? make_float2((float)c, (float)s) : make_float2(0.f, 0.f);
+        else (hf2 == 0 ? w128 : wq)[q] = make_double2(c, s);
+    }
+    __syncthreads();
+    double2 acc = make_double2(0.0, 0.0);
+    const int n1s = (M + 127) / 128;
+#pragma unroll 4
+    for (int n1 = hf2; n1 < n1s; n1 += 2) {
+        const int n = 128 * n1 + q;
+        const double hv = n < M ? (double)h[min(n, M - 1)] : 0.0;
+        const double2 w = w128[(n1 * k1) & 127];
+        acc.x = fma(hv, w.x, acc.x);
+        acc.y = fma(hv, w.y, acc.y);
+    }
+    if (hf2 == 1) part[q] = acc;
+    __syncthreads();
+    if (hf2 == 0) A[q] = cmul64(make_double2(acc.x + part[q].x, acc.y + part[q].y), wq[q]);
+    __syncthreads();
+    const double2 step = w128[q];
+    double2 w = w128[(64 * hf2 * q) & 127];
+    acc = make_double2(0.0, 0.0);
+#pragma unroll 2
+    for (int n2 = 64 * hf2; n2 < 64 * hf2 + 64; ++n2) {
+        const double2 a = A[n2];
+        acc.x = fma(a.x, w.x, fma(-a.y, w.y, acc.x));
+        acc.y = fma(a.x, w.y, fma(a.y, w.x, acc.y));
+        w = cmul64(w, step);
+    }
+    if (hf2 == 1) part[q] = acc;
+    __syncthreads();
+    const int k = k1 + 128 * q;
+    if (hf2 == 0) acc = make_double2(acc.x + part[q].x, acc.y + part[q].y);
+    double2 g = make_double2(1.0, 0.0);
+    if (ht) {  // sections hf2, hf2 + 2, ...: (b0 + z (b1 + z b2)) / (1 + z (a1 + z a2))
+        const double2 zz = cmul64(wq[1], w128[q]);  // W^k
+#pragma unroll 1
+        for (int s = hf2; s < S; s += 2) {
+            const double *c = cs[s];
+            double2 u = cmul64(make_double2(c[1] + zz.x * c[2], zz.y * c[2]), zz);
+            double2 v = cmul64(make_double2(c[3] + zz.x * c[4], zz.y * c[4]), zz);
+            u.x += c[0];
+            v.x += 1.0;
+            const double r = 1.0 / fma(v.x, v.x, v.y * v.y);
+            u = cmul64(u, make_double2(v.x, -v.y));
+            g = cmul64(g, make_double2(u.x * r, u.y * r));
+        }
+        __syncthreads();
+        if (hf2 == 1) part[q] = g;
+        __syncthreads();
+        if (hf2 == 0) g = cmul64(g, part[q]);
+    }
+    // blocks 0 and 64 hold both a bin and its mirror image: the lower one counts
+    if (hf2 == 1 || (k1 == 0 && q > 64) || (k1 == 64 && q > 63)) return;
+    const int km = (NB - k) & (NB - 1), at = f16k::spec_at(k), am = f16k::spec_at(km);
+    const bool both = km != k;
+    if (hs) {
+        const float2 v = make_float2((float)(acc.x / NB), (float)(acc.y / NB));
+        hs[at] = v;
+        if (both) hs[am] = make_float2(v.x, -v.y);
+    }
+    if (ht) {
+        const double2 t = cmul64(acc, g);
+        const float2 v = make_float2((float)(t.x / NB), (float)(t.y / NB));
+        ht[at] = v;
+        if (both) ht[am] = make_float2(v.x, -v.y);
+    }
+    if (hf) {
+        hf[k] = acc;
+        if (both) hf[km] = make_double2(acc.x, -acc.y);
+    }
+}
+
+// Decay of the cascade's response (ShortTab), CIRC_BLOCKS blocks, FP64: thread
+// p of block blk sums |H|^2 at angle (256 blk + tid + 1/2) pi / (256
+// CIRC_BLOCKS) on the unit circle and on circles of radius rho_j between the
+// largest pole radius r and 1.  By Parseval the mean of |H|^2 on a circle of
+// radius rho is sum_n h[n]^2 rho^(-2 n), so the response beyond sample L has a
+// 2-norm of at most rho^L times its root.  (Exact decays by powers of the
+// transition took 19 us in one block; this needs no chain of dependent steps
+// and overstates the memory by 15 - 20 %.)
+template <class Co>
+__device__ void circle_block(char *raw, Co co_at, int32_t S, int blk, ShortTab *out, int tid) {
+    struct Sh {
+        double co[CASC_MAX][5], r[CASC_MAX], w[4][4];
+    };
+    Sh &sh = lds_as<Sh>(raw);
+    if (tid < S * 5) sh.co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
+    __syncthreads();
+    if (tid < S) sh.r[tid] = section_radius(sh.co[tid][3], sh.co[tid][4]);
+    __syncthreads();
+    double rm = 0.0;
+    for (int s = 0; s < S; ++s) rm = sh.r[s] <= rm ? rm : sh.r[s];  // (a NaN stays)
+    double sn, cs;
+    sincospi(-((double)(256 * blk + tid) + 0.5) / (256.0 * CIRC_BLOCKS), &sn, &cs);
+#pragma unroll 1
+    for (int j = 0; j < 4; ++j) {
+        const double rho = j == 0 ? 1.0 : rm + (1.0 - rm) * (j == 1 ? 0.0625 : j == 2 ? 0.125 : 0.25);
+        const double zr = cs / rho, zi = sn / rho;
+        double num = 1.0, den = 1.0;
+#pragma unroll 1
+        for (int s = 0; s < S; ++s) {
+            const double *c = sh.co[s];
+            const double ur = fma(zr, c[2], c[1]), ui = zi * c[2], vr = fma(zr, c[4], c[3]), vi = zi * c[4];
+            const double nr = c[0] + zr * ur - zi * ui, ni = zr * ui + zi * ur;
+            const double dr = 1.0 + zr * vr - zi * vi, di = zr * vi + zi * vr;
+            num *= nr * nr + ni * ni;
+            den *= dr * dr + di * di;
+        }
+        double v = num / den;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+        if ((tid & 63) == 0) sh.w[j][tid >> 6] = v;
+        if (blk == 0 && tid == 0) out->lam[j] = rm <= 0.999 ? log2(rho) : 0.0;
+    }
+    __syncthreads();
+    if (tid < 4) out->sum[blk][tid] = (sh.w[tid][0] + sh.w[tid][1]) + (sh.w[tid][2] + sh.w[tid][3]);
+}
+
 // The prepare step of a chain in one launch.  Blocks take roles by index:
 // tap-spectrum blocks (which also write the twiddle tables), one block per
 // section (scan tables), one block for the cascade's tile transition; every
@@ -422,13 +606,20 @@ struct PrepareArgs {
     uint64_t *recs;
     int64_t nwords;
     uint32_t *hdr;
+    // 16384-point path: the first n16 blocks, for a chain that may be a
+    // short-memory one (ht16 set) CIRC_BLOCKS, then SPEC16_BLOCKS
+    int32_t n16;
+    float2 *tw16, *hs16, *ht16;
+    ShortTab *st16;
+    double2 *hf16;
 };
 
 __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
+    __shared__ __align__(16) char raw[PREP_LDS];
     const int tid = threadIdx.x;
-    const int b = blockIdx.x;
-    for (int64_t i = (int64_t)b * 256 + tid; i < a.nwords; i += (int64_t)gridDim.x * 256) a.recs[i] = 0ull;
-    if (b == 0) {  // header words; the cascade's high-Q word: one section per thread, loads in parallel
+    const int bid = blockIdx.x;
+    for (int64_t i = (int64_t)bid * 256 + tid; i < a.nwords; i += (int64_t)gridDim.x * 256) a.recs[i] = 0ull;
+    if (bid == 0) {  // header words; the cascade's high-Q word: one section per thread, loads in parallel
         __shared__ uint32_t s_any;
         if (tid == 0) s_any = 0u;
         __syncthreads();
@@ -445,11 +636,29 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
             a.hdr[HDR_ERROR] = 0u;
             a.hdr[HDR_EPOCH] = 1u;
             a.hdr[HDR_HIQ] = s_any;
+            a.hdr[HDR_BAD] = 0u;
+            a.hdr[HDR_SHORT] = 0u;
         }
     }
+    if (bid < a.n16) {
+        const StageList &sl = a.sos;
+        const auto co = [&](int s, int k) {
+            int st = 0;
+            while (s >= sl.len[st]) {
+                s -= sl.len[st];
+                ++st;
+            }
+            return (double)sl.ptr[st][5 * s + k];
+        };
+        const int r = a.ht16 ? bid - CIRC_BLOCKS : bid;
+        if (r < 0) circle_block(raw, co, a.S, bid, a.st16, tid);
+        else spec16_block(raw, a.h, a.M, co, a.S, r, a.tw16, a.hs16, a.ht16, a.hf16, tid);
+        return;
+    }
+    const int b = bid - a.n16;
     if (b < a.nspec) {
         const int blk = b % (NFFT / 16), part = b / (NFFT / 16);
-        spectrum_block(a.h, a.M, part, blk, a.hspec, tid);
+        spectrum_block(raw, a.h, a.M, part, blk, a.hspec, tid);
         if (part == 0 && tid < 16) write_twiddle(a.twid, a.tw64, blk * 16 + tid);
     } else if (b < a.nspec + a.S) {
         int s = b - a.nspec, st = 0;
@@ -461,7 +670,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
     } else if (a.casc && b == a.nspec + a.S) {
         const StageList &sl = a.sos;
         casc_table_block(
-            [&](int s, int k) {
+            raw, [&](int s, int k) {
                 int st = 0;
                 while (s >= sl.len[st]) {
                     s -= sl.len[st];
@@ -473,7 +682,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
     } else if (a.casc && a.mc && b == a.nspec + a.S + 1) {
         const StageList &sl = a.sos;
         mc_block(
-            [&](int s, int k) {
+            raw, [&](int s, int k) {
                 int st = 0;
                 while (s >= sl.len[st]) {
                     s -= sl.len[st];
@@ -485,7 +694,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
     } else if (a.casc && a.zir && b > a.nspec + a.S + 1 && b <= a.nspec + a.S + 2 + ZIR_B + ZIR_A) {
         const StageList &sl = a.sos;
         zir_block(
-            [&](int s, int k) {
+            raw, [&](int s, int k) {
                 int st = 0;
                 while (s >= sl.len[st]) {
                     s -= sl.len[st];
@@ -523,6 +732,7 @@ struct BatchPrepArgs {
 // Blocks g < nsec build section g; blocks nsec + c build clip c's cascade
 // tables (when ctab is set); every block clears a share of the records.
 __global__ __launch_bounds__(256) void batch_prep_kernel(BatchPrepArgs a) {
+    __shared__ __align__(16) char raw[PREP_LDS];
     const int tid = threadIdx.x;
     for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < a.nwords; i += (int64_t)gridDim.x * 256) a.recs[i] = 0ull;
     // block map: the last clip whose first block is <= b (first blocks never
@@ -561,7 +771,7 @@ __global__ __launch_bounds__(256) void batch_prep_kernel(BatchPrepArgs a) {
             const ClipDesc &d = a.desc[g - a.nsec];
             if (d.S > 0) {
                 const float *co = d.sos;
-                casc_table_block([&](int s, int k) { return (double)co[5 * s + k]; }, d.S, a.lc,
+                casc_table_block(raw, [&](int s, int k) { return (double)co[5 * s + k]; }, d.S, a.lc,
                                  &a.ctab[g - a.nsec], tid);
             }
         } else {
@@ -569,7 +779,7 @@ __global__ __launch_bounds__(256) void batch_prep_kernel(BatchPrepArgs a) {
             const ClipDesc &d = a.desc[c];
             if (d.S > 0) {
                 const float *co = d.sos;
-                mc_block([&](int s, int k) { return (double)co[5 * s + k]; }, d.S, &a.mtab[c], tid);
+                mc_block(raw, [&](int s, int k) { return (double)co[5 * s + k]; }, d.S, &a.mtab[c], tid);
             }
         }
         __syncthreads();  // the role's shared memory is reused by the next one
@@ -633,6 +843,18 @@ hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h
     a.nwords = p.S > 0 ? lay.cpad * lay.ntiles * p.S * REC_WORDS : 0;
     a.hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     int64_t nb = a.nspec + a.S + (a.casc ? 2 : 0) + (a.zir ? ZIR_B + ZIR_A + 1 : 0);
+    if (p.firs.n > 0 && p.fir_mode == FIR_FFT16) {
+        a.tw16 = reinterpret_cast<float2 *>(ws + lay.f16);
+        a.hs16 = a.tw16 + f16k::TW_FLOAT2;
+        a.n16 = SPEC16_BLOCKS;
+    }
+    if (lay.short_shape && p.ws_bytes >= lay.total_short) {
+        if (!a.tw16) a.tw16 = reinterpret_cast<float2 *>(ws + lay.sh);
+        a.ht16 = reinterpret_cast<float2 *>(ws + lay.sh) + f16k::TW_FLOAT2;
+        a.st16 = reinterpret_cast<ShortTab *>(ws + lay.sh + fft16k_table_bytes());
+        a.n16 = SPEC16_BLOCKS + CIRC_BLOCKS;
+    }
+    nb += a.n16;
     int64_t nclear = (a.nwords + 255) / 256;
     if (nclear > 1024) nclear = 1024;
     if (nb < nclear) nb = nclear;
@@ -650,6 +872,8 @@ __global__ void header_init_kernel(uint32_t *hdr) {
     hdr[HDR_ERROR] = 0u;
     hdr[HDR_EPOCH] = 1u;
     hdr[HDR_HIQ] = 0u;
+    hdr[HDR_SHORT] = 0u;
+    hdr[HDR_BAD] = 0u;
 }
 
 hipError_t launch_header_init(void *ws, size_t ws_bytes, hipStream_t st) {

@@ -180,6 +180,13 @@ tfx_status tfx_chain(const float *x, float *y, int64_t C, int64_t N, int64_t ldx
                      const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt,
                      void *ws, size_t ws_bytes, void *stream);
 
+/* tfx_chain for a training step: ckpt, of the size above, is only good for
+ * tfx_chain_train_backward of the same chain and signal (a chain whose response
+ * dies out quickly leaves it unwritten and is filtered without a scan). */
+tfx_status tfx_chain_train(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
+                           const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt,
+                           void *ws, size_t ws_bytes, void *stream);
+
 /* Two-phase form of tfx_chain for filters whose coefficients stay fixed over
  * many calls (serving loops, captured graphs).  tfx_chain_prepare builds the
  * per-section device tables (and the merged taps) into ws and initialises
@@ -351,6 +358,12 @@ tfx_status tfx_chain_backward(const float *x, const float *gy, float *gx, int64_
                               int64_t ldx, int64_t ldg, int64_t ldgx, const tfx_stage *stages,
                               int32_t nstages, tfx_compute cmp, const float *ckpt,
                               float *const *grads, void *ws, size_t ws_bytes, void *stream);
+/* The same from the ckpt of tfx_chain_train (written to when the forward's scan
+ * has to be run for it after all). */
+tfx_status tfx_chain_train_backward(const float *x, const float *gy, float *gx, int64_t C, int64_t N,
+                                    int64_t ldx, int64_t ldg, int64_t ldgx, const tfx_stage *stages,
+                                    int32_t nstages, tfx_compute cmp, float *ckpt,
+                                    float *const *grads, void *ws, size_t ws_bytes, void *stream);
 
 tfx_status tfx_fir_backward_workspace_size(int64_t C, int64_t N, int32_t M, tfx_compute cmp,
                                            tfx_fir_algo algo, size_t *bytes);

@@ -192,6 +192,21 @@ tfx_status chain_plan(int64_t C, int64_t N, const tfx_stage *stages, int32_t nst
     return TFX_OK;
 }
 
+// tfx_chain and tfx_chain_train (lazy: the checkpoints only serve
+// tfx_chain_train_backward).
+tfx_status chain_call(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, const tfx_stage *stages,
+                      int32_t nstages, tfx_compute cmp, float *ckpt, bool lazy, void *ws, size_t ws_bytes,
+                      void *stream) {
+    tfx_status s = check_signal(x, y, C, N, ldx, ldy);
+    if (s) return s;
+    tfx::ChainPlan p{};
+    if ((s = chain_plan(C, N, stages, nstages, cmp, ws, ws_bytes, stream, p))) return s;
+    p.x = x; p.y = y; p.ldx = ldx; p.ldy = ldy;
+    p.ckpt = ckpt;
+    p.ckpt_lazy = lazy;
+    return run(p);
+}
+
 // Validation shared by the adjoint entry points; fills bp (all but the
 // gradient lists).
 tfx_status bwd_plan(const float *x, const float *gy, float *gx, int64_t C, int64_t N, int64_t ldx, int64_t ldg,
@@ -296,6 +311,35 @@ tfx_status backward(const tfx::BwdPlan &bp) {
     const hipError_t e = tfx::launch_backward(bp);
     if (e != hipSuccess) return hip_fail(e, "adjoint kernel launch");
     return ok();
+}
+
+tfx_status chain_backward_call(const float *x, const float *gy, float *gx, int64_t C, int64_t N, int64_t ldx, int64_t ldg,
+                               int64_t ldgx, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
+                               const float *ckpt, bool lazy, float *const *grads, void *ws, size_t ws_bytes,
+                               void *stream) {
+    Gathered g;
+    tfx_status s = gather(stages, nstages, g);
+    if (s) return s;
+    int32_t mode = tfx::FIR_NONE;
+    if (g.firs.n > 0 && (s = check_fir_mode(g.Mtot, cmp, TFX_FIR_AUTO, &mode, C, N, g.S == 0))) return s;
+    tfx::BwdPlan bp{};
+    if ((s = bwd_plan(x, gy, gx, C, N, ldx, ldg, ldgx, g, mode, ckpt, ws, ws_bytes, stream, bp))) return s;
+    bp.fwd.ckpt_lazy = lazy;
+    // gradient pointers in the order of the gathered stage lists
+    for (int i = 0; i < nstages; ++i) {
+        const tfx_stage &st = stages[i];
+        float *gp = grads ? grads[i] : nullptr;
+        if (st.kind == TFX_STAGE_FIR) {
+            bp.gfir.ptr[bp.gfir.n] = gp;
+            bp.gfir.len[bp.gfir.n] = st.len;
+            bp.gfir.n++;
+        } else if (st.len > 0) {
+            bp.gsos.ptr[bp.gsos.n] = gp;
+            bp.gsos.len[bp.gsos.n] = st.len;
+            bp.gsos.n++;
+        }
+    }
+    return backward(bp);
 }
 
 // Calls that synchronise (the tuners) are refused on a capturing stream.
@@ -484,13 +528,13 @@ tfx_status tfx_sos(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, 
 tfx_status tfx_chain(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
                      const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt, void *ws,
                      size_t ws_bytes, void *stream) {
-    tfx_status s = check_signal(x, y, C, N, ldx, ldy);
-    if (s) return s;
-    tfx::ChainPlan p{};
-    if ((s = chain_plan(C, N, stages, nstages, cmp, ws, ws_bytes, stream, p))) return s;
-    p.x = x; p.y = y; p.ldx = ldx; p.ldy = ldy;
-    p.ckpt = ckpt;
-    return run(p);
+    return chain_call(x, y, C, N, ldx, ldy, stages, nstages, cmp, ckpt, false, ws, ws_bytes, stream);
+}
+
+tfx_status tfx_chain_train(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
+                           const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt, void *ws,
+                           size_t ws_bytes, void *stream) {
+    return chain_call(x, y, C, N, ldx, ldy, stages, nstages, cmp, ckpt, true, ws, ws_bytes, stream);
 }
 
 tfx_status tfx_chain_prepare(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
@@ -558,35 +602,23 @@ tfx_status tfx_chain_backward_workspace_size(int64_t C, int64_t N, const tfx_sta
     if (s) return s;
     int32_t mode = tfx::FIR_NONE;
     if (g.firs.n > 0 && (s = check_fir_mode(g.Mtot, cmp, TFX_FIR_AUTO, &mode, C, N, g.S == 0))) return s;
-    *bytes = tfx::bwd_layout(C, N, g.S, g.Mtot, g.firs.n, mode).total;
+    *bytes = tfx::bwd_layout(C, N, g.S, g.Mtot, g.firs.n, mode).fwd.total_short;
     return ok();
 }
 
 tfx_status tfx_chain_backward(const float *x, const float *gy, float *gx, int64_t C, int64_t N, int64_t ldx,
                               int64_t ldg, int64_t ldgx, const tfx_stage *stages, int32_t nstages, tfx_compute cmp,
                               const float *ckpt, float *const *grads, void *ws, size_t ws_bytes, void *stream) {
-    Gathered g;
-    tfx_status s = gather(stages, nstages, g);
-    if (s) return s;
-    int32_t mode = tfx::FIR_NONE;
-    if (g.firs.n > 0 && (s = check_fir_mode(g.Mtot, cmp, TFX_FIR_AUTO, &mode, C, N, g.S == 0))) return s;
-    tfx::BwdPlan bp{};
-    if ((s = bwd_plan(x, gy, gx, C, N, ldx, ldg, ldgx, g, mode, ckpt, ws, ws_bytes, stream, bp))) return s;
-    // gradient pointers in the order of the gathered stage lists
-    for (int i = 0; i < nstages; ++i) {
-        const tfx_stage &st = stages[i];
-        float *gp = grads ? grads[i] : nullptr;
-        if (st.kind == TFX_STAGE_FIR) {
-            bp.gfir.ptr[bp.gfir.n] = gp;
-            bp.gfir.len[bp.gfir.n] = st.len;
-            bp.gfir.n++;
-        } else if (st.len > 0) {
-            bp.gsos.ptr[bp.gsos.n] = gp;
-            bp.gsos.len[bp.gsos.n] = st.len;
-            bp.gsos.n++;
-        }
-    }
-    return backward(bp);
+    return chain_backward_call(x, gy, gx, C, N, ldx, ldg, ldgx, stages, nstages, cmp, ckpt, false, grads, ws, ws_bytes,
+                               stream);
+}
+
+tfx_status tfx_chain_train_backward(const float *x, const float *gy, float *gx, int64_t C, int64_t N, int64_t ldx,
+                                    int64_t ldg, int64_t ldgx, const tfx_stage *stages, int32_t nstages,
+                                    tfx_compute cmp, float *ckpt, float *const *grads, void *ws, size_t ws_bytes,
+                                    void *stream) {
+    return chain_backward_call(x, gy, gx, C, N, ldx, ldg, ldgx, stages, nstages, cmp, ckpt, true, grads, ws, ws_bytes,
+                               stream);
 }
 
 tfx_status tfx_fir_backward_workspace_size(int64_t C, int64_t N, int32_t M, tfx_compute cmp, tfx_fir_algo algo,

@@ -52,6 +52,7 @@ struct BArgs {
     int64_t ntiles, cpad;
     int32_t vecf, vecg, veco;
     uint32_t xcd_ks;  // block order (xcd_order)
+    const uint32_t *gate;  // header of a chain whose short-memory adjoint ran before, or null (here and below)
 };
 
 // TDF-II section over a lane's chunk from state (s1, s2), in place.
@@ -83,9 +84,11 @@ __global__ __launch_bounds__(WG, 3) void sos_bwd_kernel(BArgs a) {
     __shared__ double s_red[2][GROUPS][GWAVES][5];
     __shared__ uint32_t s_epoch;
 
+    if (a.gate && short_done(a.gate)) return;
     if ((a.hdr[HDR_HIQ] != 0u) != HIQ) return;
     const int tid = threadIdx.x, lane = tid & 63, grp = tid / GL, gl = tid % GL, gw = gl >> 6;
-    if (tid == 0) s_epoch = load_epoch(a.hdr, HDR_EPOCH);
+    // (one on from the forward's, which may have left records of its own here)
+    if (tid == 0) s_epoch = (load_epoch(a.hdr, HDR_EPOCH) + 1u) & EPOCH_MASK;
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
     const uint64_t id = xcd_order(blockIdx.x, gridDim.x, a.xcd_ks);
     const int64_t pos = (int64_t)(id / npairs);  // reverse-time processing position
@@ -308,6 +311,7 @@ struct SosGradArgs {
     int64_t C, ntiles, cpad;
     double *sums;  // [S][5]
     GradList out;
+    const uint32_t *gate;
 };
 
 constexpr int RED_THREADS = 256;
@@ -343,6 +347,7 @@ __device__ double block_sum_fixed(double v, double *sh) {
 
 __global__ __launch_bounds__(RED_THREADS) void sos_grad_reduce_kernel(SosGradArgs a) {
     __shared__ double sh[RED_THREADS];
+    if (a.gate && short_done(a.gate)) return;
     const int64_t stride = a.cpad * a.ntiles;
     const int64_t n = a.C * a.ntiles;  // entries ch * ntiles + tile, ch < C
     const double *p = a.part + (int64_t)blockIdx.x * stride;  // block = 5 s + k
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(RED_THREADS) void sos_grad_reduce_kernel(SosGradArg
 
 __global__ void sos_grad_map_kernel(SosGradArgs a) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.S) return;
+    if (s >= a.S || (a.gate && short_done(a.gate))) return;
     double d[5];
     for (int k = 0; k < 5; ++k) d[k] = a.sums[5 * s + k];
     const double b0 = a.tab[s].coef[0], a1 = a.tab[s].coef[3], a2 = a.tab[s].coef[4];
@@ -386,6 +391,7 @@ struct GhArgs {
     int64_t cpad;
     const float2 *twid;
     float *part;  // [lag block][pair-tile block][1025]
+    const uint32_t *gate;
 };
 
 __global__ __launch_bounds__(WG) void fir_gh_part_kernel(GhArgs a) {
@@ -393,6 +399,7 @@ __global__ __launch_bounds__(WG) void fir_gh_part_kernel(GhArgs a) {
     __shared__ __align__(16) float lds[2 * NFFT];
     __shared__ __align__(16) float2 wspec[NFFT];
     __shared__ __align__(16) float2 s_twl[TWL_ENTRIES];
+    if (a.gate && short_done(a.gate)) return;
     const int tid = threadIdx.x;
     twl_stage(s_twl, a.twid, tid, WG);
     const int64_t npairs = a.cpad / 2;
@@ -453,11 +460,13 @@ struct FirBwdArgs {
     float2 *spart;  // [workgroup][16][256] summed spectra, bin 256 k3 + t at [k3][t]
     int32_t want_gh;
     uint32_t xcd_ks;  // item order (xcd_order over the item index)
+    const uint32_t *gate;
 };
 
 __global__ __launch_bounds__(WG) void fir_bwd_kernel(FirBwdArgs a) {
     __shared__ __align__(16) float lds[2 * NFFT];
     __shared__ __align__(16) float2 s_twl[TWL_ENTRIES];
+    if (a.gate && short_done(a.gate)) return;
     const int tid = threadIdx.x;
     twl_stage(s_twl, a.twid, tid, WG);  // visible after the first tile's barrier
     const int64_t npairs = a.cpad / 2, nitems = npairs * a.ntiles;
@@ -511,7 +520,9 @@ __global__ __launch_bounds__(WG) void fir_bwd_kernel(FirBwdArgs a) {
 constexpr int SPEC_SPLIT = 64;
 constexpr int FIR_BWD_WGS = 512;  // two per CU fit (about 230 VGPRs)
 
-__global__ void fir_spec_reduce1_kernel(const float2 *spart, int64_t nwg, double2 *sum1) {
+__global__ void fir_spec_reduce1_kernel(const float2 *spart, int64_t nwg, double2 *sum1,
+                                        const uint32_t *gate) {
+    if (gate && short_done(gate)) return;
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t w0 = (int64_t)blockIdx.y * SPEC_SPLIT;
     const int64_t w1 = min(nwg, w0 + SPEC_SPLIT);
@@ -525,7 +536,9 @@ __global__ void fir_spec_reduce1_kernel(const float2 *spart, int64_t nwg, double
     sum1[(int64_t)blockIdx.y * NFFT + f] = make_double2(sr, si);
 }
 
-__global__ void fir_spec_reduce2_kernel(const double2 *sum1, int32_t nsplit, double2 *spec) {
+__global__ void fir_spec_reduce2_kernel(const double2 *sum1, int32_t nsplit, double2 *spec,
+                                        const uint32_t *gate) {
+    if (gate && short_done(gate)) return;
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     double sr = 0.0, si = 0.0;
     for (int k = 0; k < nsplit; ++k) {
@@ -540,8 +553,10 @@ __global__ void fir_spec_reduce2_kernel(const double2 *sum1, int32_t nsplit, dou
 // k = 4 blockIdx.x + u, u < 4: thread t takes bins f = t + 256 j for all four
 // lags, then a fixed-order block sum per lag.
 constexpr int GH_DFT_LAGS = 4;
-__global__ void fir_gh_dft_kernel(const double2 *spec, const double2 *tw64, int32_t M, float *gh) {
+__global__ void fir_gh_dft_kernel(const double2 *spec, const double2 *tw64, int32_t M, float *gh,
+                                  const uint32_t *gate) {
     __shared__ double wsum[GH_DFT_LAGS][WG / 64];
+    if (gate && short_done(gate)) return;
     const int k0 = blockIdx.x * GH_DFT_LAGS, t = threadIdx.x;
     double acc[GH_DFT_LAGS] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
@@ -571,7 +586,9 @@ __global__ void fir_gh_dft_kernel(const double2 *spec, const double2 *tw64, int3
 // (sum1[split][k]), level 2 the splits in order.
 constexpr int GH_SPLIT = 128;
 
-__global__ void fir_gh_reduce1_kernel(const float *part, int32_t M, int64_t nparts, double *sum1) {
+__global__ void fir_gh_reduce1_kernel(const float *part, int32_t M, int64_t nparts, double *sum1,
+                                      const uint32_t *gate) {
+    if (gate && short_done(gate)) return;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= M) return;
     const int64_t i0 = (int64_t)blockIdx.y * GH_SPLIT;
@@ -581,7 +598,9 @@ __global__ void fir_gh_reduce1_kernel(const float *part, int32_t M, int64_t npar
     sum1[(int64_t)blockIdx.y * M + k] = strided_sum(p, (i1 - i0) * FFT_PART, 0, FFT_PART);
 }
 
-__global__ void fir_gh_reduce2_kernel(const double *sum1, int32_t M, int32_t nsplit, float *dst) {
+__global__ void fir_gh_reduce2_kernel(const double *sum1, int32_t M, int32_t nsplit, float *dst,
+                                      const uint32_t *gate) {
+    if (gate && short_done(gate)) return;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= M) return;
     dst[k] = (float)strided_sum(sum1 + k, (int64_t)nsplit * M, 0, M);
@@ -623,7 +642,6 @@ static size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode) {
     BwdLayout b{};
     b.fwd = ws_layout(C, N, S, M_merged, n_fir, fir_mode);
-    b.fwd.short_shape = false;
     const int64_t ntiles = b.fwd.ntiles, cpad = b.fwd.cpad, npairs = cpad / 2;
     // the forward layout ends with a 256-aligned total (or 0 when it needs nothing)
     size_t off = b.fwd.total ? b.fwd.total : 256;
@@ -670,6 +688,9 @@ BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t 
         }
     }
     b.total = off;
+    b.fwd.sh = off;
+    b.short_area = off + al256(fft16k_table_bytes() + sizeof(ShortTab));
+    b.fwd.total_short = b.fwd.short_shape ? b.short_area + short_bwd_bytes(C, N) : off;
     return b;
 }
 
@@ -694,7 +715,18 @@ hipError_t launch_backward(const BwdPlan &bp) {
     const float *h = has_fir ? (p.firs.n == 1 ? p.firs.ptr[0] : reinterpret_cast<const float *>(ws + lay.fwd.taps))
                              : nullptr;
     // tables, merged taps, spectrum; clears the look-back records
-    if ((e = launch_tables(p, lay.fwd, h, M)) != hipSuccess) return e;
+    const bool short_try = lay.fwd.short_shape && p.ws_bytes >= lay.fwd.total_short;
+    void *area = ws + lay.short_area;
+    if ((e = launch_tables(p, lay.fwd, h, M, short_try ? short_bwd_hf(area) : nullptr)) != hipSuccess) return e;
+    bool any = false;
+    for (int i = 0; i < bp.gfir.n; ++i) any = any || bp.gfir.ptr[i] != nullptr;
+    float *gH = !any ? nullptr : p.firs.n == 1 ? bp.gfir.ptr[0] : reinterpret_cast<float *>(ws + lay.gH);
+    uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.fwd.hdr);
+    const uint32_t *gate = short_try ? hdr : nullptr;
+    if (short_try &&
+        (e = launch_short_bwd(bp, M, ws + lay.fwd.sh, ws + (p.fir_mode == FIR_FFT16 ? lay.fwd.f16 : lay.fwd.sh), area, gH,
+                              hdr)) != hipSuccess)
+        return e;
     // the cascade input f and the gradient of the cascade input gf
     const float *f = p.x;
     int64_t ldf = p.ldx;
@@ -706,7 +738,7 @@ hipError_t launch_backward(const BwdPlan &bp) {
     if (has_fir && has_sos) {
         if (!fuse) {
             float *fb = reinterpret_cast<float *>(ws + lay.fbuf);
-            if ((e = launch_fir_pass(p, lay.fwd, p.x, p.ldx, fb, p.N, false)) != hipSuccess) return e;
+            if ((e = launch_fir_pass(p, lay.fwd, p.x, p.ldx, fb, p.N, false, gate)) != hipSuccess) return e;
             f = fb;
             ldf = p.N;
         }
@@ -715,7 +747,12 @@ hipError_t launch_backward(const BwdPlan &bp) {
     }
     const int64_t ntiles = lay.fwd.ntiles, cpad = lay.fwd.cpad, npairs = cpad / 2;
     if (has_sos) {
+        // checkpoints that the forward of a short-memory chain has left out
+        if (p.ckpt_lazy && lay.fwd.short_shape &&
+            (e = launch_ckpt(p, lay.fwd, f, ldf, bp.gx, bp.ldgx, !short_try)) != hipSuccess)
+            return e;
         BArgs b{};
+        b.gate = gate;
         b.f = f;
         b.g = bp.gy;
         b.gf = has_fir ? gf : bp.gx;
@@ -729,7 +766,7 @@ hipError_t launch_backward(const BwdPlan &bp) {
         b.ckpt = p.ckpt;
         b.part = reinterpret_cast<double *>(ws + lay.part_sos);
         b.recs = reinterpret_cast<uint64_t *>(ws + lay.fwd.recs);
-        b.hdr = reinterpret_cast<uint32_t *>(ws + lay.fwd.hdr);
+        b.hdr = hdr;
         b.ntiles = ntiles;
         b.cpad = cpad;
         b.vecf = (reinterpret_cast<uintptr_t>(b.f) % 16 == 0 && b.ldf % 4 == 0) ? 1 : 0;
@@ -755,6 +792,7 @@ hipError_t launch_backward(const BwdPlan &bp) {
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         SosGradArgs r{};
+        r.gate = gate;
         r.part = b.part;
         r.tab = b.tab;
         r.S = p.S;
@@ -771,13 +809,11 @@ hipError_t launch_backward(const BwdPlan &bp) {
     if (!has_fir) return hipSuccess;
     const float *gfc = has_sos ? gf : bp.gy;
     const int64_t ldgfc = has_sos ? ldgf : bp.ldg;
-    bool any = false;
-    for (int i = 0; i < bp.gfir.n; ++i) any = any || bp.gfir.ptr[i] != nullptr;
-    float *gH = p.firs.n == 1 ? bp.gfir.ptr[0] : reinterpret_cast<float *>(ws + lay.gH);
     if (lay.spec_path) {
         // input gradient and tap-gradient spectra in one pass, then the
         // fixed-order reductions and the inverse DFT per lag
         FirBwdArgs fb{};
+        fb.gate = gate;
         fb.x = p.x;
         fb.g = gfc;
         fb.gx = bp.gx;
@@ -799,20 +835,21 @@ hipError_t launch_backward(const BwdPlan &bp) {
         double2 *sum1 = reinterpret_cast<double2 *>(ws + lay.gh1);
         double2 *spec = reinterpret_cast<double2 *>(ws + lay.spec);
         hipLaunchKernelGGL(fir_spec_reduce1_kernel, dim3(NFFT / 256, (unsigned)lay.spec_nsplit), dim3(256), 0, st,
-                           static_cast<const float2 *>(fb.spart), lay.spec_wg, sum1);
+                           static_cast<const float2 *>(fb.spart), lay.spec_wg, sum1, gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(fir_spec_reduce2_kernel, dim3(NFFT / 256), dim3(256), 0, st,
-                           static_cast<const double2 *>(sum1), (int32_t)lay.spec_nsplit, spec);
+                           static_cast<const double2 *>(sum1), (int32_t)lay.spec_nsplit, spec, gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(fir_gh_dft_kernel, dim3((unsigned)((M + GH_DFT_LAGS - 1) / GH_DFT_LAGS)), dim3(WG), 0, st,
                            static_cast<const double2 *>(spec), reinterpret_cast<const double2 *>(ws + lay.fwd.tw64),
-                           M, gH);
+                           M, gH, gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         // input gradient: correlation of the cascade-input gradient with the taps
-        if ((e = launch_fir_pass(p, lay.fwd, gfc, ldgfc, bp.gx, bp.ldgx, true)) != hipSuccess) return e;
+        if ((e = launch_fir_pass(p, lay.fwd, gfc, ldgfc, bp.gx, bp.ldgx, true, gate)) != hipSuccess) return e;
         if (!any) return hipSuccess;
         GhArgs g{};
+        g.gate = gate;
         g.x = p.x;
         g.g = gfc;
         g.C = p.C;
@@ -836,10 +873,10 @@ hipError_t launch_backward(const BwdPlan &bp) {
         const int32_t nsplit = (int32_t)((nbx + GH_SPLIT - 1) / GH_SPLIT);
         double *sum1 = reinterpret_cast<double *>(ws + lay.gh1);
         hipLaunchKernelGGL(fir_gh_reduce1_kernel, dim3((unsigned)((M + 255) / 256), (unsigned)nsplit), dim3(256), 0,
-                           st, static_cast<const float *>(g.part), M, nbx, sum1);
+                           st, static_cast<const float *>(g.part), M, nbx, sum1, gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(fir_gh_reduce2_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const double *>(sum1), M, nsplit, gH);
+                           static_cast<const double *>(sum1), M, nsplit, gH, gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (p.firs.n == 1) return hipSuccess;

@@ -111,8 +111,13 @@ struct KArgs {
     const float *hist;    // streaming: the M - 1 FIR inputs before the block, [C][M - 1] (null = zeros)
     int64_t ldh;          // M - 1
     uint32_t xcd_ks;      // block order: xcd_order's log2 K (0 = block ids in order)
-    int32_t after_short;  // the short-memory kernel ran before this one: nothing to do if it did the work
+    int32_t after_short;  // the short-memory kernel ran before this one: nothing to do if it did the work (2: nor
+                          // if the chain is not a short-memory one)
 };
+
+__device__ __forceinline__ bool short_skip(const KArgs &a) {
+    return a.after_short && (short_done(a.hdr) || (a.after_short == 2 && a.hdr[HDR_SHORT] == 0u));
+}
 
 // FIR input x[ch][n] of the block, n < N, with the streaming history for
 // n in [-(M - 1), 0) and zeros before it.
@@ -618,7 +623,7 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
     // for both)
     float2 *s_twl = reinterpret_cast<float2 *>(s_dyn);
 
-    if (HAS_SOS && a.after_short && short_done(a.hdr)) return;
+    if (HAS_SOS && short_skip(a)) return;
     if (HAS_SOS && (a.hdr[HDR_HIQ] != 0u) != HIQ) {  // the other variant runs
         advance_epoch(a.hdr);
         return;
@@ -812,7 +817,7 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
     __shared__ __align__(16) float lds[mc_lds_floats<FIRM>()];
     __shared__ uint32_t s_epoch;
     __shared__ __align__(16) float2 s_twl[FIRM == FIR_FFT ? TWL_ENTRIES : 2];  // the transforms' twiddles
-    if (a.after_short && short_done(a.hdr)) return;
+    if (short_skip(a)) return;
     if (a.hdr[HDR_HIQ] != 0u) {  // the FP64-carry variant runs
         advance_epoch(a.hdr);
         return;
@@ -937,7 +942,7 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
 hipError_t launch_state_passthrough(const float *in, float *out, int64_t n, hipStream_t st);
 
 template <int F, bool S, bool STOUT>
-static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t st) {
+static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t st, bool hiq = true) {
     // (with the FFT FIR the dynamic area first holds the twiddles)
     constexpr size_t twl = (F == FIR_FFT || F == FIR_FFT_PARTS) ? sizeof(float2) * TWL_ENTRIES : 0;
     const size_t dyn = std::max(twl, S ? sizeof(SecLds) * (size_t)(k.S < LDS_SECTIONS ? k.S : LDS_SECTIONS) : 0);
@@ -957,7 +962,7 @@ static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t s
     }
     hipError_t e = hipGetLastError();
     if constexpr (S) {
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || !hiq) return e;
         hipLaunchKernelGGL((chain_kernel<F, S, true, false, STOUT>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
         e = hipGetLastError();
     }
@@ -1051,7 +1056,8 @@ hipError_t launch_run(const ChainPlan &p) {
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     // a chain that may be a short-memory one, with nothing asked for that only
     // the scan gives (checkpoints, registers, a stream's history)
-    const bool short_try = lay.short_shape && p.ws_bytes >= lay.total_short && !p.n_layout && !p.ckpt && !p.state_in &&
+    const bool short_try = lay.short_shape && p.ws_bytes >= lay.total_short && !p.n_layout &&
+                           (!p.ckpt || p.ckpt_lazy) && !p.state_in &&
                            !p.state_out && !p.hist_in && !p.hist_out;
     if (short_try) {
         const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot, ws + lay.sh,
@@ -1129,12 +1135,12 @@ hipError_t launch_run(const ChainPlan &p) {
 }
 
 hipError_t launch_fir_pass(const ChainPlan &p, const WsLayout &lay, const float *in, int64_t ldin, float *out,
-                           int64_t ldout, bool correlate) {
+                           int64_t ldout, bool correlate, const uint32_t *gate) {
     const int32_t Mtot = merged_taps(p.firs);
     if (p.N == 0 || Mtot == 0) return hipSuccess;
     char *ws = static_cast<char *>(p.ws);
     if (p.fir_mode == FIR_FFT16)
-        return launch_fft16k(in, out, p.C, p.N, ldin, ldout, Mtot, ws + lay.f16, correlate, nullptr, nullptr,
+        return launch_fft16k(in, out, p.C, p.N, ldin, ldout, Mtot, ws + lay.f16, correlate, nullptr, gate,
                              p.stream);
     KArgs k{};
     k.x = in;
@@ -1161,6 +1167,41 @@ hipError_t launch_fir_pass(const ChainPlan &p, const WsLayout &lay, const float 
     if (p.fir_mode == FIR_FFT && k.nparts > 1) return launch_main<FIR_FFT_PARTS, false>(k, nblocks, p.stream);
     return p.fir_mode == FIR_FFT ? launch_main<FIR_FFT, false>(k, nblocks, p.stream)
                                  : launch_main<FIR_DIRECT, false>(k, nblocks, p.stream);
+}
+
+hipError_t launch_ckpt(const ChainPlan &p, const WsLayout &lay, const float *in, int64_t ldin, float *out, int64_t ldout,
+                       bool always) {
+    char *ws = static_cast<char *>(p.ws);
+    KArgs k{};
+    k.x = in;
+    k.y = out;
+    k.C = p.C;
+    k.N = p.N;
+    k.ldx = ldin;
+    k.ldy = ldout;
+    const bool fft = p.fir_mode == FIR_FFT;  // else in is the FIR's output
+    k.M = fft ? merged_taps(p.firs) : 0;
+    k.h = taps_ptr(p, lay);
+    k.S = p.S;
+    k.ckpt = p.ckpt;
+    k.ntiles = lay.ntiles;
+    k.cpad = lay.cpad;
+    k.hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
+    k.tab = reinterpret_cast<const SecTab *>(ws + lay.tab);
+    k.recs = reinterpret_cast<uint64_t *>(ws + lay.recs);
+    k.vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0 && ldin % 4 == 0 &&
+             ldout % 4 == 0) ? 1 : 0;
+    k.twid = reinterpret_cast<const float2 *>(ws + lay.twid);
+    k.hspec = reinterpret_cast<const float2 *>(ws + lay.hspec);
+    k.nparts = 1;
+    k.casc = reinterpret_cast<const CascTab *>(ws + lay.casc);
+    k.zir = reinterpret_cast<const CascZir *>(ws + lay.zir);
+    k.mc = reinterpret_cast<const McTab *>(ws + lay.mc);
+    k.xcd_ks = xcd_window(lay.cpad / 2);
+    k.after_short = always ? 0 : 2;
+    const int64_t nblocks = (lay.cpad / 2) * lay.ntiles;
+    return fft ? launch_variants<FIR_FFT, true, false>(k, nblocks, p.stream, false)
+               : launch_variants<FIR_NONE, true, false>(k, nblocks, p.stream, false);
 }
 
 }  // namespace tfx

@@ -330,6 +330,45 @@ __device__ __forceinline__ void load_block(float (&z)[R], const float *x, int64_
     }
 }
 
+// The tile x[n0 .. n0 + cnt), up to N, zero-padded to a block (cnt a multiple of
+// 64: a wave's 64 values are inside the tile or not together).
+__device__ __forceinline__ void load_tile(float (&z)[R], const float *x, int64_t n0, int cnt, int64_t N, int t) {
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int c64 = cnt >> 6;
+    const float *p = x + n0 + t;
+    if (n0 + cnt <= N) {
+#pragma unroll
+        for (int a = 0; a < R; ++a) z[a] = 8 * a + w < c64 ? p[512 * a] : 0.f;
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < R; ++a) z[a] = (8 * a + w < c64 && n0 + 512 * a + t < N) ? p[512 * a] : 0.f;
+}
+
+// Memory V of the chain of an M-tap FIR and the cascade (M - 1 and the length of
+// the cascade's response that the decay sums prove, rounded up to 64), or 0
+// when the sums prove none up to FFT16_MEM.  By a whole wave, the same in each.
+__device__ __forceinline__ int short_memory(const ShortTab *st, int32_t M, int lane) {
+    const int j = lane & 3;
+    const double lam = st->lam[j];
+    double s = st->sum[lane >> 2][j];
+#pragma unroll
+    for (int d = 4; d < 64; d <<= 1) s += __shfl_xor(s, d);
+    const double unit = __shfl(s, 0);
+    // (false for a NaN, for an unstable cascade and for one with FP64 carry)
+    float len = 1e9f;
+    if (lam < 0.0 && unit < 1e300 && s < 1e300) {
+        const float r = (float)(unit / s);
+        if (r > 0.f) len = fmaxf((SHORT_LOG2_EPS + 0.5f * log2f(r)) / (float)lam, 0.f);
+        else if (unit == 0.0) len = 0.f;
+    }
+#pragma unroll
+    for (int d = 1; d < 4; d <<= 1) len = fminf(len, __shfl_xor(len, d));
+    if (!(len <= (float)FFT16_MEM)) return 0;
+    const int V = (M - 1 + (int)len + 1 + 63) & ~63;
+    return __builtin_amdgcn_readfirstlane(V <= FFT16_MEM ? V : 0);
+}
+
 // Stores the block's values i in [lo, lo + cnt) to y[n0 + i - lo], up to N.
 // lo and cnt are multiples of 64: a wave's 64 values are stored or not
 // together (scalar tests).

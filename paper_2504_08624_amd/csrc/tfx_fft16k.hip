@@ -63,30 +63,6 @@ __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
 }
 
-// Memory V of the chain of an M-tap FIR and the cascade (M - 1 and the length of
-// the cascade's response that the decay sums prove, rounded up to 64), or 0
-// when the sums prove none up to FFT16_MEM.  By a whole wave, the same in each.
-__device__ __forceinline__ int short_memory(const ShortTab *st, int32_t M, int lane) {
-    const int j = lane & 3;
-    const double lam = st->lam[j];
-    double s = st->sum[lane >> 2][j];
-#pragma unroll
-    for (int d = 4; d < 64; d <<= 1) s += __shfl_xor(s, d);
-    const double unit = __shfl(s, 0);
-    // (false for a NaN, for an unstable cascade and for one with FP64 carry)
-    float len = 1e9f;
-    if (lam < 0.0 && unit < 1e300 && s < 1e300) {
-        const float r = (float)(unit / s);
-        if (r > 0.f) len = fmaxf((SHORT_LOG2_EPS + 0.5f * log2f(r)) / (float)lam, 0.f);
-        else if (unit == 0.0) len = 0.f;
-    }
-#pragma unroll
-    for (int d = 1; d < 4; d <<= 1) len = fminf(len, __shfl_xor(len, d));
-    if (!(len <= (float)FFT16_MEM)) return 0;
-    const int V = (M - 1 + (int)len + 1 + 63) & ~63;
-    return __builtin_amdgcn_readfirstlane(V <= FFT16_MEM ? V : 0);
-}
-
 // A short-memory chain (FIR and cascade as one filter of memory V; the grid is
 // sized for the longest memory).  The same two
 // transforms a block as above.  A value that is not finite marks the run, and

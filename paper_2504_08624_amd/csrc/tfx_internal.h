@@ -222,6 +222,7 @@ struct ChainPlan {
     const float *state_in;
     float *state_out;
     float *ckpt;
+    bool ckpt_lazy;   // ckpt only serves launch_backward, which does without it for a short-memory chain
     const float *hist_in;   // streaming: FIR inputs before the block, [C][M - 1] (null = zeros)
     float *hist_out;        // streaming: receives the last M - 1 inputs up to the block's end
     int64_t n_layout;       // block length the workspace layout was made for (0 = N)
@@ -269,12 +270,19 @@ uint32_t xcd_window(int64_t npairs);
 
 // Merged tap count of the FIR stages (each extra stage adds len - 1).
 int32_t merged_taps(const StageList &f);
-// The kernels of the prepare step into the workspace described by lay.
-hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h, int32_t M);
+// The kernels of the prepare step into the workspace described by lay (hf: the
+// adjoint's FP64 FIR response, or null).
+hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h, int32_t M, void *hf = nullptr);
 // FIR part of a prepared chain alone over (in -> out): convolution with the
 // merged taps, or correlation with them (the FIR adjoint) when correlate.
+// (gate: as hdr of launch_fft16k.)
 hipError_t launch_fir_pass(const ChainPlan &p, const WsLayout &lay, const float *in, int64_t ldin, float *out,
-                           int64_t ldout, bool correlate);
+                           int64_t ldout, bool correlate, const uint32_t *gate = nullptr);
+// The forward's fp32 scan again for its checkpoints (p.ckpt), from the chain
+// input (FFT FIR) or its FIR's output, where the adjoint of a short-memory chain
+// met a value that is not finite (always: in any case); out is scratch.
+hipError_t launch_ckpt(const ChainPlan &p, const WsLayout &lay, const float *in, int64_t ldin, float *out, int64_t ldout,
+                       bool always);
 
 // ---- matrix-core block-Toeplitz FIR (tfx_toeplitz.hip) --------------------------
 int32_t toeplitz_lags(int32_t M);
@@ -385,8 +393,18 @@ struct BwdLayout {
     // (spec_wg workgroups, spec_split of them per first-level sum)
     bool spec_path;
     int64_t spec_wg, spec_nsplit;
+    size_t short_area;  // short-memory adjoint's buffers (in fwd.total_short bytes, the whole workspace)
 };
 BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode);
 hipError_t launch_backward(const BwdPlan &p);
+
+// ---- adjoint of a short-memory chain (tfx_short_bwd.hip) ------------------------
+size_t short_bwd_bytes(int64_t C, int64_t N);
+void *short_bwd_hf(void *area);  // where the prepare step leaves the FIR's response in FP64
+// gx and the gradients (gH: of the merged taps, null: not wanted) of a chain
+// prepared with tab / tw as in launch_short16k, if it is a short-memory one;
+// area: short_bwd_bytes.
+hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const void *tw, void *area, float *gH,
+                            uint32_t *hdr);
 
 }  // namespace tfx

@@ -810,7 +810,7 @@ hipError_t launch_batch_prepare(const BatchLayout &lay, int lc, int32_t nclips, 
     return hipGetLastError();
 }
 
-hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h, int32_t M) {
+hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h, int32_t M, void *hf) {
     char *ws = static_cast<char *>(p.ws);
     hipError_t e;
     if (p.firs.n > 1) {
@@ -852,6 +852,7 @@ hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h
         if (!a.tw16) a.tw16 = reinterpret_cast<float2 *>(ws + lay.sh);
         a.ht16 = reinterpret_cast<float2 *>(ws + lay.sh) + f16k::TW_FLOAT2;
         a.st16 = reinterpret_cast<ShortTab *>(ws + lay.sh + fft16k_table_bytes());
+        a.hf16 = static_cast<double2 *>(hf);
         a.n16 = SPEC16_BLOCKS + CIRC_BLOCKS;
     }
     nb += a.n16;

@@ -205,7 +205,7 @@ def _stages(stages, device):
     return kept, desc
 
 
-def _chain_raw(x: torch.Tensor, stages, compute: str = "f32", return_ckpt: bool = False):
+def _chain_raw(x: torch.Tensor, stages, compute: str = "f32", return_ckpt: bool = False, train: bool = False):
     x2, squeeze, ld = _signal(x)
     C, N = x2.shape
     kept, desc = _stages(stages, x.device)
@@ -219,7 +219,7 @@ def _chain_raw(x: torch.Tensor, stages, compute: str = "f32", return_ckpt: bool 
     nb = lib.size_out()
     lib.call("tfx_chain_workspace_size", C, N, arr, len(desc), lib.COMPUTE[compute], nb)
     ws, wsb = _workspace(nb.value, x.device)
-    lib.call("tfx_chain", _ptr(x2), _ptr(y), C, N, ld, max(N, 1), arr, len(desc),
+    lib.call("tfx_chain_train" if train else "tfx_chain", _ptr(x2), _ptr(y), C, N, ld, max(N, 1), arr, len(desc),
              lib.COMPUTE[compute], _ptr(ck), _ptr(ws), wsb, _stream(x.device))
     _track(ws, wsb, x.device)
     del kept
@@ -276,6 +276,10 @@ def chain_backward(x: torch.Tensor, gy: torch.Tensor, stages, ckpt, compute: str
     """(dL/dx, [dL/dcoef of every stage]) of y = chain(x, stages) given gy
     and the forward's checkpoints (``chain(..., return_ckpt=True)``; None when
     the chain has no SOS stage)."""
+    return _chain_backward(x, gy, stages, ckpt, compute, need_coef, "tfx_chain_backward")
+
+
+def _chain_backward(x, gy, stages, ckpt, compute, need_coef, entry):
     x2, squeeze, ld = _signal(x)
     g2, _, ldg = _signal(gy)
     C, N = x2.shape
@@ -290,7 +294,7 @@ def chain_backward(x: torch.Tensor, gy: torch.Tensor, stages, ckpt, compute: str
     nb = lib.size_out()
     lib.call("tfx_chain_backward_workspace_size", C, N, arr, len(desc), lib.COMPUTE[compute], nb)
     ws, wsb = _workspace(nb.value, x.device)
-    lib.call("tfx_chain_backward", _ptr(x2), _ptr(g2), _ptr(gx), C, N, ld, ldg, max(N, 1), arr, len(desc),
+    lib.call(entry, _ptr(x2), _ptr(g2), _ptr(gx), C, N, ld, ldg, max(N, 1), arr, len(desc),
              lib.COMPUTE[compute], _ptr(ck), parr, _ptr(ws), wsb, _stream(x.device))
     _track(ws, wsb, x.device)
     del kept
@@ -351,7 +355,7 @@ class _ChainFn(torch.autograd.Function):
         stages = list(zip(kinds, coefs))
         has_sos = any(k == "sos" for k in kinds)
         if has_sos:
-            y, ck = _chain_raw(x, stages, compute, return_ckpt=True)
+            y, ck = _chain_raw(x, stages, compute, return_ckpt=True, train=True)
         else:
             y, ck = _chain_raw(x, stages, compute), None
         ctx.kinds, ctx.compute = kinds, compute
@@ -363,8 +367,8 @@ class _ChainFn(torch.autograd.Function):
     def backward(ctx, gy):
         x, ck, *coefs = ctx.saved_tensors
         need_coef = any(ctx.needs_input_grad[3:])
-        gx, grads = chain_backward(x, gy.contiguous(), list(zip(ctx.kinds, coefs)), ck if ctx.has_ck else None,
-                                   ctx.compute, need_coef)
+        gx, grads = _chain_backward(x, gy.contiguous(), list(zip(ctx.kinds, coefs)), ck if ctx.has_ck else None,
+                                    ctx.compute, need_coef, "tfx_chain_train_backward")
         out = [None, None, gx if ctx.needs_input_grad[2] else None]
         for c, g, need in zip(coefs, grads, ctx.needs_input_grad[3:]):
             out.append(g.reshape(c.shape) if (need and g is not None) else None)

@@ -65,6 +65,8 @@ _SIGS = {
     "tfx_sos": (_i32, [_vp, _vp, _i64, _i64, _i64, _i64, _vp, _i32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "tfx_chain": (_i32, [_vp, _vp, _i64, _i64, _i64, _i64, ctypes.POINTER(Stage), _i32, _i32, _vp, _vp, _sz,
                          _vp]),
+    "tfx_chain_train": (_i32, [_vp, _vp, _i64, _i64, _i64, _i64, ctypes.POINTER(Stage), _i32, _i32, _vp, _vp, _sz,
+                               _vp]),
     "tfx_chain_noalloc": (_i32, [_vp, _vp, _i64, _i64, _i64, _i64, ctypes.POINTER(Stage), _i32, _i32, _vp, _vp,
                                  _vp]),
     "tfx_chain_prepare": (_i32, [_i64, _i64, ctypes.POINTER(Stage), _i32, _i32, _vp, _sz, _vp]),
@@ -76,6 +78,8 @@ _SIGS = {
                                                  ctypes.POINTER(_sz)]),
     "tfx_chain_backward": (_i32, [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, ctypes.POINTER(Stage), _i32,
                                   _i32, _vp, ctypes.POINTER(_vp), _vp, _sz, _vp]),
+    "tfx_chain_train_backward": (_i32, [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, ctypes.POINTER(Stage), _i32,
+                                        _i32, _vp, ctypes.POINTER(_vp), _vp, _sz, _vp]),
     "tfx_fir_backward_workspace_size": (_i32, [_i64, _i64, _i32, _i32, _i32, ctypes.POINTER(_sz)]),
     "tfx_fir_backward": (_i32, [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, _vp, _i32, _vp, _i32, _i32, _vp,
                                 _sz, _vp]),

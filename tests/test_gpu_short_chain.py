@@ -17,6 +17,7 @@ from tests.metrics import TOL_FIR_F32, TOL_IIR_F32, assert_close
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
+TOL_GRAD = 1e-4    # every gradient's bar, relative over each tensor
 WORK = 10_000_000  # samples times sections from which the form is taken
 
 
@@ -153,7 +154,15 @@ def test_values_that_are_not_finite(bad, M):
     want_b, want_c = _scan(xb, st), _scan(xc, st)
     assert not bool(torch.isfinite(want_b).all())
     got_c = tfx.chain(xc, st)
-    assert _same(tfx.chain(xb, st), want_b)
+
+    # how many tiles behind it a bad sample reaches is up to which of the scan's
+    # records are out when a tile looks: two runs of the scan may differ there
+    def same_b(y):
+        lo, hi = 800_000 - 40_000, 800_000 + 40_000 + 30 * 3072
+        return _same(y[:, :lo], want_b[:, :lo]) and _same(y[:, hi:], want_b[:, hi:]) and \
+            _same(torch.isfinite(y[:, 800_000:802_000]).float(), torch.isfinite(want_b[:, 800_000:802_000]).float())
+
+    assert same_b(tfx.chain(xb, st))
     assert_close(_cpu(got_c), _cpu(want_c).astype(np.float64), TOL_IIR_F32, "clean")
     # several runs on one prepared workspace
     kept, desc = _stages(st, torch.device(DEV))
@@ -164,10 +173,10 @@ def test_values_that_are_not_finite(bad, M):
     y = torch.empty_like(xb)
     sp = torch.cuda.current_stream().cuda_stream
     lib.call("tfx_chain_prepare", C, N, arr, len(desc), 0, ws.data_ptr(), nb.value, sp)
-    for x, want in ((xc, got_c), (xb, want_b), (xb, want_b), (xc, got_c), (xb, want_b), (xc, got_c)):
+    for x, bad_run in ((xc, 0), (xb, 1), (xb, 1), (xc, 0), (xb, 1), (xc, 0)):
         lib.call("tfx_chain_run", x.data_ptr(), y.data_ptr(), C, N, N, N, arr, len(desc), 0, None, ws.data_ptr(),
                  nb.value, sp)
-        assert _same(y, want)
+        assert same_b(y) if bad_run else _same(y, got_c)
 
 
 def test_graph_replays():
@@ -193,4 +202,123 @@ def test_graph_replays():
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
-        assert _same(y, tfx.chain(x, st))
+        w = tfx.chain(x, st)
+        assert _same(y, w) if k != 2 else _same(y[:, 200_000:], w[:, 200_000:]) and bool(torch.isnan(y[0, 5]))
+
+
+# ------------------------------------------------------------------ the adjoint
+
+def _grads(x, g, coefs, kinds, need=None):
+    """Autograd's gradients of the chain (None where not needed)."""
+    need = need or [True] * (1 + len(coefs))
+    ts = [t.clone().requires_grad_(n) for t, n in zip([x] + coefs, need)]
+    tfx.chain(ts[0], list(zip(kinds, ts[1:]))).backward(g)
+    return [t.grad for t in ts]
+
+
+def _scan_backward(x, g, stages):
+    """The adjoint by the scan: checkpoints, and a workspace without the room the
+    other form wants."""
+    _, ck = tfx.chain(x, stages, return_ckpt=True)
+    C, N = x.shape
+    kept, desc = _stages(stages, torch.device(DEV))
+    arr = lib.stage_array(desc)
+    nb = lib.size_out()
+    lib.call("tfx_chain_backward_workspace_size", C, N, arr, len(desc), 0, nb)
+    ws = torch.zeros(nb.value, dtype=torch.uint8, device=DEV)
+    gx = torch.empty_like(x)
+    gs = [torch.empty_like(t) for t in kept]
+    lib.call("tfx_chain_backward", x.data_ptr(), g.data_ptr(), gx.data_ptr(), C, N, N, N, N, arr, len(desc), 0,
+             ck.data_ptr(), lib.pointer_array([t.data_ptr() for t in gs]), ws.data_ptr(), nb.value - 256,
+             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return [gx] + gs
+
+
+def _rel(a, b):
+    return np.linalg.norm(_cpu(a).astype(np.float64).ravel() - np.ravel(b)) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("S", [1, 2, 7, 8])
+@pytest.mark.parametrize("M", [49, 1025, 2049])
+def test_gradients_against_oracle(S, M):
+    C = 3
+    N = WORK // (S * C) + 33
+    print("short adjoint S=%d M=%d N=%d" % (S, M, N), flush=True)
+    x = _x(C, N, (811, S, M))
+    h = design.fir_lowpass(M, 9000.0, 48000.0).astype(np.float32)
+    sec = _eq(S, M)
+    # a residual correlated with the output, as a loss gives
+    g = (np.roll(x, 3, axis=1) + 0.1 * _x(C, N, (812, S, M), 1.0)).astype(np.float32)
+    got = _grads(_gpu(x), _gpu(g), [_gpu(h), _gpu(sec)], ["fir", "sos"])
+    rgx, (rgh, rgs) = O.chain_backward(g, x, [("fir", h), ("sos", sec)])
+    assert_close(_cpu(got[0]), rgx, TOL_FIR_F32, "dL/dx")
+    for a, b, what in ((got[1], rgh, "dL/dh"), (got[2], rgs, "dL/dsos")):
+        e = _rel(a, b)
+        print("%s rel err %.2e" % (what, e), flush=True)
+        assert e <= TOL_GRAD, "%s rel err %.3e" % (what, e)
+
+
+def test_gradients_of_several_stages():
+    """Two FIR and two section stages in mixed order, all gradients and some."""
+    C, N = 2, 1_300_001
+    x, g = _x(C, N, (813,)), _x(C, N, (814,))
+    g = (g + np.roll(x, 1, axis=1)).astype(np.float32)
+    coefs = [_eq(2, 1), design.fir_lowpass(100, 9000.0, 48000.0).astype(np.float32), _eq(3, 2),
+             design.fir_lowpass(33, 12000.0, 48000.0).astype(np.float32)]
+    kinds = ["sos", "fir", "sos", "fir"]
+    xg, gg, cg = _gpu(x), _gpu(g), [_gpu(c) for c in coefs]
+    got = _grads(xg, gg, cg, kinds)
+    rgx, refs = O.chain_backward(g, x, list(zip(kinds, coefs)))
+    assert_close(_cpu(got[0]), rgx, TOL_FIR_F32, "dL/dx")
+    for i, (a, b) in enumerate(zip(got[1:], refs)):
+        assert _rel(a, b) <= TOL_GRAD, "stage %d" % i
+    some = _grads(xg, gg, cg, kinds, [True, False, True, False, False])
+    assert torch.equal(some[0], got[0]) and torch.equal(some[2], got[2]) and some[1] is None
+    only = _grads(xg, gg, cg, kinds, [True, False, False, False, False])
+    assert torch.equal(only[0], got[0])
+    coef = _grads(xg, gg, cg, kinds, [False, True, True, True, True])
+    assert all(torch.equal(a, b) for a, b in zip(coef[1:], got[1:]))
+
+
+@pytest.mark.parametrize("M", [255, 1500])
+@pytest.mark.parametrize("where", ["x", "g"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_gradients_of_values_that_are_not_finite(bad, where, M):
+    C, N = 3, 1_700_011
+    x, g = _gpu(_x(C, N, (815,))), _gpu(_x(C, N, (816,)))
+    h, sec = _gpu(design.fir_lowpass(M, 9000.0, 48000.0).astype(np.float32)), _gpu(_eq(2, 3))
+    clean = _grads(x, g, [h, sec], ["fir", "sos"])
+    (x if where == "x" else g)[1, 900_000] = bad
+    got = _grads(x, g, [h, sec], ["fir", "sos"])
+    want = _scan_backward(x, g, [("fir", h), ("sos", sec)])
+    for a, b, c in zip(got[1:], want[1:], clean[1:]):
+        assert _same(torch.isfinite(a).float(), torch.isfinite(b).float()) and bool(torch.isfinite(c).all())
+    assert not bool(torch.isfinite(got[1]).all())
+    # how many tiles before it a bad sample of g reaches is up to which of the
+    # scan's records are out when a tile looks: between 30 tiles before and the
+    # next block after it two runs of the scan may differ
+    a, b = got[0], want[0]
+    lo, hi = 900_000 - 30 * 3072, 900_000 + 3 * 8192
+    assert _same(a[2], b[2]) and _same(a[:, :lo], b[:, :lo]) and _same(a[:, hi:], b[:, hi:])
+    assert bool(torch.isfinite(a[1, 900_000])) == bool(torch.isfinite(b[1, 900_000])) == (where == "x")
+
+
+def test_gradients_of_other_chains_and_explicit_checkpoints():
+    x, g = _gpu(_x(2, 2_600_000, (817,))), _gpu(_x(2, 2_600_000, (818,)))
+    h = _gpu(design.fir_lowpass(255, 9000.0, 48000.0).astype(np.float32))
+    rings = _gpu(np.array([[1, -1.99, 1, -1.995, 0.9956]] * 2, np.float32))
+    for sec, short in ((rings, False), (_gpu(_eq(2, 5)), True)):
+        st = [("fir", h), ("sos", sec)]
+        want = _scan_backward(x, g, st)
+        got = _grads(x, g, [h, sec], ["fir", "sos"])
+        gx, gs = tfx.chain_backward(x, g, st, _scan_ckpt(x, st))
+        for a, b, c in zip(got, want, [gx] + gs):
+            if short:                          # (two runs of the scan differ in their last bits for the other)
+                assert torch.equal(a, c) and not torch.equal(a, b)
+            for v in (a, c):
+                assert _rel(v, _cpu(b).astype(np.float64)) <= 2 * TOL_GRAD
+
+
+def _scan_ckpt(x, stages):
+    return tfx.chain(x, stages, return_ckpt=True)[1]

@@ -98,15 +98,27 @@ def istft(spec: torch.Tensor, n_fft: int, hop_length=None, win_length=None, wind
     total = n_fft + hop * (T - 1)
     start = n_fft // 2 if center else 0
     L = (total - 2 * (n_fft // 2) if center else total) if length is None else int(length)
-    wnp = np.ones(wl) if window is None else torch.as_tensor(window).detach().double().cpu().numpy()
-    full = np.zeros(n_fft)
-    full[(n_fft - wl) // 2:(n_fft - wl) // 2 + wl] = wnp
-    if _envelope_min(full * full, hop, T, start, min(start + L, total)) < 1e-11:
-        raise ValueError("window overlap-add is zero somewhere (NOLA fails)")
+    # a window on the device is fetched ahead of the kernel and looked at while
+    # that runs (waiting for it first left the device idle for a third of the call)
+    wsrc = None if window is None else torch.as_tensor(window).detach()
+    fetched = None
+    if wsrc is not None and wsrc.device.type == "cuda":
+        host = torch.empty(wsrc.shape, dtype=wsrc.dtype, pin_memory=True)
+        with torch.cuda.device(wsrc.device):
+            host.copy_(wsrc, non_blocking=True)
+            fetched = torch.cuda.Event()
+            fetched.record()
+        wsrc = host
     w = _window(window, wl, spec.device)
     y = torch.empty((C, L), dtype=torch.float32, device=spec.device)
     lib.call("tfx_istft", fm.data_ptr(), C, T, n_fft, hop, _ptr(w), wl, int(bool(center)), int(bool(normalized)),
              y.data_ptr() if L else None, L, max(L, 1), _stream(spec.device))
+    if fetched is not None:
+        fetched.synchronize()
+    full = np.zeros(n_fft)
+    full[(n_fft - wl) // 2:(n_fft - wl) // 2 + wl] = 1.0 if wsrc is None else wsrc.double().numpy()
+    if _envelope_min(full * full, hop, T, start, min(start + L, total)) < 1e-11:
+        raise ValueError("window overlap-add is zero somewhere (NOLA fails)")
     return y[0] if squeeze else y
 
 

@@ -11,9 +11,8 @@
 // block starts at the tile, the spectrum is conjugated, and the first T
 // outputs are the tile.
 //
-// Bound by its vector arithmetic and LDS traffic, not by HBM: per block two
-// transforms (tfx_fft16k.h) and the product, about 1700 lane operations per
-// 16 points.
+// Bound by its vector arithmetic, not by HBM: per block two transforms
+// (tfx_fft16k.h) and the product.
 #include <hip/hip_runtime.h>
 
 #include "tfx_fft16k.h"
@@ -40,7 +39,7 @@ struct F16Args {
 
 __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     __shared__ __align__(16) float P[PLANE];
-    __shared__ __align__(16) float2 twl[TW_FLOAT2];
+    __shared__ __align__(16) float2 twl[TW_LDS];
     if (a.gate && short_done(a.gate)) return;
     const int t = threadIdx.x;
     tw_stage(twl, a.tw, t);
@@ -55,9 +54,7 @@ __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     load_block(zr, xc, n0 - lead, a.N, hc, a.hlen, t);
     load_block(zi, xc, n1 - lead, a.N, hc, a.hlen, t);
     __syncthreads();  // the twiddle rows
-    forward(zr, zi, P, twl, t);
-    spec_mul(zr, zi, a.hs, t, a.correlate ? -1.f : 1.f);
-    inverse(zr, zi, P, twl, t);
+    convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
     float *yc = a.y + ch * a.ldy;
     store_block(zr, yc, n0, lead, T, a.N, t);
     if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
@@ -79,7 +76,7 @@ struct ShortArgs {
 
 __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     __shared__ __align__(16) float P[PLANE];
-    __shared__ __align__(16) float2 twl[TW_FLOAT2];
+    __shared__ __align__(16) float2 twl[TW_LDS];
     const int V = short_memory(a.st, a.M, threadIdx.x & 63), T = NB - V;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
@@ -96,9 +93,7 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     load_block(zr, xc, n0 - V, a.N, nullptr, 0, t);
     load_block(zi, xc, n1 - V, a.N, nullptr, 0, t);
     __syncthreads();  // the twiddle rows
-    forward(zr, zi, P, twl, t);
-    spec_mul(zr, zi, a.hs, t, 1.f);
-    inverse(zr, zi, P, twl, t);
+    convolve(zr, zi, a.hs, 1.f, P, twl, a.tw, t);
     float *yc = a.y + ch * a.ldy;
     store_block(zr, yc, n0, V, T, a.N, t);
     if (n1 < a.N) store_block(zi, yc, n1, V, T, a.N, t);

@@ -41,7 +41,7 @@ struct ShortBwdArgs {
 // 192 data registers a thread: one workgroup a CU.
 __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     __shared__ __align__(16) float P[PLANE];
-    __shared__ __align__(16) float2 twl[TW_FLOAT2];
+    __shared__ __align__(16) float2 twl[TW_LDS];
     const int t = threadIdx.x;
     const int V = short_memory(a.st, a.M, t & 63), T = NB - V;
     if (blockIdx.x == 0 && t == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
@@ -62,22 +62,21 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
         load_block(zr, gc, n0, a.N, nullptr, 0, t);
         load_block(zi, gc, n1, a.N, nullptr, 0, t);
         __syncthreads();  // the twiddle rows; the last unit's reads of P
-        forward(zr, zi, P, twl, t);
+        forward(zr, zi, P, twl, a.tw, t);
         if (a.want) {
             float xr[R], xi[R];
             const float *xc = a.x + ch * a.ldx;
             load_tile(xr, xc, n0, T, a.N, t);
             load_tile(xi, xc, n1, T, a.N, t);
             __syncthreads();  // the other waves' reads of their rows of P
-            forward(xr, xi, P, twl, t);
+            forward(xr, xi, P, twl, a.tw, t);
 #pragma unroll
             for (int k = 0; k < R; ++k) {  // += conj(X) B
                 ar[k] = fmaf(xr[k], zr[k], fmaf(xi[k], zi[k], ar[k]));
                 ai[k] = fmaf(xr[k], zi[k], fmaf(-xi[k], zr[k], ai[k]));
             }
         }
-        spec_mul(zr, zi, a.hs, t, -1.f);
-        inverse(zr, zi, P, twl, t);
+        product_inverse(zr, zi, a.hs, -1.f, P, twl, a.tw, t);
         float *oc = a.gx + ch * a.ldgx;
         store_block(zr, oc, n0, 0, T, a.N, t);
         if (n1 < a.N) store_block(zi, oc, n1, 0, T, a.N, t);

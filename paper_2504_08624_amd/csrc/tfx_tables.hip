@@ -460,17 +460,41 @@ __device__ void spec16_block(char *raw, const float *h, int32_t M, Co co_at, int
     auto &cs = sh.cs;
     const int q = tid & 127, hf2 = tid >> 7;
     if (ht && tid < S * 5) cs[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
-    // W_128^q (threads < 128), W^(q k1) (the others), then the twiddle row entry:
-    // one loop, so that the sine's code is there once
-    const int i = k1 * 256 + tid, row = i / f16k::TWS, kr = i % f16k::TWS;
-    const int mr = kr < f16k::R ? (row < 32 ? 16 * row : row - 32) * kr : 0;
+    // W_128^q (threads < 128), W^(q k1) (the others), then the twiddle table's
+    // entry: one loop, so that the sine's code is there once
+    const int i = k1 * 256 + tid;
+    int role = -1, m1 = 0, m2 = 0;  // entry's form (-1: none), its angle, the angle of the cosine it is divided by
+    if (i < f16k::TW_LDS) {
+        const int row = i / f16k::TWS, e = i % f16k::TWS;
+        role = e < f16k::R ? e >> 3 : 4;
+        m1 = 16 * row * e;
+        m2 = 16 * row * (e - 16);
+    } else if (i < f16k::TW_FLOAT2) {  // float4 of thread t: m = 1, 2, or 4, 8
+        const int f = i - f16k::TW_LDS, t = (f >> 1) & (f16k::WGB - 1);
+        role = 5;
+        m1 = ((t >> 4) + 32 * (t & 15)) << (2 * (f >> 10) + (f & 1));
+    }
+    double c1 = 0.0, s1 = 0.0;
 #pragma unroll 1
-    for (int r = 0; r < (i < f16k::TW_FLOAT2 ? 2 : 1); ++r) {
-        const int m = r == 0 ? (hf2 == 0 ? 128 * q : q * k1) : mr;
+    for (int r = 0; r < (role < 0 ? 1 : role == 3 ? 3 : 2); ++r) {
+        const int m = r == 0 ? (hf2 == 0 ? 128 * q : q * k1) : r == 1 ? m1 : m2;
         double s, c;
         sincospi(-2.0 * (double)(m & (NB - 1)) / NB, &s, &c);
-        if (r == 1) tw[i] = kr < f16k::R ? make_float2((float)c, (float)s) : make_float2(0.f, 0.f);
-        else (hf2 == 0 ? w128 : wq)[q] = make_double2(c, s);
+        if (r == 0) {
+            (hf2 == 0 ? w128 : wq)[q] = make_double2(c, s);
+            continue;
+        }
+        const double cz = fabs(c) < 0x1p-28 ? 0x1p-28 : c;
+        if (r == 1) {
+            c1 = cz;
+            s1 = -s;
+            const float2 v = role == 0 ? make_float2((float)c, (float)-s)
+                           : role == 4 ? make_float2(0.f, 0.f)
+                           : role == 5 ? make_float2((float)c, (float)s) : make_float2((float)(-s / cz), (float)cz);
+            if (role != 3) tw[i] = v;
+        } else {
+            tw[i] = make_float2((float)(s1 / c1), (float)(c1 / cz));
+        }
     }
     __syncthreads();
     double2 acc = make_double2(0.0, 0.0);

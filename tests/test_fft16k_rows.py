@@ -49,20 +49,44 @@ def exchange(v, w, r):
 
 def forward(z):
     w = lambda m: np.exp(-2j * np.pi * (m % NB) / NB)  # noqa: E731
-    v = np.fft.fft(z.reshape(R, WG).T, axis=1) * w(T[:, None] * K)
-    v = exchange(v, cols(), rows())
-    v = np.fft.fft(v, axis=1) * w(32 * C[:, None] * K)
-    v = exchange(v, rot(), grp())
-    return np.concatenate([np.fft.fft(v[:, :16], axis=1), np.fft.fft(v[:, 16:], axis=1)], axis=1)
+    v = np.fft.fft(z.reshape(R, WG).T, axis=1)
+    v = exchange(v, cols(), rows())                            # thread (k1, c) over b
+    v = np.fft.fft(v * w(16 * (T >> 4)[:, None] * K), axis=1)
+    v = exchange(v, rot(), grp())                              # thread (k1, k2 mod 16) over c, two halves
+    out = []
+    for h in range(2):
+        kappa = (T >> 4) + 32 * C + 512 * h
+        out.append(np.fft.fft(v[:, 16 * h:16 * h + 16] * w(kappa[:, None] * np.arange(16)), axis=1))
+    return np.concatenate(out, axis=1)
 
 
 def inverse(v):
     w = lambda m: np.exp(2j * np.pi * (m % NB) / NB)  # noqa: E731
-    v = 16 * np.concatenate([np.fft.ifft(v[:, :16], axis=1), np.fft.ifft(v[:, 16:], axis=1)], axis=1)
-    v = exchange(v, grp(), rot())
-    v = 32 * np.fft.ifft(v * w(32 * C[:, None] * K), axis=1)
-    v = exchange(v, rows(), cols())
-    return (32 * np.fft.ifft(v * w(T[:, None] * K), axis=1)).T.reshape(-1)
+    halves = []
+    for h in range(2):
+        kappa = (T >> 4) + 32 * C + 512 * h
+        halves.append(16 * np.fft.ifft(v[:, 16 * h:16 * h + 16], axis=1) * w(kappa[:, None] * np.arange(16)))
+    v = exchange(np.concatenate(halves, axis=1), grp(), rot())
+    v = exchange(32 * np.fft.ifft(v, axis=1), rows(), cols())  # thread t = 16 b + c over k1
+    return (32 * np.fft.ifft(v * w(16 * (T >> 4)[:, None] * K), axis=1)).T.reshape(-1)
+
+
+def test_butterflies_with_turned_inputs():
+    """The four-point butterfly whose inputs carry twiddles as tan and cos, with
+    the table's stand-in for a cosine of zero."""
+    g = np.random.default_rng(2)
+    for _ in range(200):
+        phi = 2 * np.pi * g.integers(0, 1024, 3) / 1024
+        x = g.standard_normal(4) + 1j * g.standard_normal(4)
+        c = np.cos(phi)
+        c = np.where(np.abs(c) < 2.0 ** -28, 2.0 ** -28, c)
+        t = np.sin(phi) / c
+        y = x[1:] * (1 - 1j * t)                               # e^{-i phi} / cos phi
+        a, b = x[0] + c[1] * y[1], x[0] - c[1] * y[1]
+        p, m = y[0] + c[2] / c[0] * y[2], y[0] - c[2] / c[0] * y[2]
+        got = np.array([a + c[0] * p, b - 1j * c[0] * m, a - c[0] * p, b + 1j * c[0] * m])
+        ref = np.fft.fft(x * np.exp(-1j * np.concatenate([[0.0], phi])))
+        assert np.max(np.abs(got - ref)) < 1e-7
 
 
 def test_maps_are_one_to_one_and_in_range():

@@ -174,7 +174,9 @@ tfx_status tfx_sos(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, 
  * convolution on the device) applied first, and all SOS stages are
  * concatenated into one cascade fused behind it in the same kernel.  Only
  * rounding differs from the written order.
- *   cmp  : arithmetic of the FIR part (TFX_COMPUTE_F32 for the plain chain)
+ *   cmp  : arithmetic of the FIR part (TFX_COMPUTE_F32 for the plain chain;
+ *          with bf16 or fp16 operands a chain whose response dies out quickly
+ *          takes the rounded operands through fp32 transforms)
  *   ckpt : NULL or as for tfx_sos with S = total sections (for the backward). */
 tfx_status tfx_chain(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
                      const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt,

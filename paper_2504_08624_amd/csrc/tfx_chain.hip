@@ -931,7 +931,8 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
     w.f16 = off;
     if (fir_mode == FIR_FFT16) off += al256(fft16k_table_bytes());
     w.short_shape = S > 0 && S <= CASC_MAX && M_merged <= FFT16_MAX_TAPS && C * N * S >= SHORT_MIN_WORK &&
-                    ((fir_mode == FIR_FFT && fft_parts(M_merged) == 1) || fir_mode == FIR_FFT16);
+                    ((fir_mode == FIR_FFT && fft_parts(M_merged) == 1) || fir_mode == FIR_FFT16 ||
+                     (fir_mode == FIR_TOEPLITZ && M_merged >= 1));
     w.sh = off;
     w.total = (S > 0 || n_fir > 1 || fir_mode == FIR_FFT || fir_mode == FIR_TOEPLITZ || fir_mode == FIR_FFT16) ? off : 0;
     w.total_short = w.total + (w.short_shape ? al256(fft16k_table_bytes() + sizeof(ShortTab)) : 0);
@@ -1056,11 +1057,11 @@ hipError_t launch_run(const ChainPlan &p) {
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     // a chain that may be a short-memory one, with nothing asked for that only
     // the scan gives (checkpoints, registers, a stream's history)
-    const bool short_try = lay.short_shape && p.ws_bytes >= lay.total_short && !p.n_layout &&
-                           (!p.ckpt || p.ckpt_lazy) && !p.state_in &&
-                           !p.state_out && !p.hist_in && !p.hist_out;
+    const bool short_try = short_wanted(p, lay) && !p.n_layout && (!p.ckpt || p.ckpt_lazy) &&
+                           !p.state_in && !p.state_out && !p.hist_in && !p.hist_out;
     if (short_try) {
-        const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot, ws + lay.sh,
+        const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot,
+                                             p.fir_mode == FIR_TOEPLITZ ? p.cmp : TFX_COMPUTE_F32, ws + lay.sh,
                                              ws + (p.fir_mode == FIR_FFT16 ? lay.f16 : lay.sh), hdr, p.stream);
         if (e != hipSuccess) return e;
         k.after_short = 1;

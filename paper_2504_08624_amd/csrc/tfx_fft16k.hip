@@ -74,6 +74,17 @@ struct ShortArgs {
     int32_t M;
 };
 
+// A value as the FIR's operand type holds it: the matrix-core modes round their
+// operands to bf16 or fp16 and add in fp32; the FIR here is linear in them, so
+// rounded operands through the fp32 transform are that same product sum.
+template <int CMP>
+__device__ __forceinline__ float operand(float v) {
+    if constexpr (CMP == TFX_COMPUTE_BF16) return (float)(__bf16)v;
+    if constexpr (CMP == TFX_COMPUTE_F16) return (float)(_Float16)v;
+    return v;
+}
+
+template <int CMP>
 __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     __shared__ __align__(16) float P[PLANE];
     __shared__ __align__(16) float2 twl[TW_LDS];
@@ -92,6 +103,11 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     float zr[R], zi[R];
     load_block(zr, xc, n0 - V, a.N, nullptr, 0, t);
     load_block(zi, xc, n1 - V, a.N, nullptr, 0, t);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        zr[k] = operand<CMP>(zr[k]);
+        zi[k] = operand<CMP>(zi[k]);
+    }
     __syncthreads();  // the twiddle rows
     convolve(zr, zi, a.hs, 1.f, P, twl, a.tw, t);
     float *yc = a.y + ch * a.ldy;
@@ -135,7 +151,7 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
 }
 
 hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                           const void *tab, const void *tw, uint32_t *hdr, hipStream_t st) {
+                           int32_t cmp, const void *tab, const void *tw, uint32_t *hdr, hipStream_t st) {
     ShortArgs a{};
     a.x = x;
     a.y = y;
@@ -149,7 +165,12 @@ hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64
     a.hdr = hdr;
     a.M = M;
     const int64_t T2 = 2 * (int64_t)(NB - FFT16_MEM);  // the shortest tiles: the most blocks
-    hipLaunchKernelGGL(short16k_kernel, dim3((unsigned)(C * ((N + T2 - 1) / T2))), dim3(WGB), 0, st, a);
+    const dim3 grid((unsigned)(C * ((N + T2 - 1) / T2)));
+    switch (cmp) {
+        case TFX_COMPUTE_BF16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_BF16>, grid, dim3(WGB), 0, st, a); break;
+        case TFX_COMPUTE_F16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_F16>, grid, dim3(WGB), 0, st, a); break;
+        default: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_F32>, grid, dim3(WGB), 0, st, a);
+    }
     return hipGetLastError();
 }
 

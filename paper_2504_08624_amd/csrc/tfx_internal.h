@@ -172,8 +172,8 @@ struct alignas(16) McTab {
 // the last run in which its kernel met a value that is not finite.
 enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5 };
 
-// Short-memory chains: an FFT FIR with a cascade of up to CASC_MAX sections
-// whose impulse response has died out within FFT16_MEM samples is one FIR, and
+// Short-memory chains: an FFT FIR, or a FIR with bf16 or fp16 operands, with a
+// cascade of up to CASC_MAX sections whose impulse response has died out within FFT16_MEM samples is one FIR, and
 // runs as one (short16k_kernel) instead of a FIR and a scan.  Whether a chain is
 // one is found out on the device: the prepare step leaves the sums below, and
 // the kernel takes as the response's length the smallest L that a circle
@@ -190,7 +190,7 @@ struct ShortTab {
 // point blocks; below, the scan's 3072-sample tiles fill the chip better.  Per
 // call, scan against blocks: 2 sections (101 taps) 2 x 0.48 M samples 30 / 36 us,
 // 8 x 0.5 M 36 / 38, 8 x 1 M 52 / 43; 6 sections (1023 taps) 2 x 0.48 M 37 / 37,
-// 8 x 0.5 M 46 / 39, 8 x 5.76 M 252 / 147.
+// 8 x 0.5 M 46 / 39, 8 x 5.76 M 252 / 129.
 constexpr int64_t SHORT_MIN_WORK = 10000000;
 
 // Larger pole radius of 1 + a1 z^-1 + a2 z^-2.
@@ -305,7 +305,12 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
 // rows tw (the prepare step writes them once, in front of its first spectrum),
 // if it is a short-memory one (which the kernel leaves in the header).
 hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                           const void *tab, const void *tw, uint32_t *hdr, hipStream_t st);
+                           int32_t cmp, const void *tab, const void *tw, uint32_t *hdr, hipStream_t st);
+// Whether a call of this plan is prepared for that.
+inline bool short_wanted(const ChainPlan &p, const WsLayout &lay) {
+    return lay.short_shape && p.ws_bytes >= lay.total_short &&
+           !(p.fir_mode == FIR_TOEPLITZ && p.cmp != TFX_COMPUTE_BF16 && p.cmp != TFX_COMPUTE_F16);
+}
 
 // ---- batched ragged clips (tfx_batched.hip) -------------------------------------
 // Device descriptor of one clip, in processing order.  Blocks of the single

@@ -448,8 +448,8 @@ __device__ __forceinline__ double2 cmul64(double2 a, double2 b) {
     return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
 template <class Co>
-__device__ void spec16_block(char *raw, const float *h, int32_t M, Co co_at, int32_t S, int k1, float2 *tw, float2 *hs, float2 *ht,
-                             double2 *hf, int tid) {
+__device__ void spec16_block(char *raw, const float *h, int32_t M, int32_t cmp, Co co_at, int32_t S, int k1, float2 *tw,
+                             float2 *hs, float2 *ht, double2 *hf, int tid) {
     constexpr int NB = FFT16_POINTS;
     struct Sh {
         double2 w128[128], wq[128], A[128], part[128];
@@ -502,7 +502,9 @@ __device__ void spec16_block(char *raw, const float *h, int32_t M, Co co_at, int
 #pragma unroll 4
     for (int n1 = hf2; n1 < n1s; n1 += 2) {
         const int n = 128 * n1 + q;
-        const double hv = n < M ? (double)h[min(n, M - 1)] : 0.0;
+        float hq = h[min(n, M - 1)];
+        hq = cmp == TFX_COMPUTE_BF16 ? (float)(__bf16)hq : cmp == TFX_COMPUTE_F16 ? (float)(_Float16)hq : hq;
+        const double hv = n < M ? (double)hq : 0.0;
         const double2 w = w128[(n1 * k1) & 127];
         acc.x = fma(hv, w.x, acc.x);
         acc.y = fma(hv, w.y, acc.y);
@@ -632,7 +634,7 @@ struct PrepareArgs {
     uint32_t *hdr;
     // 16384-point path: the first n16 blocks, for a chain that may be a
     // short-memory one (ht16 set) CIRC_BLOCKS, then SPEC16_BLOCKS
-    int32_t n16;
+    int32_t n16, cmp16;  // cmp16: operand type of the FIR's taps
     float2 *tw16, *hs16, *ht16;
     ShortTab *st16;
     double2 *hf16;
@@ -676,7 +678,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
         };
         const int r = a.ht16 ? bid - CIRC_BLOCKS : bid;
         if (r < 0) circle_block(raw, co, a.S, bid, a.st16, tid);
-        else spec16_block(raw, a.h, a.M, co, a.S, r, a.tw16, a.hs16, a.ht16, a.hf16, tid);
+        else spec16_block(raw, a.h, a.M, a.cmp16, co, a.S, r, a.tw16, a.hs16, a.ht16, a.hf16, tid);
         return;
     }
     const int b = bid - a.n16;
@@ -872,7 +874,9 @@ hipError_t launch_tables(const ChainPlan &p, const WsLayout &lay, const float *h
         a.hs16 = a.tw16 + f16k::TW_FLOAT2;
         a.n16 = SPEC16_BLOCKS;
     }
-    if (lay.short_shape && p.ws_bytes >= lay.total_short) {
+    a.cmp16 = TFX_COMPUTE_F32;
+    if (short_wanted(p, lay)) {
+        if (p.fir_mode == FIR_TOEPLITZ) a.cmp16 = p.cmp;
         if (!a.tw16) a.tw16 = reinterpret_cast<float2 *>(ws + lay.sh);
         a.ht16 = reinterpret_cast<float2 *>(ws + lay.sh) + f16k::TW_FLOAT2;
         a.st16 = reinterpret_cast<ShortTab *>(ws + lay.sh + fft16k_table_bytes());

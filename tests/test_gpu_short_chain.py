@@ -127,6 +127,33 @@ def test_other_chains_run_as_before(sec):
         assert bool(torch.isfinite(y[:, -1]).all()) == bool(torch.isfinite(want[:, -1]).all())
 
 
+@pytest.mark.parametrize("cmp,dt", [("bf16", torch.bfloat16), ("f16", torch.float16)])
+@pytest.mark.parametrize("S,M", [(1, 5), (2, 255), (6, 1023), (8, 2049)])
+def test_rounded_operands(cmp, dt, S, M):
+    """bf16 and fp16 operands: the oracle on the rounded signal and taps, and the
+    scan behind the matrix-core FIR."""
+    C = 3
+    N = WORK // (S * C) + 17
+    x = _x(C, N, (820, S, M))
+    h = design.fir_lowpass(M, 9000.0, 48000.0).astype(np.float32)
+    sec = _eq(S, M)
+    st = [("fir", _gpu(h)), ("sos", _gpu(sec))]
+    xg = _gpu(x)
+    y = tfx.chain(xg, st, compute=cmp)
+    xr, hr = _cpu(xg.to(dt).float()), _cpu(st[0][1].to(dt).float())
+    assert_close(_cpu(y), O.chain(xr, [("fir", hr), ("sos", sec)]), TOL_FIR_F32, "%s S=%d M=%d" % (cmp, S, M))
+    scan = tfx.chain(xg, st, compute=cmp, return_ckpt=True)[0]
+    assert not torch.equal(y, scan)
+    assert_close(_cpu(y), _cpu(scan).astype(np.float64), TOL_IIR_F32, "against the scan")
+    if cmp == "f16":                                       # over fp16's range: infinite there, and done again
+        xg[1, 200_000] = 7e4
+        want = tfx.chain(xg, st, compute=cmp, return_ckpt=True)[0]
+        got = tfx.chain(xg, st, compute=cmp)
+        lo, hi = 200_000 - 9000, 200_000 + 9000 + 30 * 3072
+        assert _same(got[:, :lo], want[:, :lo]) and _same(got[:, hi:], want[:, hi:])
+        assert not bool(torch.isfinite(got[1, 200_000])) and not bool(torch.isfinite(want[1, 200_000]))
+
+
 def test_a_smaller_workspace_still_serves():
     x = _gpu(_x(2, 900_001, (806,)))
     st = [("fir", _gpu(design.fir_lowpass(255, 9000.0, 48000.0).astype(np.float32))), ("sos", _gpu(_eq(6, 2)))]

@@ -50,7 +50,6 @@ struct BArgs {
     uint64_t *recs;     // adjoint look-back records [cpad][ntiles][S]
     uint32_t *hdr;
     int64_t ntiles, cpad;
-    int32_t vecf, vecg, veco;
     uint32_t xcd_ks;  // block order (xcd_order)
     const uint32_t *gate;  // header of a chain whose short-memory adjoint ran before, or null (here and below)
 };
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(WG, 3) void sos_bwd_kernel(BArgs a) {
             stg_all[STG_FLOATS + cphys(j)] = in ? zi[q] : 0.f;
         }
     } else {
-        stage_tile(stg, a.f + ch * a.ldf + n0, a.N - n0, valid, a.vecf != 0, gl);
+        stage_tile(stg, a.f + ch * a.ldf + n0, a.N - n0, valid, gl);
     }
     __syncthreads();
     const uint32_t epoch = s_epoch;
@@ -181,7 +180,7 @@ __global__ __launch_bounds__(WG, 3) void sos_bwd_kernel(BArgs a) {
     }
     // 3. stage g (over f); lanes take their reverse-time chunk
     __syncthreads();
-    stage_tile(stg, a.g + ch * a.ldg + n0, a.N - n0, valid, a.vecg != 0, gl);
+    stage_tile(stg, a.g + ch * a.ldg + n0, a.N - n0, valid, gl);
     __syncthreads();
     float gr[L];
     load_chunk(stg, mc, gr);
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(WG, 3) void sos_bwd_kernel(BArgs a) {
     __syncthreads();
     store_chunk(stg, mc, gr);
     __syncthreads();
-    if (valid) store_tile(a.gf + ch * a.ldo + n0, stg, a.N - n0, a.veco != 0, gl);
+    if (valid) store_tile(a.gf + ch * a.ldo + n0, stg, a.N - n0, gl);
 }
 
 // Section-coefficient gradients from the per-tile partial sums.  One block
@@ -769,9 +768,6 @@ hipError_t launch_backward(const BwdPlan &bp) {
         b.hdr = hdr;
         b.ntiles = ntiles;
         b.cpad = cpad;
-        b.vecf = (reinterpret_cast<uintptr_t>(b.f) % 16 == 0 && b.ldf % 4 == 0) ? 1 : 0;
-        b.vecg = (reinterpret_cast<uintptr_t>(b.g) % 16 == 0 && b.ldg % 4 == 0) ? 1 : 0;
-        b.veco = (reinterpret_cast<uintptr_t>(b.gf) % 16 == 0 && b.ldo % 4 == 0) ? 1 : 0;
         b.xcd_ks = xcd_window(npairs);
         const size_t dyn = (size_t)p.S * sizeof(SecLds) +
                            std::max((size_t)p.S * GROUPS * GL * sizeof(float2),

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
             const int k = e / DD, i = (e % DD) / D, j = e % D;
             cT[e] = ct.T[k][i][j];
         }
-        stage_tile<LC>(stg, d.x + ch * d.ldx + n0, d.N - n0, valid, d.vec != 0, gl);
+        stage_tile<LC>(stg, d.x + ch * d.ldx + n0, d.N - n0, valid, gl);
         __syncthreads();
         load_chunk<LC>(stg, gl, v);
         if (S > 0) {  // (no state otherwise: y = x; block-uniform)
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
         }
     } else {
         stage_tables(s_tab, a.tab, (int)d.tab0, min(d.S, LDS_SECTIONS), tid, WG);
-        stage_tile<LC>(stg, d.x + ch * d.ldx + n0, d.N - n0, valid, d.vec != 0, gl);
+        stage_tile<LC>(stg, d.x + ch * d.ldx + n0, d.N - n0, valid, gl);
         __syncthreads();
         load_chunk<LC>(stg, gl, v);
         for (int s = 0; s < d.S; ++s) {
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
     __syncthreads();
     store_chunk<LC>(stg, gl, v);
     __syncthreads();
-    if (valid) store_tile<LC>(d.y + ch * d.ldy + n0, stg, d.N - n0, d.vec != 0, gl);
+    if (valid) store_tile<LC>(d.y + ch * d.ldy + n0, stg, d.N - n0, gl);
 }
 
 // Matrix-core form (chunk length 24, i.e. 3072-sample tiles, every cascade
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(WG, 4) void batch_mc_kernel(BatchArgs a) {
     const float *src[GROUPS];
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) src[g] = 2 * pair + g < d.C ? d.x + (2 * pair + g) * d.ldx + n0 : nullptr;
-    mc_stage_pair(lds, src, rem, d.vec != 0, tid);
+    mc_stage_pair(lds, src, rem, tid);
     if (d.S > 0) {  // block-uniform
         McCtx m;
         m.mt = &a.mtab[s_clip];
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(WG, 4) void batch_mc_kernel(BatchArgs a) {
     float *dst[GROUPS];
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) dst[g] = 2 * pair + g < d.C ? d.y + (2 * pair + g) * d.ldy + n0 : nullptr;
-    mc_store_pair(lds, dst, rem, d.vec != 0, tid);
+    mc_store_pair(lds, dst, rem, tid);
 }
 
 // The descriptor table reaches the device through kernel arguments, 32
@@ -316,8 +316,7 @@ BatchLayout batch_plan(const ClipIn *clips, int32_t n, int lc, int order, ClipDe
         d.blk0 = blk;
         d.tab0 = tab;
         d.rec0 = rec;
-        d.vec = ((reinterpret_cast<uintptr_t>(c.x) | reinterpret_cast<uintptr_t>(c.y)) % 16 == 0 && c.ldx % 4 == 0 &&
-                 c.ldy % 4 == 0) ? 1 : 0;
+        d.reserved = 0;
         blk += d.cpad / 2 * d.ntiles;
         tab += c.S;
         if (c.S > lay.smax) lay.smax = c.S;

@@ -98,7 +98,6 @@ struct KArgs {
     uint64_t *recs;
     uint32_t *hdr;
     int64_t ntiles, cpad;
-    int32_t vec;          // x and y rows 16-byte aligned: float4 tile I/O
     int32_t correlate;    // FIR part: y[n] = sum_k h[k] x[n+k] (adjoint) instead of convolution
     const float2 *twid;   // e^{-2 pi i j / 4096}
     const float2 *hspec;  // [nparts][4096] spectra of the tap partitions / 4096
@@ -110,6 +109,8 @@ struct KArgs {
     int32_t tzQ;          // its frame lags Q
     const float *hist;    // streaming: the M - 1 FIR inputs before the block, [C][M - 1] (null = zeros)
     int64_t ldh;          // M - 1
+    float *hist_out;      // chain_last_kernel: its blocks from tile_blocks on write the next history
+    uint32_t tile_blocks;
     uint32_t xcd_ks;      // block order: xcd_order's log2 K (0 = block ids in order)
     int32_t after_short;  // the short-memory kernel ran before this one: nothing to do if it did the work (2: nor
                           // if the chain is not a short-memory one)
@@ -119,11 +120,24 @@ __device__ __forceinline__ bool short_skip(const KArgs &a) {
     return a.after_short && (short_done(a.hdr) || (a.after_short == 2 && a.hdr[HDR_SHORT] == 0u));
 }
 
+// Streaming: hist_out[c][j] = the input M - 1 - j samples before the block's end
+// (from the block, then from hist, then zeros); thread e of C (M - 1).
+__device__ __forceinline__ void write_history(const float *x, int64_t ldx, const float *hin, float *hout, int64_t C,
+                                              int64_t N, int64_t H, int64_t e) {
+    if (e >= C * H) return;
+    const int64_t c = e / H, j = e % H;
+    const int64_t n = N - H + j;
+    hout[e] = n >= 0 ? x[c * ldx + n] : (hin ? hin[c * H + H + n] : 0.f);
+}
+
 // FIR input x[ch][n] of the block, n < N, with the streaming history for
 // n in [-(M - 1), 0) and zeros before it.
+// (No branch around a load: see load_pair_block.)
 __device__ __forceinline__ float fir_input(const KArgs &a, const float *xc, int64_t ch, int64_t n) {
-    if (n >= 0) return n < a.N ? xc[n] : 0.f;
-    return (a.hist && n >= -a.ldh) ? a.hist[ch * a.ldh + a.ldh + n] : 0.f;
+    const bool inh = a.hist && n < 0 && n >= -a.ldh;
+    const float *p = inh ? a.hist + ch * a.ldh : xc;
+    const float v = p[inh ? a.ldh + n : max(min(n, a.N - 1), (int64_t)0)];
+    return inh || (n >= 0 && n < a.N) ? v : 0.f;
 }
 
 // Fused matrix-core FIR of a tile (both channels of the pair), written into
@@ -171,7 +185,7 @@ __device__ void tz_tile(const KArgs &a, float *lds, int64_t pair, int64_t n0, in
             Tt *ag = ast + g * TZ_ROWS * TROW;
             const int total = nrows * (TP / 4);
             const int64_t nlo = fbase * TP, nhi = (fbase + nrows) * TP;
-            if (ch < a.C && a.vec && nlo >= 0 && nhi <= a.N) {
+            if (ch < a.C && nlo >= 0 && nhi <= a.N) {
                 // inside the signal: TZ_SU four-sample loads in flight per thread
                 for (int e0 = tid; e0 < total; e0 += TZ_SU * WG) {
                     float4 t[TZ_SU];
@@ -179,7 +193,7 @@ __device__ void tz_tile(const KArgs &a, float *lds, int64_t pair, int64_t n0, in
                     for (int k = 0; k < TZ_SU; ++k) {
                         // clamped, not skipped: loads inside a branch are each waited for
                         const int e = min(e0 + k * WG, total - 1);
-                        t[k] = *reinterpret_cast<const float4 *>(xc + nlo + 4 * e);
+                        t[k] = load4u(xc + nlo + 4 * e);
                     }
 #pragma unroll
                     for (int k = 0; k < TZ_SU; ++k) {
@@ -200,8 +214,8 @@ __device__ void tz_tile(const KArgs &a, float *lds, int64_t pair, int64_t n0, in
                 const int row = e >> 3, c4 = e & 7;  // TP / 4 = 8 four-sample pieces a row
                 const int64_t n = (fbase + row) * TP + 4 * c4;
                 float v4[4];
-                if (ch < a.C && a.vec && n >= 0 && n + 3 < a.N) {
-                    const float4 t = *reinterpret_cast<const float4 *>(xc + n);
+                if (ch < a.C && n >= 0 && n + 3 < a.N) {
+                    const float4 t = load4u(xc + n);
                     v4[0] = t.x;
                     v4[1] = t.y;
                     v4[2] = t.z;
@@ -362,6 +376,7 @@ __device__ void fft_block(const KArgs &a, float *lds, int64_t pair, int64_t n0, 
 // in v.  stg: the group's DIRECT_GROUP_FLOATS of LDS.  Contains workgroup
 // barriers (every lane of the workgroup calls it).
 __device__ void direct_tile(const KArgs &a, float *stg, int64_t ch, bool valid, int gl, int64_t n0, float (&v)[L]) {
+    if (!valid) ch = a.C - 1;  // (its loads are clamped, not skipped)
     const float *xc = a.x + ch * a.ldx;
     const int p0 = gl * L;
     float acc[L];
@@ -372,18 +387,20 @@ __device__ void direct_tile(const KArgs &a, float *stg, int64_t ch, bool valid, 
         // stage x[src0 + i], i < T + KBL: convolution needs x[n - k],
         // correlation x[n + k]
         const int64_t src0 = a.correlate ? n0 + k0 : n0 - (k0 + a.KBL - 1);
+        const bool inside = src0 >= 0 && src0 + T + a.KBL <= a.N;
         for (int i0 = 0; i0 < T + a.KBL; i0 += 8 * GL) {
             float t8[8];
+            if (inside) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + gl + GL * u;
-                const int64_t n = src0 + i;
-                t8[u] = (valid && i < T + a.KBL) ? fir_input(a, xc, ch, n) : 0.f;
+                for (int u = 0; u < 8; ++u) t8[u] = xc[src0 + min(i0 + gl + GL * u, T + a.KBL - 1)];
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t8[u] = fir_input(a, xc, ch, src0 + i0 + gl + GL * u);
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + gl + GL * u;
-                if (i < T + a.KBL) stg[cphys(i)] = t8[u];
+                if (i < T + a.KBL) stg[cphys(i)] = valid ? t8[u] : 0.f;
             }
         }
         __syncthreads();
@@ -605,17 +622,26 @@ constexpr int chain_min_blocks() {
     return (HAS_SOS && CASC && !HIQ && !STOUT && (FIRM == FIR_NONE || FIRM == FIR_FFT)) ? 4 : 1;
 }
 
+template <int FIRM>
+struct ChainLds {
+    alignas(16) float lds[lds_floats<FIRM>()];
+    double agg[2 * GROUPS][GWAVES][2];
+    double pre[2 * GROUPS][2];
+    uint32_t epoch;
+};
+
+// One workgroup's tile: block `block` of `nblocks`.
 template <int FIRM, bool HAS_SOS, bool HIQ, bool CASC, bool STOUT>
-__global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STOUT>())) void chain_kernel(KArgs a) {
-    __shared__ __align__(16) float lds[lds_floats<FIRM>()];
-    __shared__ double s_agg[2 * GROUPS][GWAVES][2];
-    __shared__ double s_pre[2 * GROUPS][2];
-    __shared__ uint32_t s_epoch;
+__device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, unsigned char *s_dyn, uint32_t block,
+                                           uint32_t nblocks) {
+    float *lds = sh.lds;
+    auto &s_agg = sh.agg;
+    auto &s_pre = sh.pre;
+    uint32_t &s_epoch = sh.epoch;
     constexpr bool FFT = FIRM == FIR_FFT || FIRM == FIR_FFT_PARTS;
     // dynamic: the fp32 tables (LDS_SECTIONS sections at a time, or all of a
     // cascade-level cascade without their look-back powers), then the
     // cascade look-back area unless it sits in the FFT buffers' tail
-    extern __shared__ __align__(16) unsigned char s_dyn[];
     SecLds *s_tab = reinterpret_cast<SecLds *>(s_dyn);
     SecLdsC *s_tabc = reinterpret_cast<SecLdsC *>(s_dyn);
     // with the FFT FIR the same area first holds the transforms' twiddles
@@ -623,11 +649,6 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
     // for both)
     float2 *s_twl = reinterpret_cast<float2 *>(s_dyn);
 
-    if (HAS_SOS && short_skip(a)) return;
-    if (HAS_SOS && (a.hdr[HDR_HIQ] != 0u) != HIQ) {  // the other variant runs
-        advance_epoch(a.hdr);
-        return;
-    }
     TileCtx c;
     c.tid = threadIdx.x;
     c.lane = c.tid & 63;
@@ -653,8 +674,9 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
         c.epoch = s_epoch;
     }
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
-    const uint64_t id = xcd_order(blockIdx.x, gridDim.x, a.xcd_ks);
-    c.tile = (int64_t)(id / npairs);
+    const uint64_t id = xcd_order(block, nblocks, a.xcd_ks);
+    // (returning the registers is the last tile's launch)
+    c.tile = STOUT && CASC ? a.ntiles - 1 : (int64_t)(id / npairs);
     const int64_t pair = (int64_t)(id % npairs);
     c.ch = 2 * pair + c.grp;
     c.valid = c.ch < a.C;
@@ -663,7 +685,7 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
     float *stg = lds + c.grp * (FIRM == FIR_DIRECT ? DIRECT_GROUP_FLOATS : STG_FLOATS);
 
     if (FIRM == FIR_NONE) {
-        stage_tile(stg, a.x + c.ch * a.ldx + n0, a.N - n0, c.valid, a.vec != 0, c.gl);
+        stage_tile(stg, a.x + c.ch * a.ldx + n0, a.N - n0, c.valid, c.gl);
         __syncthreads();
         load_chunk(stg, c.gl, v);
     } else if constexpr (is_tz<FIRM>()) {
@@ -706,14 +728,18 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
         float *cr = casc_in_tail(FIRM, a.S) ? lds + GROUPS * STG_FLOATS
                                             : reinterpret_cast<float *>(s_dyn + a.S * sizeof(SecLdsC));
         float *cT = cr, *cM = cr + 3 * DD + c.grp * DD, *cE = cr + (3 + GROUPS) * DD + 32 * c.grp, *cP = cE + 16;
-        for (int e = c.tid; e < 3 * DD; e += WG) {  // read in phase B, after phase A's barriers
-            const int k = e / DD, i = (e % DD) / D, j = e % D;
-            cT[e] = a.casc->T[k][i][j];
-        }
+        // a signal of one tile (a stream's block) enters it with a known state
+        // and has nothing to publish: phase C alone
+        const bool alone = STOUT && a.ntiles == 1;
+        if (!alone)
+            for (int e = c.tid; e < 3 * DD; e += WG) {  // read in phase B, after phase A's barriers
+                const int k = e / DD, i = (e % DD) / D, j = e % D;
+                cT[e] = a.casc->T[k][i][j];
+            }
         // (A) zero tile-entering state: the cascade's tile aggregate and its
         //     response to the tile's input
         float eA0 = 0.f, eA1 = 0.f;
-        for (int s = 0; s < a.S; ++s) {
+        for (int s = 0; !alone && s < a.S; ++s) {
             float e0, e1, E0, E1;
             const int buf = (s & 1) * GROUPS + c.grp;
             casc_section_a<L, true>(s_tabc[s], v, c.lane, c.gw, s_agg, buf, e0, e1, E0, E1);
@@ -733,7 +759,9 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
         // barrier until the output is staged (ordered by phase B's barrier)
         if (ZIR && a.S <= ZIR_MAX) zt_stage(lds, a.zir, 2 * a.S, c.tid);
         // (B) one look-back of the cascade state (first wave of each group)
-        if (c.gw == 0) {
+        if (alone) {
+            if (c.gl < D) cP[c.gl] = (a.state_in && c.valid) ? a.state_in[c.ch * D + c.gl] : 0.f;
+        } else if (c.gw == 0) {
             CascCtx cc;
             cc.lane = c.lane;
             cc.D = 2 * a.S;
@@ -758,7 +786,7 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
         for (int s = 0; s < a.S; ++s) {
             const SecLdsC &tb = s_tabc[s];
             float c1 = 0.f, c2 = 0.f;
-            if (s == 0) {
+            if (s == 0 && !alone) {
                 float e0 = eA0, e1 = eA1;
                 fold_prefix(tb, c.lane, c.gw, cP[0], cP[1], e0, e1);
                 if (STOUT && c.is_last) section_from<L, true>(tb.coef, v, e0, e1, r_cap, c1, c2);
@@ -798,7 +826,52 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
     __syncthreads();
     store_chunk(stg, c.gl, v);
     __syncthreads();
-    if (c.valid) store_tile(a.y + c.ch * a.ldy + n0, stg, a.N - n0, a.vec != 0, c.gl);
+    if (c.valid) store_tile(a.y + c.ch * a.ldy + n0, stg, a.N - n0, c.gl);
+}
+
+template <int FIRM, bool HAS_SOS, bool HIQ, bool CASC, bool STOUT>
+__global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STOUT>())) void chain_kernel(KArgs a) {
+    __shared__ ChainLds<FIRM> sh;
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    if (HAS_SOS && short_skip(a)) return;
+    if (HAS_SOS && (a.hdr[HDR_HIQ] != 0u) != HIQ) {  // the other variant runs
+        advance_epoch(a.hdr);
+        return;
+    }
+    chain_tile<FIRM, HAS_SOS, HIQ, CASC, STOUT>(a, sh, s_dyn, blockIdx.x, gridDim.x);
+}
+
+// The last launch of a call that returns the registers, cascades up to CASC_MAX
+// sections: the last tile (its tile blocks lead the grid; the launch before ran
+// the others), every tile in FP64 carries where a section asks for that, and in
+// blocks of its own the stream's next history (hist is only read here).  A
+// stream's block of one tile, whose time is launches and one tile's latency, is
+// this launch alone (8 channels x 512 samples, 1023 taps, 6 sections: 28.7 us a
+// block as history, filter and empty FP64 launch, 21.4 us as one).
+template <int FIRM>
+__global__ __launch_bounds__(WG) void chain_last_kernel(KArgs a) {
+    __shared__ ChainLds<FIRM> sh;
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    const uint32_t np = (uint32_t)(a.cpad / 2);
+    const uint32_t hiq = a.hdr[HDR_HIQ];
+    if (blockIdx.x >= a.tile_blocks) {
+        write_history(a.x, a.ldx, a.hist, a.hist_out, a.C, a.N, a.ldh,
+                      (int64_t)(blockIdx.x - a.tile_blocks) * WG + threadIdx.x);
+        return;
+    }
+    if (hiq)
+        chain_tile<FIRM, true, true, false, true>(a, sh, s_dyn, blockIdx.x, a.tile_blocks);
+    else if (blockIdx.x < np)
+        chain_tile<FIRM, true, false, true, true>(a, sh, s_dyn, blockIdx.x, np);
+    else
+        return;
+    // the next run's epoch, by the last of the blocks that have read this one's
+    // (with FP64 carries and more tiles the launch before has set it)
+    if (threadIdx.x == 0 && (!hiq || a.ntiles == 1) &&
+        __hip_atomic_fetch_add(a.hdr + HDR_DONE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1) {
+        next_epoch(a.hdr);
+        a.hdr[HDR_DONE] = 0u;
+    }
 }
 
 template <int FIRM>
@@ -863,7 +936,7 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
         const float *src[GROUPS];
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) src[g] = 2 * pair + g < a.C ? a.x + (2 * pair + g) * a.ldx + n0 : nullptr;
-        mc_stage_pair(X, src, rem, a.vec != 0, tid);
+        mc_stage_pair(X, src, rem, tid);
     }
     McCtx m;
     m.mt = a.mc;
@@ -887,7 +960,7 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
     float *dst[GROUPS];
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) dst[g] = 2 * pair + g < a.C ? a.y + (2 * pair + g) * a.ldy + n0 : nullptr;
-    mc_store_pair(X, dst, rem, a.vec != 0, tid);
+    mc_store_pair(X, dst, rem, tid);
 }
 
 // ------------------------------------------------------------------- host
@@ -942,26 +1015,47 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
 // kernel of the prepare step (tfx_tables.hip)
 hipError_t launch_state_passthrough(const float *in, float *out, int64_t n, hipStream_t st);
 
+// (hiq: also the FP64-carry variant)
 template <int F, bool S, bool STOUT>
 static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t st, bool hiq = true) {
     // (with the FFT FIR the dynamic area first holds the twiddles)
     constexpr size_t twl = (F == FIR_FFT || F == FIR_FFT_PARTS) ? sizeof(float2) * TWL_ENTRIES : 0;
     const size_t dyn = std::max(twl, S ? sizeof(SecLds) * (size_t)(k.S < LDS_SECTIONS ? k.S : LDS_SECTIONS) : 0);
-    if constexpr (S) {
-        const size_t dync = std::max(twl, sizeof(SecLdsC) * (size_t)k.S +
-                                              (casc_in_tail(F, k.S) ? 0 : sizeof(float) * (size_t)casc_floats(2 * k.S)));
-        constexpr bool mc = !STOUT && (F == FIR_NONE || F == FIR_FFT || F == FIR_DIRECT || is_tz<F>());
-        if (mc && k.S >= MC_MIN_SECTIONS && k.S <= CASC_MAX) {
+    const size_t dync = std::max(twl, sizeof(SecLdsC) * (size_t)k.S +
+                                          (casc_in_tail(F, k.S) ? 0 : sizeof(float) * (size_t)casc_floats(2 * k.S)));
+    hipError_t e = hipSuccess;
+    if constexpr (!S) {
+        hipLaunchKernelGGL((chain_kernel<F, S, false, false, false>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
+    } else if (k.S > CASC_MAX) {
+        hipLaunchKernelGGL((chain_kernel<F, S, false, false, STOUT>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
+    } else if constexpr (STOUT) {
+        // the final state is the last tile's affair: the tiles before it run as
+        // without one (tables or matrix cores instead of a second pass of every
+        // section), then the last one, on the same records (12 x 5.29 M, odd
+        // length, 4 sections: 389 us a call with the second pass everywhere and
+        // one-sample row accesses, 206 us now)
+        const int64_t np = k.cpad / 2;
+        if (k.ntiles > 1) {
+            KArgs m = k;
+            m.state_out = nullptr;
+            if ((e = launch_variants<F, true, false>(m, np * (k.ntiles - 1), st, false)) != hipSuccess) return e;
+        }
+        KArgs last = k;
+        last.tile_blocks = (uint32_t)nblocks;
+        const int64_t nh = k.hist_out ? (k.C * k.ldh + WG - 1) / WG : 0;
+        hipLaunchKernelGGL((chain_last_kernel<F>), dim3((unsigned)(nblocks + nh)), dim3(WG), std::max(dyn, dync), st,
+                           last);
+        return hipGetLastError();
+    } else {
+        constexpr bool mc = F == FIR_NONE || F == FIR_FFT || F == FIR_DIRECT || is_tz<F>();
+        if (mc && k.S >= MC_MIN_SECTIONS) {
             if constexpr (mc)
                 hipLaunchKernelGGL((chain_mc_kernel<F>), dim3((unsigned)nblocks), dim3(WG), 0, st, k);
-        } else if (k.S <= CASC_MAX)
-            hipLaunchKernelGGL((chain_kernel<F, S, false, true, STOUT>), dim3((unsigned)nblocks), dim3(WG), dync, st, k);
-        else
-            hipLaunchKernelGGL((chain_kernel<F, S, false, false, STOUT>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
-    } else {
-        hipLaunchKernelGGL((chain_kernel<F, S, false, false, false>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
+        } else {
+            hipLaunchKernelGGL((chain_kernel<F, S, false, true, false>), dim3((unsigned)nblocks), dim3(WG), dync, st, k);
+        }
     }
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if constexpr (S) {
         if (e != hipSuccess || !hiq) return e;
         hipLaunchKernelGGL((chain_kernel<F, S, true, false, STOUT>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
@@ -1017,21 +1111,24 @@ hipError_t launch_prepare(const ChainPlan &p) {
     return launch_toeplitz_prepare(taps_ptr(p, lay), Mtot, p.cmp, static_cast<char *>(p.ws) + lay.ttab, p.stream);
 }
 
-// Streaming: hist_out[c][j] = the input M - 1 - j samples before the
-// block's end (from the block, then from hist_in, then zeros).
 __global__ void hist_update_kernel(const float *x, int64_t ldx, const float *hin, float *hout, int64_t C, int64_t N,
                                    int64_t H) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= C * H) return;
-    const int64_t c = e / H, j = e % H;
-    const int64_t n = N - H + j;
-    hout[e] = n >= 0 ? x[c * ldx + n] : (hin ? hin[c * H + H + n] : 0.f);
+    write_history(x, ldx, hin, hout, C, N, H, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 hipError_t launch_run(const ChainPlan &p) {
     int32_t Mtot = merged_taps(p.firs);
     const WsLayout lay = ws_layout(p.C, p.n_layout ? p.n_layout : p.N, p.S, Mtot, p.firs.n, p.fir_mode);
-    if (p.hist_out && Mtot > 1) {  // stream-ordered before the filter, which reads hist_in only
+    // matrix-core FIR with a cascade behind it, bf16 or fp16 operands: fused
+    // into the chain kernel (the split-bf16 form and a FIR alone run the
+    // stand-alone Toeplitz kernel)
+    const bool tz_fused = Mtot > 0 && p.fir_mode == FIR_TOEPLITZ && p.S > 0 && (p.cmp == TZ_BF16 || p.cmp == TZ_F16);
+    // the next history of a stream: by extra blocks of the chain kernel where one
+    // that returns the registers filters the block from x, else by a launch of
+    // its own, stream-ordered before the filter, which reads hist_in only
+    const bool hist_fused = p.hist_out && Mtot > 1 && p.N > 0 && p.state_out && p.S > 0 && p.S <= CASC_MAX &&
+                            (p.fir_mode == FIR_DIRECT || p.fir_mode == FIR_FFT || tz_fused);
+    if (p.hist_out && Mtot > 1 && !hist_fused) {
         const int64_t n = p.C * (int64_t)(Mtot - 1);
         hipLaunchKernelGGL(hist_update_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, p.stream, p.x, p.ldx,
                            p.hist_in, p.hist_out, p.C, p.N, (int64_t)(Mtot - 1));
@@ -1050,10 +1147,6 @@ hipError_t launch_run(const ChainPlan &p) {
     k.N = p.N;
     k.ldx = p.ldx;
     k.ldy = p.ldy;
-    // matrix-core FIR with a cascade behind it, bf16 or fp16 operands: fused
-    // into the chain kernel (the split-bf16 form and a FIR alone run the
-    // stand-alone Toeplitz kernel)
-    const bool tz_fused = Mtot > 0 && p.fir_mode == FIR_TOEPLITZ && p.S > 0 && (p.cmp == TZ_BF16 || p.cmp == TZ_F16);
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     // a chain that may be a short-memory one, with nothing asked for that only
     // the scan gives (checkpoints, registers, a stream's history)
@@ -1102,8 +1195,6 @@ hipError_t launch_run(const ChainPlan &p) {
     k.hdr = hdr;
     k.tab = reinterpret_cast<const SecTab *>(ws + lay.tab);
     k.recs = reinterpret_cast<uint64_t *>(ws + lay.recs);
-    k.vec = ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.y)) % 16 == 0 && p.ldx % 4 == 0 &&
-             p.ldy % 4 == 0) ? 1 : 0;
     k.twid = reinterpret_cast<const float2 *>(ws + lay.twid);
     k.hspec = reinterpret_cast<const float2 *>(ws + lay.hspec);
     k.nparts = fft_parts(Mtot);
@@ -1112,6 +1203,7 @@ hipError_t launch_run(const ChainPlan &p) {
     k.mc = reinterpret_cast<const McTab *>(ws + lay.mc);
     k.hist = Mtot > 1 ? p.hist_in : nullptr;
     k.ldh = Mtot > 1 ? Mtot - 1 : 0;
+    k.hist_out = hist_fused ? p.hist_out : nullptr;
     k.xcd_ks = xcd_window(lay.cpad / 2);
     const int64_t nblocks = (lay.cpad / 2) * k.ntiles;
     const bool s = p.S > 0;
@@ -1157,8 +1249,6 @@ hipError_t launch_fir_pass(const ChainPlan &p, const WsLayout &lay, const float 
     k.S = 0;
     k.ntiles = lay.ntiles;
     k.cpad = lay.cpad;
-    k.vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0 && ldin % 4 == 0 &&
-             ldout % 4 == 0) ? 1 : 0;
     k.correlate = correlate ? 1 : 0;
     k.twid = reinterpret_cast<const float2 *>(ws + lay.twid);
     k.hspec = reinterpret_cast<const float2 *>(ws + lay.hspec);
@@ -1190,8 +1280,6 @@ hipError_t launch_ckpt(const ChainPlan &p, const WsLayout &lay, const float *in,
     k.hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     k.tab = reinterpret_cast<const SecTab *>(ws + lay.tab);
     k.recs = reinterpret_cast<uint64_t *>(ws + lay.recs);
-    k.vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0 && ldin % 4 == 0 &&
-             ldout % 4 == 0) ? 1 : 0;
     k.twid = reinterpret_cast<const float2 *>(ws + lay.twid);
     k.hspec = reinterpret_cast<const float2 *>(ws + lay.hspec);
     k.nparts = 1;

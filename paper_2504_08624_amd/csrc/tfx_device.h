@@ -34,13 +34,14 @@ __device__ __forceinline__ void st_word(uint64_t *p, uint64_t v) {
 __device__ __forceinline__ uint32_t load_epoch(const uint32_t *hdr, int word) {
     return __hip_atomic_load(hdr + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void next_epoch(uint32_t *hdr) {
+    const uint32_t ne = (hdr[HDR_EPOCH] + 1u) & EPOCH_MASK;
+    hdr[HDR_EPOCH] = ne == 0u ? 1u : ne;
+}
 // Run by the filter-kernel variant that does not match the high-Q word
 // before it exits: its block 0 advances the look-back epoch for the next run.
 __device__ __forceinline__ void advance_epoch(uint32_t *hdr) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint32_t ne = (hdr[HDR_EPOCH] + 1u) & EPOCH_MASK;
-        hdr[HDR_EPOCH] = ne == 0u ? 1u : ne;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) next_epoch(hdr);
 }
 
 // Whether the short-memory kernel has done this run's work: the chain is a
@@ -210,43 +211,67 @@ __device__ __forceinline__ void store_chunk(float *stg, int gl, const float (&v)
             make_float4(v[4 * q + 0], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
 }
 
+// Four samples at any 4-byte boundary: rows of odd length start off a 16-byte
+// one, and the memory pipe takes 16-byte accesses there too (a batch of 48
+// clips, 1 to 30 s, most with such rows: 1302 us a call with one-sample
+// accesses for them, 846 us with these).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4u(const float *p) {
+    const f32x4u v = *reinterpret_cast<const f32x4u *>(p);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store4u(float *p, float4 v) {
+    f32x4u u;
+    u[0] = v.x;
+    u[1] = v.y;
+    u[2] = v.z;
+    u[3] = v.w;
+    *reinterpret_cast<f32x4u *>(p) = u;
+}
+
 // One group (GL lanes) stages the tile's samples src[0..rem) (zeros past rem)
-// into stg in the chunk layout.  vec: src is 16-byte aligned.
+// into stg in the chunk layout.
 template <int LC = L>
-__device__ __forceinline__ void stage_tile(float *stg, const float *src, int64_t rem, bool valid, bool vec, int gl) {
+__device__ __forceinline__ void stage_tile(float *stg, const float *src, int64_t rem, bool valid, int gl) {
     typedef Chunk<LC> K;
-    if (vec && rem >= K::T) {
+    if (rem >= K::T) {
         float4 t4[K::T / (4 * GL)];
 #pragma unroll
         for (int k = 0; k < K::T / (4 * GL); ++k)
-            t4[k] = valid ? reinterpret_cast<const float4 *>(src)[gl + GL * k] : make_float4(0.f, 0.f, 0.f, 0.f);
+            t4[k] = valid ? load4u(src + 4 * (gl + GL * k)) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int k = 0; k < K::T / (4 * GL); ++k)
             *reinterpret_cast<float4 *>(&stg[K::phys(4 * (gl + GL * k))]) = t4[k];
-    } else {  // ragged last tile or unaligned rows
-#pragma unroll 4
+    } else {  // ragged last tile: every load issued before the first store (a short signal or a block of a
+              // stream is this tile alone, and waits for it)
+        float v[K::T / GL];
+        const int n = valid ? (int)rem : 0;
+#pragma unroll
+        for (int k = 0; k < K::T / GL; ++k) v[k] = n > 0 ? src[min(gl + GL * k, n - 1)] : 0.f;
+#pragma unroll
         for (int k = 0; k < K::T / GL; ++k) {
             const int i = gl + GL * k;
-            stg[K::phys(i)] = (valid && i < rem) ? src[i] : 0.f;
+            stg[K::phys(i)] = i < n ? v[k] : 0.f;
         }
     }
 }
 
 // One group writes its staged tile (chunk layout) to dst[0..rem).
 template <int LC = L>
-__device__ __forceinline__ void store_tile(float *dst, const float *stg, int64_t rem, bool vec, int gl) {
+__device__ __forceinline__ void store_tile(float *dst, const float *stg, int64_t rem, int gl) {
     typedef Chunk<LC> K;
-    if (vec && rem >= K::T) {
+    if (rem >= K::T) {
 #pragma unroll
         for (int k = 0; k < K::T / (4 * GL); ++k) {
             const int f = gl + GL * k;
-            reinterpret_cast<float4 *>(dst)[f] = *reinterpret_cast<const float4 *>(&stg[K::phys(4 * f)]);
+            store4u(dst + 4 * f, *reinterpret_cast<const float4 *>(&stg[K::phys(4 * f)]));
         }
     } else {
+        const int n = (int)min(rem, (int64_t)K::T);
 #pragma unroll 4
         for (int k = 0; k < K::T / GL; ++k) {
             const int i = gl + GL * k;
-            if (i < rem) dst[i] = stg[K::phys(i)];
+            if (i < n) dst[i] = stg[K::phys(i)];
         }
     }
 }
@@ -509,13 +534,21 @@ __device__ __forceinline__ void load_pair_block(float (&zr)[16], float (&zi)[16]
         }
         return;
     }
+    // the signal's ends: every element reads some address that is there and is
+    // then kept or cleared.  A load inside a branch is waited for before the
+    // next one, 32 times over (a stream's block of 512 samples through 1023
+    // taps and 6 sections: the kernel 25.8 us with branches here and phases A
+    // and B in chain_tile, 20.4 us without either)
+    const bool two = xb != nullptr;
+    const float *pb = two ? xb : xa, *qb = two ? hb : ha;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int64_t n = base + 256 * q + tid;
-        const bool in = n >= 0 && n < hi;
-        const bool inh = n < 0 && n >= -hlen;
-        zr[q] = in ? xa[n] : (inh ? ha[hlen + n] : 0.f);
-        zi[q] = (in && xb) ? xb[n] : ((inh && hb) ? hb[hlen + n] : 0.f);
+        const bool inh = n < 0 && n >= -hlen, in = inh || (n >= 0 && n < hi);
+        const int64_t m = inh ? hlen + n : max(min(n, hi - 1), (int64_t)0);
+        const float va = (inh ? ha : xa)[m], vb = (inh ? qb : pb)[m];
+        zr[q] = in ? va : 0.f;
+        zi[q] = in && two ? vb : 0.f;
     }
 }
 

@@ -168,9 +168,10 @@ struct alignas(16) McTab {
 // Header words of a workspace: look-back error bit, look-back epoch,
 // whether any section needs the FP64 carry (the filter kernels come in two
 // variants; the one that does not match this word exits at once), the memory
-// of a short-memory chain (V | 1, V a multiple of 64; 0: none), and the epoch of
-// the last run in which its kernel met a value that is not finite.
-enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5 };
+// of a short-memory chain (V | 1, V a multiple of 64; 0: none), the epoch of
+// the last run in which its kernel met a value that is not finite, and the
+// blocks of chain_last_kernel that are done (0 between launches).
+enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5, HDR_DONE = 6 };
 
 // Short-memory chains: an FFT FIR, or a FIR with bf16 or fp16 operands, with a
 // cascade of up to CASC_MAX sections whose impulse response has died out within FFT16_MEM samples is one FIR, and
@@ -323,7 +324,7 @@ struct alignas(16) ClipDesc {
     int64_t C, N, ldx, ldy;
     int64_t blk0, tab0, rec0;
     int64_t ntiles, cpad;
-    int32_t S, vec;
+    int32_t S, reserved;
 };
 
 struct BatchLayout {

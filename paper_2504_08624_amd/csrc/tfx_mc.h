@@ -246,17 +246,15 @@ static __device__ void mc_cascade_tile(float *lds, const McCtx &m, int tid) {
 }
 
 // Stages the tile of a channel pair into X: src[g] (null: the channel does
-// not exist) holds rem samples from the tile's start (zeros past rem);
-// vec: rows 16-byte aligned.
-__device__ __forceinline__ void mc_stage_pair(float *X, const float *const (&src)[GROUPS], int64_t rem, bool vec,
-                                              int tid) {
+// not exist) holds rem samples from the tile's start (zeros past rem).
+__device__ __forceinline__ void mc_stage_pair(float *X, const float *const (&src)[GROUPS], int64_t rem, int tid) {
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
         float *dst = X + g * MC_NCH * MC_XS;
-        if (src[g] && vec && rem >= T) {
+        if (src[g] && rem >= T) {
             float4 t4[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) t4[k] = reinterpret_cast<const float4 *>(src[g])[tid + WG * k];
+            for (int k = 0; k < 3; ++k) t4[k] = load4u(src[g] + 4 * (tid + WG * k));
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 const int j = 4 * (tid + WG * k);
@@ -270,18 +268,16 @@ __device__ __forceinline__ void mc_stage_pair(float *X, const float *const (&src
 
 // Writes the pair's output chunks from X: dst[g] (null: skip) receives rem
 // samples (at most one tile).
-__device__ __forceinline__ void mc_store_pair(const float *X, float *const (&dst)[GROUPS], int64_t rem, bool vec,
-                                              int tid) {
+__device__ __forceinline__ void mc_store_pair(const float *X, float *const (&dst)[GROUPS], int64_t rem, int tid) {
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
         if (!dst[g]) continue;
         const float *src = X + g * MC_NCH * MC_XS;
-        if (vec && rem >= T) {
+        if (rem >= T) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 const int j = 4 * (tid + WG * k);
-                reinterpret_cast<float4 *>(dst[g])[tid + WG * k] =
-                    *reinterpret_cast<const float4 *>(src + MC_XS * (j >> 5) + (j & 31));
+                store4u(dst[g] + j, *reinterpret_cast<const float4 *>(src + MC_XS * (j >> 5) + (j & 31)));
             }
         } else {
             for (int j = tid; j < T; j += WG)

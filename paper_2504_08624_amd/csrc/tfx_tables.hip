@@ -664,6 +664,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
             a.hdr[HDR_HIQ] = s_any;
             a.hdr[HDR_BAD] = 0u;
             a.hdr[HDR_SHORT] = 0u;
+            a.hdr[HDR_DONE] = 0u;
         }
     }
     if (bid < a.n16) {
@@ -903,6 +904,7 @@ __global__ void header_init_kernel(uint32_t *hdr) {
     hdr[HDR_HIQ] = 0u;
     hdr[HDR_SHORT] = 0u;
     hdr[HDR_BAD] = 0u;
+    hdr[HDR_DONE] = 0u;
 }
 
 hipError_t launch_header_init(void *ws, size_t ws_bytes, hipStream_t st) {

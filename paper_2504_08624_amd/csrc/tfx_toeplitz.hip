@@ -64,7 +64,6 @@ struct TzArgs {
     int32_t Q;            // frame lags
     int64_t nft;          // frame tiles per channel
     const void *bhi, *blo;
-    int32_t vec;          // x rows 16-byte aligned
     const float *hist;    // streaming: the M - 1 inputs before the block, [C][M - 1] (null = zeros)
     int64_t ldh;          // M - 1
 };
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(64 * TWAVES) void toeplitz_kernel(TzArgs a) {
         __syncthreads();
         const int total = nrows * (TP / 4);
         const int64_t nlo = fbase * TP, nhi = (fbase + nrows) * TP;
-        if (a.vec && nlo >= 0 && nhi <= a.N) {
+        if (nlo >= 0 && nhi <= a.N) {
             // inside the signal: TZ_SU four-sample loads in flight per thread
             for (int e0 = tid; e0 < total; e0 += TZ_SU * 64 * TWAVES) {
                 float4 t[TZ_SU];
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(64 * TWAVES) void toeplitz_kernel(TzArgs a) {
                 for (int k = 0; k < TZ_SU; ++k) {
                     // clamped, not skipped: loads inside a branch are each waited for
                     const int e = min(e0 + k * 64 * TWAVES, total - 1);
-                    t[k] = *reinterpret_cast<const float4 *>(xc + nlo + 4 * e);
+                    t[k] = load4u(xc + nlo + 4 * e);
                 }
 #pragma unroll
                 for (int k = 0; k < TZ_SU; ++k) {
@@ -142,8 +141,8 @@ __global__ __launch_bounds__(64 * TWAVES) void toeplitz_kernel(TzArgs a) {
             const int row = e / (TP / 4), c4 = e % (TP / 4);
             const int64_t n = (fbase + row) * TP + 4 * c4;
             float v4[4];
-            if (a.vec && n >= 0 && n + 3 < a.N) {
-                const float4 t = *reinterpret_cast<const float4 *>(xc + n);
+            if (n >= 0 && n + 3 < a.N) {
+                const float4 t = load4u(xc + n);
                 v4[0] = t.x;
                 v4[1] = t.y;
                 v4[2] = t.z;
@@ -299,7 +298,6 @@ hipError_t launch_toeplitz(const float *x, float *y, int64_t C, int64_t N, int64
     const int64_t n = 2 * (int64_t)a.Q * 64 * 8;
     a.bhi = tab;
     a.blo = static_cast<const char *>(tab) + n * 2;
-    a.vec = (reinterpret_cast<uintptr_t>(x) % 16 == 0 && ldx % 4 == 0) ? 1 : 0;
     a.hist = M > 1 ? hist : nullptr;
     a.ldh = M - 1;
     const dim3 grid((unsigned)(C * a.nft)), block(64 * TWAVES);

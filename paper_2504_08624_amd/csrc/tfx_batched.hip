@@ -90,7 +90,8 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
     const int64_t id = blockIdx.x;
     find_clip(a, id, tid, &s_clip, &s_epoch);
     __syncthreads();
-    const ClipDesc &d = a.desc[s_clip];
+    const int clip = __builtin_amdgcn_readfirstlane(s_clip);  // the descriptor by scalar loads
+    const ClipDesc &d = a.desc[clip];
     const uint32_t epoch = s_epoch;
     const int64_t npairs = d.cpad / 2, local = id - d.blk0;
     const int64_t tile = local / npairs, pair = local % npairs;
@@ -104,12 +105,9 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
         // tables, then the cascade look-back area
         float *cr = reinterpret_cast<float *>(s_dyn + S * sizeof(SecLdsC));
         float *cT = cr, *cM = cr + 3 * DD + grp * DD, *cE = cr + (3 + GROUPS) * DD + 32 * grp, *cP = cE + 16;
-        const CascTab &ct = a.ctab[s_clip];
+        const CascTab &ct = a.ctab[clip];
         stage_tables(s_tabc, a.tab, (int)d.tab0, S, tid, WG);
-        for (int e = tid; e < 3 * DD; e += WG) {
-            const int k = e / DD, i = (e % DD) / D, j = e % D;
-            cT[e] = ct.T[k][i][j];
-        }
+        stage_powers(cT, ct, D, tid);
         stage_tile<LC>(stg, d.x + ch * d.ldx + n0, d.N - n0, valid, gl);
         __syncthreads();
         load_chunk<LC>(stg, gl, v);
@@ -121,9 +119,9 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
                 float e0, e1, E0, E1;
                 const int buf = (s & 1) * GROUPS + grp;
                 if (s + 1 < S)
-                    casc_section_a<LC, true>(s_tabc[s], v, lane, gw, s_agg, buf, e0, e1, E0, E1);
+                    casc_section_a<LC, true, false>(s_tabc[s], nullptr, v, lane, gw, s_agg, buf, e0, e1, E0, E1);
                 else
-                    casc_section_a<LC, false>(s_tabc[s], v, lane, gw, s_agg, buf, e0, e1, E0, E1);
+                    casc_section_a<LC, false, false>(s_tabc[s], nullptr, v, lane, gw, s_agg, buf, e0, e1, E0, E1);
                 if (s == 0) {
                     eA0 = e0;
                     eA1 = e1;
@@ -158,7 +156,7 @@ __global__ __launch_bounds__(WG) void batch_kernel(BatchArgs a) {
                     fold_prefix(tb, lane, gw, cP[0], cP[1], e0, e1);
                     section_from<LC>(tb.coef, v, e0, e1, -1, c1, c2);
                 } else {
-                    casc_section_c<LC, false>(tb, v, lane, gw, cP[2 * s], cP[2 * s + 1], s_agg,
+                    casc_section_c<LC, false, false>(tb, nullptr, v, lane, gw, cP[2 * s], cP[2 * s + 1], s_agg,
                                               (s & 1) * GROUPS + grp, -1, c1, c2);
                 }
             }
@@ -218,7 +216,8 @@ __global__ __launch_bounds__(WG, 4) void batch_mc_kernel(BatchArgs a) {
     const int64_t id = blockIdx.x;
     find_clip(a, id, tid, &s_clip, &s_epoch);
     __syncthreads();
-    const ClipDesc &d = a.desc[s_clip];
+    const int clip = __builtin_amdgcn_readfirstlane(s_clip);  // the descriptor by scalar loads
+    const ClipDesc &d = a.desc[clip];
     const int64_t npairs = d.cpad / 2, local = id - d.blk0;
     const int64_t tile = local / npairs, pair = local % npairs;
     const int64_t n0 = tile * T, rem = d.N - n0;
@@ -228,8 +227,8 @@ __global__ __launch_bounds__(WG, 4) void batch_mc_kernel(BatchArgs a) {
     mc_stage_pair(lds, src, rem, tid);
     if (d.S > 0) {  // block-uniform
         McCtx m;
-        m.mt = &a.mtab[s_clip];
-        m.ct = &a.ctab[s_clip];
+        m.mt = &a.mtab[clip];
+        m.ct = &a.ctab[clip];
         m.S = d.S;
         m.pos = tile;
         m.epoch = s_epoch;

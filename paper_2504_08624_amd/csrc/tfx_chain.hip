@@ -555,7 +555,7 @@ __device__ void run_section(const KArgs &a, const TB &tb, int s, float (&v)[L], 
 // the row's components by lane shuffles.  F is block lower triangular, and
 // so are its powers.  The powers are read from LDS (zt_stage): mb[(i D + j)
 // 16 + b] = (F^(L b))[i][j] and ma[(a D + j) 16 + i] = (F^(16 L a))[i][j];
-// G, read at lane-uniform indices, from global memory.
+// G, the same for every lane, comes by scalar loads.
 template <int D>
 __device__ __forceinline__ void casc_zir_add(float (&v)[L], const CascZir *zt, const float *mb, const float *P, int k) {
     const int a = k >> 4, b = k & 15, ri = k & 15;
@@ -574,8 +574,9 @@ __device__ __forceinline__ void casc_zir_add(float (&v)[L], const CascZir *zt, c
         float zi = 0.f;  // component i of F^(L b) R_a
 #pragma unroll
         for (int j = 0; j < (i | 1) + 1; ++j) zi = fmaf(mb[(i * D + j) * 16 + b], r[j], zi);
+        const const_float *g = as_const(&zt->G[i][0]);
 #pragma unroll
-        for (int q = 0; q < L; ++q) v[q] = fmaf(zt->G[q][i], zi, v[q]);
+        for (int q = 0; q < L; ++q) v[q] = fmaf(g[q], zi, v[q]);
     }
 }
 
@@ -731,18 +732,14 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         // a signal of one tile (a stream's block) enters it with a known state
         // and has nothing to publish: phase C alone
         const bool alone = STOUT && a.ntiles == 1;
-        if (!alone)
-            for (int e = c.tid; e < 3 * DD; e += WG) {  // read in phase B, after phase A's barriers
-                const int k = e / DD, i = (e % DD) / D, j = e % D;
-                cT[e] = a.casc->T[k][i][j];
-            }
+        if (!alone) stage_powers(cT, *a.casc, D, c.tid);  // read in phase B, after phase A's barriers
         // (A) zero tile-entering state: the cascade's tile aggregate and its
         //     response to the tile's input
         float eA0 = 0.f, eA1 = 0.f;
         for (int s = 0; !alone && s < a.S; ++s) {
             float e0, e1, E0, E1;
             const int buf = (s & 1) * GROUPS + c.grp;
-            casc_section_a<L, true>(s_tabc[s], v, c.lane, c.gw, s_agg, buf, e0, e1, E0, E1);
+            casc_section_a<L, true, true>(s_tabc[s], as_const(a.tab[s].zir), v, c.lane, c.gw, s_agg, buf, e0, e1, E0, E1);
             if (s == 0) {
                 eA0 = e0;
                 eA1 = e1;
@@ -789,14 +786,14 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
             if (s == 0 && !alone) {
                 float e0 = eA0, e1 = eA1;
                 fold_prefix(tb, c.lane, c.gw, cP[0], cP[1], e0, e1);
-                if (STOUT && c.is_last) section_from<L, true>(tb.coef, v, e0, e1, r_cap, c1, c2);
-                else section_from<L>(tb.coef, v, e0, e1, -1, c1, c2);
+                if (STOUT && c.is_last) section_from<L, true, true>(tb.coef, v, e0, e1, r_cap, c1, c2);
+                else section_from<L, false, true>(tb.coef, v, e0, e1, -1, c1, c2);
             } else {
                 const int buf = (s & 1) * GROUPS + c.grp;
                 if (STOUT && c.is_last)
-                    casc_section_c<L, true>(tb, v, c.lane, c.gw, cP[2 * s], cP[2 * s + 1], s_agg, buf, r_cap, c1, c2);
+                    casc_section_c<L, true, true>(tb, nullptr, v, c.lane, c.gw, cP[2 * s], cP[2 * s + 1], s_agg, buf, r_cap, c1, c2);
                 else
-                    casc_section_c<L, false>(tb, v, c.lane, c.gw, cP[2 * s], cP[2 * s + 1], s_agg, buf, -1, c1, c2);
+                    casc_section_c<L, false, true>(tb, as_const(a.tab[s].zir), v, c.lane, c.gw, cP[2 * s], cP[2 * s + 1], s_agg, buf, -1, c1, c2);
             }
             if (STOUT && r_cap >= 0 && c.valid && a.state_out) {
                 a.state_out[(c.ch * a.S + s) * 2 + 0] = c1;
@@ -1033,7 +1030,7 @@ static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t s
         // without one (tables or matrix cores instead of a second pass of every
         // section), then the last one, on the same records (12 x 5.29 M, odd
         // length, 4 sections: 389 us a call with the second pass everywhere and
-        // one-sample row accesses, 206 us now)
+        // one-sample row accesses, 190 us now)
         const int64_t np = k.cpad / 2;
         if (k.ntiles > 1) {
             KArgs m = k;

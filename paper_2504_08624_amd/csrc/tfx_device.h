@@ -705,9 +705,10 @@ __device__ void carry(const TB &tb, const CarryCtx &cc, float z0, float z1, floa
         t1 = dpp<DPP_ROW_BCAST31, 0xC>(w1);
         madd2<TR>(w0, w1, Tab<CT>::fold(tb, (lane & 31) + 1), t0, t1);
     }
+    CT *ag = reinterpret_cast<CT *>(&s_agg[buf][0][0]);  // [GWAVES][2]
     if (lane == 63) {
-        s_agg[buf][cc.gw][0] = (double)w0;
-        s_agg[buf][cc.gw][1] = (double)w1;
+        ag[2 * cc.gw] = w0;
+        ag[2 * cc.gw + 1] = w1;
     }
     __syncthreads();
     // wave-entering states for a zero tile-entering state; E ends as the
@@ -720,7 +721,7 @@ __device__ void carry(const TB &tb, const CarryCtx &cc, float z0, float z1, floa
             ew0 = E0;
             ew1 = E1;
         }
-        CT g0 = (CT)s_agg[buf][w][0], g1 = (CT)s_agg[buf][w][1];
+        CT g0 = ag[2 * w], g1 = ag[2 * w + 1];
         madd2<TR>(g0, g1, Psi, E0, E1);
         E0 = g0;
         E1 = g1;
@@ -780,9 +781,10 @@ __device__ void carry_local(const TB &tb, int lane, int gw, float z0, float z1, 
         t1 = dpp<DPP_ROW_BCAST31, 0xC>(w1);
         madd2<false>(w0, w1, Tab<CT>::fold(tb, (lane & 31) + 1), t0, t1);
     }
+    CT *ag = reinterpret_cast<CT *>(&s_agg[buf][0][0]);  // [GWAVES][2]
     if (lane == 63) {
-        s_agg[buf][gw][0] = (double)w0;
-        s_agg[buf][gw][1] = (double)w1;
+        ag[2 * gw] = w0;
+        ag[2 * gw + 1] = w1;
     }
     __syncthreads();
     const CT *Psi = Tab<CT>::psi(tb, 1);
@@ -793,7 +795,7 @@ __device__ void carry_local(const TB &tb, int lane, int gw, float z0, float z1, 
             ew0 = A0;
             ew1 = A1;
         }
-        CT g0 = (CT)s_agg[buf][w][0], g1 = (CT)s_agg[buf][w][1];
+        CT g0 = ag[2 * w], g1 = ag[2 * w + 1];
         madd2<false>(g0, g1, Psi, A0, A1);
         A0 = g0;
         A1 = g1;
@@ -809,19 +811,49 @@ __device__ void carry_local(const TB &tb, int lane, int gw, float z0, float z1, 
 }
 
 // ---------------------------------------------- cascade-level section form
-// TDF-II over the chunk from (s1, s2), in place; with CAP the state after
+// Values of an earlier kernel that are the same for the whole wave, read
+// through the constant address space: scalar loads into scalar registers (from
+// a plain pointer they are vector loads, one register a lane for each value,
+// since the compiler cannot tell that no store of this kernel goes there).
+typedef __attribute__((address_space(4))) float const_float;
+__device__ __forceinline__ const const_float *as_const(const float *p) {
+    return (const const_float *)(uintptr_t)p;
+}
+
+// One sample of a section.  ST: by its state, y = s1 + b0 x, s' = A s + B x (A
+// the one-sample transition): as many operations as with y fed back, a chain of
+// two from sample to sample instead of three, and y's rounding stays out of the
+// state (6 sections from 100 Hz up, blocks of 3000 samples: error 2.1e-5 with y
+// fed back, 1.0e-5 so).
+template <bool ST>
+struct SecStep {
+    float b0, c1, c2, a1, a2;
+    __device__ __forceinline__ explicit SecStep(const float *co)
+        : b0(co[0]), c1(ST ? fmaf(-co[3], co[0], co[1]) : co[1]), c2(ST ? fmaf(-co[4], co[0], co[2]) : co[2]),
+          a1(co[3]), a2(co[4]) {}
+    __device__ __forceinline__ float step(float x, float &s1, float &s2) const {
+        const float y = fmaf(b0, x, s1);
+        if (ST) {
+            const float n1 = fmaf(-a1, s1, fmaf(c1, x, s2));
+            s2 = fmaf(-a2, s1, c2 * x);
+            s1 = n1;
+        } else {
+            s1 = fmaf(c1, x, fmaf(-a1, y, s2));
+            s2 = fmaf(c2, x, -a2 * y);
+        }
+        return y;
+    }
+};
+
+// The section over the chunk from (s1, s2), in place; with CAP the state after
 // sample r_cap (if 0 <= r_cap < LC) is returned in (c1, c2).
-template <int LC, bool CAP = false>
+template <int LC, bool CAP = false, bool ST = false>
 __device__ __forceinline__ void section_from(const float *co, float (&v)[LC], float s1, float s2, int r_cap,
                                              float &c1, float &c2) {
-    const float b0 = co[0], b1 = co[1], b2 = co[2], a1 = co[3], a2 = co[4];
+    const SecStep<ST> c(co);
 #pragma unroll
     for (int r = 0; r < LC; ++r) {
-        const float xv = v[r];
-        const float yv = fmaf(b0, xv, s1);
-        s1 = fmaf(b1, xv, fmaf(-a1, yv, s2));
-        s2 = fmaf(b2, xv, -a2 * yv);
-        v[r] = yv;
+        v[r] = c.step(v[r], s1, s2);
         if (CAP && r == r_cap) {
             c1 = s1;
             c2 = s2;
@@ -838,39 +870,16 @@ __device__ __forceinline__ void fold_prefix(const TB &tb, int lane, int gw, floa
     madd2<false>(e0, e1, Tab<float>::fold(tb, lane), x0, x1);
 }
 
-// Phase-A form of a section (zero tile-entering state): zero-state response
-// over the chunk, the in-tile carry to the chunk-entering state e, and the
-// zero-input response of e added in place.  !RUN: only the state is needed
-// (the last section), so the zero-state pass keeps no output and no
-// correction follows.
-template <int LC, bool RUN>
-__device__ __forceinline__ void casc_section_a(const SecLdsC &tb, float (&v)[LC], int lane, int gw,
-                                               double (*s_agg)[GWAVES][2], int buf, float &e0, float &e1, float &E0,
-                                               float &E1) {
-    const float b0 = tb.coef[0], b1 = tb.coef[1], b2 = tb.coef[2], a1 = tb.coef[3], a2 = tb.coef[4];
-    float s1 = 0.f, s2 = 0.f;
-    if (RUN) {
+// v[r] += the section's zero-input response at sample r of the chunk to the
+// chunk-entering state (z1, z2).  With SecTab's P_r (P not null) two operations
+// a sample, by stepping the state three and a chain through the chunk.
+template <int LC>
+__device__ __forceinline__ void add_zir(float (&v)[LC], const const_float *P, float a1, float a2, float z1, float z2) {
+    if (P) {
+        v[0] += z1;
 #pragma unroll
-        for (int r = 0; r < LC; ++r) {
-            const float xv = v[r];
-            const float yv = fmaf(b0, xv, s1);
-            s1 = fmaf(b1, xv, fmaf(-a1, yv, s2));
-            s2 = fmaf(b2, xv, -a2 * yv);
-            v[r] = yv;
-        }
-    } else {  // s' = A s + B x: 4 operations a sample
-        const float B0 = fmaf(-a1, b0, b1), B1 = fmaf(-a2, b0, b2);
-#pragma unroll
-        for (int r = 0; r < LC; ++r) {
-            const float xv = v[r];
-            const float n1 = fmaf(B0, xv, fmaf(-a1, s1, s2));
-            s2 = fmaf(B1, xv, -a2 * s1);
-            s1 = n1;
-        }
-    }
-    carry_local<float, SecLdsC>(tb, lane, gw, s1, s2, 0.f, 0.f, e0, e1, E0, E1, s_agg, buf);
-    if (RUN) {
-        float z1 = e0, z2 = e1;
+        for (int r = 1; r < LC; ++r) v[r] = fmaf(P[r], z1, fmaf(P[r - 1], z2, v[r]));
+    } else {
 #pragma unroll
         for (int r = 0; r < LC; ++r) {
             v[r] += z1;
@@ -881,22 +890,50 @@ __device__ __forceinline__ void casc_section_a(const SecLdsC &tb, float (&v)[LC]
     }
 }
 
-// Phase-C form (known tile-entering state P): zero-state response, carry,
-// then the zero-input response of the chunk-entering state added in place;
-// with CAP the state after sample r_cap is returned in (c1, c2).
-template <int LC, bool CAP>
-__device__ __forceinline__ void casc_section_c(const SecLdsC &tb, float (&v)[LC], int lane, int gw, float P0,
-                                               float P1, double (*s_agg)[GWAVES][2], int buf, int r_cap, float &c1,
-                                               float &c2) {
-    const float b0 = tb.coef[0], b1 = tb.coef[1], b2 = tb.coef[2], a1 = tb.coef[3], a2 = tb.coef[4];
+// The two section functions below come in two roundings.  TAB (a chain): the
+// state's form and the table of P_r.  Without it (a batch): y fed back and the
+// response stepped: at radii of .999 what bounds a clip's accuracy is the state
+// carried from tile to tile, either form is up to 1.8e-5 from the exact value,
+// and the batch is no faster with the tables (48 clips, 1 to 30 s: 777 us a call
+// without, 806 with them).
+//
+// Phase-A form of a section (zero tile-entering state): zero-state response
+// over the chunk, the in-tile carry to the chunk-entering state e, and the
+// zero-input response of e added in place.  !RUN: only the state is needed
+// (the last section), so the zero-state pass keeps no output and no
+// correction follows.
+template <int LC, bool RUN, bool TAB>
+__device__ __forceinline__ void casc_section_a(const SecLdsC &tb, const const_float *zir, float (&v)[LC], int lane,
+                                               int gw, double (*s_agg)[GWAVES][2], int buf, float &e0, float &e1,
+                                               float &E0, float &E1) {
+    const SecStep<TAB || !RUN> c(tb.coef);
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int r = 0; r < LC; ++r) {
-        const float xv = v[r];
-        const float yv = fmaf(b0, xv, s1);
-        s1 = fmaf(b1, xv, fmaf(-a1, yv, s2));
-        s2 = fmaf(b2, xv, -a2 * yv);
-        v[r] = yv;
+        if (RUN) {
+            v[r] = c.step(v[r], s1, s2);
+        } else {  // s' = A s + B x: 4 operations a sample
+            const float n1 = fmaf(c.c1, v[r], fmaf(-c.a1, s1, s2));
+            s2 = fmaf(c.c2, v[r], -c.a2 * s1);
+            s1 = n1;
+        }
+    }
+    carry_local<float, SecLdsC>(tb, lane, gw, s1, s2, 0.f, 0.f, e0, e1, E0, E1, s_agg, buf);
+    if (RUN) add_zir<LC>(v, TAB ? zir : nullptr, c.a1, c.a2, e0, e1);
+}
+
+// Phase-C form (known tile-entering state P): zero-state response, carry,
+// then the zero-input response of the chunk-entering state added in place;
+// with CAP the state after sample r_cap is returned in (c1, c2).
+template <int LC, bool CAP, bool TAB>
+__device__ __forceinline__ void casc_section_c(const SecLdsC &tb, const const_float *zir, float (&v)[LC], int lane,
+                                               int gw, float P0, float P1, double (*s_agg)[GWAVES][2], int buf,
+                                               int r_cap, float &c1, float &c2) {
+    const SecStep<TAB> c(tb.coef);
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int r = 0; r < LC; ++r) {
+        v[r] = c.step(v[r], s1, s2);
         if (CAP && r == r_cap) {
             c1 = s1;
             c2 = s2;
@@ -904,13 +941,17 @@ __device__ __forceinline__ void casc_section_c(const SecLdsC &tb, float (&v)[LC]
     }
     float z1, z2, E0, E1;
     carry_local<float, SecLdsC>(tb, lane, gw, s1, s2, P0, P1, z1, z2, E0, E1, s_agg, buf);
+    if (!CAP) {
+        add_zir<LC>(v, TAB ? zir : nullptr, c.a1, c.a2, z1, z2);
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < LC; ++r) {
         v[r] += z1;
-        const float n1 = fmaf(-a1, z1, z2);
-        z2 = -a2 * z1;
+        const float n1 = fmaf(-c.a1, z1, z2);
+        z2 = -c.a2 * z1;
         z1 = n1;
-        if (CAP && r == r_cap) {  // state after the sample = zero-state + zero-input states
+        if (r == r_cap) {  // state after the sample = zero-state + zero-input states
             c1 += z1;
             c2 += z2;
         }
@@ -944,6 +985,19 @@ __device__ __forceinline__ float row_matvec(const float *Tm, int D, int c, float
     const float *tr = Tm + (c < D ? c : 0) * D;
     for (int d = 0; d < D; ++d) acc = fmaf(tr[d], __shfl(v, src_row * 16 + d), acc);
     return c < D ? acc : 0.f;
+}
+
+// The tile-transition powers of the look-back into LDS, D x D each (WG threads).
+__device__ __forceinline__ void stage_powers(float *cT, const CascTab &t, int D, int tid) {
+    const int i = tid >> 4, j = tid & 15;
+    static_assert(WG == 256, "one thread per element of a 16 x 16 power");
+    if (i < D && j < D) {
+        const float t0 = t.T[0][i][j], t1 = t.T[1][i][j], t2 = t.T[2][i][j];
+        float *p = cT + i * D + j;
+        p[0] = t0;
+        p[D * D] = t1;
+        p[2 * D * D] = t2;
+    }
 }
 
 __device__ void casc_lookback(const CascCtx &cc, const float *T, const float *E, float *P, float *Mw) {

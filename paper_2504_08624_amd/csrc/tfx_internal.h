@@ -64,7 +64,11 @@ struct alignas(16) SecTab {
     float fold[64][4];       // Phi^k, k = 0..63
     float psi[GWAVES][4];    // Psi^w, w < GWAVES
     float lb[9][4];          // PhiT^(2^j), j = 0..8
-    double fold_d[64][4];
+    union {
+        double fold_d[64][4];  // sections with the FP64 carry
+        float zir[32];         // the others: P_r = (A^r)_00, A the one-sample transition; a chunk-entering
+                               // state e moves sample r of the chunk by P_r e_0 + P_(r-1) e_1
+    };
     double psi_d[GWAVES][4];
     double lb_d[9][4];
 };
@@ -122,13 +126,13 @@ struct alignas(16) CascTab {
 // maps the state to the cascade output under zero input, G[r] = c F^r.  The
 // output of a tile is its zero-entering-state response plus
 // G[r] . (F^(L k) P) at sample r of chunk k, P being the state entering the
-// tile.  With k = 16 a + b, F^(L k) = F^(L b) F^(16 L a): Mb[i][j][b] =
+// tile (the table holds component i's L values in row i).  With k = 16 a + b, F^(L k) = F^(L b) F^(16 L a): Mb[i][j][b] =
 // (F^(L b))[i][j] (b < 16) and MaT[a][j][i] = (F^(16 L a))[i][j] (a < 8),
 // both with the lane's index (b, i) innermost: the kernel copies the rows
 // j < 2S of both into LDS as they are.
 constexpr int ZIR_B = 16, ZIR_A = GL / ZIR_B;
 struct alignas(16) CascZir {
-    float G[L][16];
+    float G[16][L];
     float Mb[16][16][ZIR_B];
     float MaT[ZIR_A][16][16];
 };

@@ -146,10 +146,7 @@ static __device__ void mc_cascade_tile(float *lds, const McCtx &m, int tid) {
         const int K = 48 * w + 16 * cb + lc;
         *reinterpret_cast<mcf4 *>(U + MC_US * K + 4 * lq) = acc[2][cb];
     }
-    for (int e = tid; e < 3 * DD; e += WG) {  // tile-transition powers for the look-back
-        const int k = e / DD, i = (e % DD) / D, j = e % D;
-        cT[e] = m.ct->T[k][i][j];
-    }
+    stage_powers(cT, *m.ct, D, tid);
     const int ri = lane & 15, sg = 4 * w + lq, K0 = MC_SEG * sg;  // segment sg: chunks K0 .. K0 + 11
     float fr[16];
     mc_load16(fr, mt->Fr[ri]);

@@ -73,9 +73,16 @@ __device__ void build_section_block(SecTab *tb, const float *co, int Lc, int tid
     mat2_pow(Psi, GWAVES, W);
     if (tid == 0) s_dep = 65;
     __syncthreads();
+    const bool hiq = section_hiq(a1, a2);
+    if (tid >= 64 && tid < 64 + 32 && !hiq) {
+        mat2_pow(A, tid - 64, R);
+        tb->zir[tid - 64] = (float)R[0];
+    }
     if (tid < 64) {
         mat2_pow(Phi, tid, R);
-        put4(tb->fold[tid], tb->fold_d[tid], R);
+        for (int q = 0; q < 4; ++q) tb->fold[tid][q] = (float)R[q];
+        if (hiq)
+            for (int q = 0; q < 4; ++q) tb->fold_d[tid][q] = R[q];
         mat2_pow(W, tid + 1, R);
         if (mat2_maxabs(R) <= DEPTH_EPS) atomicMin(&s_dep, tid + 1);
     }
@@ -92,7 +99,7 @@ __device__ void build_section_block(SecTab *tb, const float *co, int Lc, int tid
         for (int i = 0; i < 5; ++i) tb->coef[i] = co[i];
         tb->pad = 0;
         tb->depth = s_dep > 64 ? 0 : s_dep;
-        tb->hiq = section_hiq(a1, a2) ? 1 : 0;
+        tb->hiq = hiq ? 1 : 0;
     }
 }
 
@@ -237,7 +244,7 @@ __device__ void zir_block(char *raw, Co co_at, int32_t S, int Lc, int k, CascZir
     for (int r = 0; r < Lc; ++r) {  // G[r] = g, then g <- g F
         double acc = 0.0;
         if (tid < 16) {
-            out->G[r][tid] = (float)g[tid];
+            out->G[tid][r] = (float)g[tid];
             for (int q = 0; q < 16; ++q) acc += g[q] * Fm[q][tid];
         }
         __syncthreads();
@@ -773,14 +780,20 @@ __global__ __launch_bounds__(256) void batch_prep_kernel(BatchPrepArgs a) {
         }
         a.map[b] = lo;
     }
-    if (blockIdx.x == 0 && tid == 0) {
-        a.hdr[HDR_ERROR] = 0u;
-        a.hdr[HDR_EPOCH] = 1u;
+    if (blockIdx.x == gridDim.x - 1) {  // (the first blocks have the longest roles)
+        // eight threads a clip (by one thread in turn it was the kernel's length)
         uint32_t any = 0u;
-        for (int c = 0; c < a.nclips; ++c)
-            for (int s = 0; s < a.desc[c].S; ++s)
-                any |= section_hiq(a.desc[c].sos[5 * s + 3], a.desc[c].sos[5 * s + 4]) ? 1u : 0u;
-        a.hdr[HDR_HIQ] = any;
+        for (int c = tid >> 3; c < a.nclips; c += 32) {
+            const float *co = a.desc[c].sos;
+            const int S = a.desc[c].S;
+            for (int s = tid & 7; s < S; s += 8) any |= section_hiq(co[5 * s + 3], co[5 * s + 4]) ? 1u : 0u;
+        }
+        any = __syncthreads_or(any);
+        if (tid == 0) {
+            a.hdr[HDR_ERROR] = 0u;
+            a.hdr[HDR_EPOCH] = 1u;
+            a.hdr[HDR_HIQ] = any ? 1u : 0u;
+        }
     }
     const int64_t nroles = a.nsec + (a.ctab ? a.nclips : 0) + (a.mtab ? a.nclips : 0);
     for (int64_t g = blockIdx.x; g < nroles; g += gridDim.x) {

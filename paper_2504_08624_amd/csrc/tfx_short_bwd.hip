@@ -133,83 +133,129 @@ struct ShortGradArgs {
     float *gh;
 };
 
-// Block k1, thread k2: bin k = k1 + 128 k2.  With R the summed spectrum, Hf the
+// Block k1: bins k = k1 + 128 k2.  With R the summed spectrum, Hf the
 // FIR's response and H_s = B_s / A_s the sections', T_s = R conj(Hf prod_{t != s}
 // H_t / A_s) gives the bin's shares of section s's gradients: Re T_s conj(z^i)
 // for b_i, -Re T_s conj(H_s z^i) for a_i (z = e^{-2 pi i k / N}).  The tap
 // gradient is the inverse transform of Q = R conj(prod H_t); its first half, for
 // j = j1 + 128 j2, B[k1][j1] = sum_k2 Q(k) e^{2 pi i k2 j1 / 128}, is done here.
-__global__ __launch_bounds__(128) void short_grad_kernel(ShortGradArgs a) {
+//
+// 16384 bins are few for the chip, so the time is one wave's instructions: four
+// threads share a bin (two sections each, a quarter of the sums over k2), the
+// sums over the bins go through LDS, a row a wave (64 x 192000, 8 sections: 17.7
+// us with one thread a bin and every sum in every wave, 9.2 us so).
+__global__ __launch_bounds__(512) void short_grad_kernel(ShortGradArgs a) {
     __shared__ double co[CASC_MAX][5];
-    __shared__ double2 q[128];
-    __shared__ double wsum[2][5 * CASC_MAX];
+    __shared__ double2 q[128], sH[CASC_MAX][128];
+    __shared__ double sv[5 * CASC_MAX][128];  // first the splits' sums, [4][128] double2, at the end the parts of B
     if (!short_done(a.hdr)) return;
-    const int k1 = blockIdx.x, t = threadIdx.x, k = k1 + 128 * t;
+    const int tid = threadIdx.x, t = tid & 127, g = tid >> 7;  // bin k2 = t, share g
+    const int k1 = blockIdx.x, k = k1 + 128 * t;
     const int S = a.S;
-    if (t < 5 * S) {
-        int s = t / 5, st = 0;
+    const int pos = spec_at(k);
+    static_assert(SB_SPLITS % 4 == 0 && CASC_MAX == 8, "shares of the four threads of a bin");
+    double2 Rk = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int w = 0; w < SB_SPLITS / 4; ++w) {
+        const double2 v = a.sum1[(int64_t)(4 * w + g) * NB + pos];
+        Rk.x += v.x;
+        Rk.y += v.y;
+    }
+    const double2 hf = a.hf[k];
+    if (tid < 5 * S) {
+        int s = tid / 5, st = 0;
         while (s >= a.sos.len[st]) {
             s -= a.sos.len[st];
             ++st;
         }
-        co[t / 5][t % 5] = (double)a.sos.ptr[st][5 * s + t % 5];
+        co[tid / 5][tid % 5] = (double)a.sos.ptr[st][5 * s + tid % 5];
     }
-    __syncthreads();
-    const int pos = spec_at(k);
-    double2 Rk = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int w = 0; w < SB_SPLITS; ++w) {
-        const double2 v = a.sum1[(int64_t)w * NB + pos];
-        Rk.x += v.x;
-        Rk.y += v.y;
-    }
+    double2 *part = reinterpret_cast<double2 *>(&sv[0][0]);
+    part[128 * g + t] = Rk;
     double2 z;
     sincospi(-2.0 * (double)k / NB, &z.y, &z.x);
     const double2 z2 = cm(z, z);
-    double2 H[CASC_MAX], iA[CASC_MAX], pre[CASC_MAX], acc = make_double2(1.0, 0.0);
+    __syncthreads();
+    double2 iA[2];
 #pragma unroll
-    for (int s = 0; s < CASC_MAX; ++s) {
+    for (int u = 0; u < 2; ++u) {
+        const int s = g + 4 * u;
         if (s < S) {
             const double2 n = make_double2(co[s][0] + co[s][1] * z.x + co[s][2] * z2.x, co[s][1] * z.y + co[s][2] * z2.y);
             const double2 d = make_double2(1.0 + co[s][3] * z.x + co[s][4] * z2.x, co[s][3] * z.y + co[s][4] * z2.y);
             const double r = 1.0 / fma(d.x, d.x, d.y * d.y);
-            iA[s] = make_double2(d.x * r, -d.y * r);
-            H[s] = cm(n, iA[s]);
-            pre[s] = acc;
-            acc = cm(acc, H[s]);
+            iA[u] = make_double2(d.x * r, -d.y * r);
+            sH[s][t] = cm(n, iA[u]);
         }
     }
-    q[t] = cmc(Rk, acc);
-    double2 X = cmc(Rk, a.hf[k]);  // R conj(Hf prod of the later sections)
+    Rk = part[t];
 #pragma unroll
-    for (int s = CASC_MAX - 1; s >= 0; --s) {
+    for (int w = 1; w < 4; ++w) {
+        Rk.x += part[128 * w + t].x;
+        Rk.y += part[128 * w + t].y;
+    }
+    __syncthreads();
+    double2 pr[2] = {make_double2(1.0, 0.0), make_double2(1.0, 0.0)}, all = make_double2(1.0, 0.0);  // without s; all
+#pragma unroll
+    for (int s = 0; s < CASC_MAX; ++s) {
         if (s < S) {
-            const double2 T = cmc(X, cm(pre[s], iA[s]));
-            const double2 U = cmc(T, H[s]);
-            double v[5] = {T.x, fma(T.x, z.x, T.y * z.y), fma(T.x, z2.x, T.y * z2.y), -fma(U.x, z.x, U.y * z.y),
-                           -fma(U.x, z2.x, U.y * z2.y)};
+            const double2 h = sH[s][t];
+            if (s != g) pr[0] = cm(pr[0], h);
+            if (s != g + 4) pr[1] = cm(pr[1], h);
+            if (g == 0) all = cm(all, h);
+        }
+    }
+    if (g == 0) q[t] = cmc(Rk, all);
+    const double2 X = cmc(Rk, hf);
 #pragma unroll
-            for (int c = 0; c < 5; ++c) {
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) v[c] += __shfl_xor(v[c], d);
-                if ((t & 63) == 0) wsum[t >> 6][5 * s + c] = v[c];
-            }
-            X = cmc(X, H[s]);
+    for (int u = 0; u < 2; ++u) {
+        const int s = g + 4 * u;
+        if (s < S) {
+            const double2 T = cmc(X, cm(pr[u], iA[u]));
+            const double2 U = cmc(T, sH[s][t]);
+            sv[5 * s][t] = T.x;
+            sv[5 * s + 1][t] = fma(T.x, z.x, T.y * z.y);
+            sv[5 * s + 2][t] = fma(T.x, z2.x, T.y * z2.y);
+            sv[5 * s + 3][t] = -fma(U.x, z.x, U.y * z.y);
+            sv[5 * s + 4][t] = -fma(U.x, z2.x, U.y * z2.y);
         }
     }
     __syncthreads();
-    if (t < 5 * S) a.part[k1 * 5 * CASC_MAX + t] = wsum[0][t] + wsum[1][t];
-    // first half of the tap gradient's inverse transform: thread t is j1
-    double2 st, w = make_double2(1.0, 0.0), b = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {  // row 8 i + wave
+        const int r = 8 * i + (tid >> 6);
+        if (r < 5 * S) {
+            double v = sv[r][tid & 63] + sv[r][64 + (tid & 63)];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+            if ((tid & 63) == 0) a.part[k1 * 5 * CASC_MAX + r] = v;
+        }
+    }
+    // first half of the tap gradient's inverse transform: j1 = t, k2 from 32 g on,
+    // whose first factor e^{2 pi i 32 g j1 / 128} is i^(g j1)
+    double2 st, w, b = make_double2(0.0, 0.0);
     sincospi((double)t / 64.0, &st.y, &st.x);
+    const int quarter = (g * t) & 3;
+    w.x = quarter == 0 ? 1.0 : quarter == 2 ? -1.0 : 0.0;
+    w.y = quarter == 1 ? 1.0 : quarter == 3 ? -1.0 : 0.0;
 #pragma unroll 4
-    for (int k2 = 0; k2 < 128; ++k2) {
+    for (int k2 = 32 * g; k2 < 32 * g + 32; ++k2) {
         const double2 v = q[k2];
         b.x = fma(v.x, w.x, fma(-v.y, w.y, b.x));
         b.y = fma(v.x, w.y, fma(v.y, w.x, b.y));
         w = cm(w, st);
     }
-    a.colsum[k1 * 128 + t] = b;
+    __syncthreads();  // the rows are summed
+    part[128 * g + t] = b;
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+        for (int u = 1; u < 4; ++u) {
+            b.x += part[128 * u + t].x;
+            b.y += part[128 * u + t].y;
+        }
+        a.colsum[k1 * 128 + t] = b;
+    }
 }
 
 // Blocks < nj: dL/dh[j] = Re sum_k1 e^{2 pi i k1 j / N} B[k1][j mod 128] / N for
@@ -326,7 +372,7 @@ hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const
                        reinterpret_cast<const float2 *>(w + l.spart), (int32_t)nwg,
                        reinterpret_cast<double2 *>(w + l.sum1), static_cast<const uint32_t *>(hdr));
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(short_grad_kernel, dim3(128), dim3(128), 0, st, r);
+    hipLaunchKernelGGL(short_grad_kernel, dim3(128), dim3(512), 0, st, r);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int32_t nj = gH ? (M + SB_LAGS - 1) / SB_LAGS : 0;
     hipLaunchKernelGGL(short_grad_out_kernel, dim3((unsigned)(nj + 1)), dim3(256), 0, st, r, nj);

@@ -72,27 +72,30 @@ __device__ void build_section_block(SecTab *tb, const float *co, int Lc, int tid
     mat2_pow(Phi, 64, Psi);
     mat2_pow(Psi, GWAVES, W);
     if (tid == 0) s_dep = 65;
-    __syncthreads();
     const bool hiq = section_hiq(a1, a2);
-    if (tid >= 64 && tid < 64 + 32 && !hiq) {
-        mat2_pow(A, tid - 64, R);
-        tb->zir[tid - 64] = (float)R[0];
-    }
-    if (tid < 64) {
-        mat2_pow(Phi, tid, R);
-        for (int q = 0; q < 4; ++q) tb->fold[tid][q] = (float)R[q];
+    __syncthreads();
+    // a wave each: the folds; the look-back depth; psi and lb; the zero-input response
+    const int wv = tid >> 6, l = tid & 63;
+    if (wv == 0) {
+        mat2_pow(Phi, l, R);
+        for (int q = 0; q < 4; ++q) tb->fold[l][q] = (float)R[q];
         if (hiq)
-            for (int q = 0; q < 4; ++q) tb->fold_d[tid][q] = R[q];
-        mat2_pow(W, tid + 1, R);
-        if (mat2_maxabs(R) <= DEPTH_EPS) atomicMin(&s_dep, tid + 1);
-    }
-    if (tid < GWAVES) {
-        mat2_pow(Psi, tid, R);
-        put4(tb->psi[tid], tb->psi_d[tid], R);
-    }
-    if (tid < 9) {
-        mat2_pow(W, 1 << tid, R);
-        put4(tb->lb[tid], tb->lb_d[tid], R);
+            for (int q = 0; q < 4; ++q) tb->fold_d[l][q] = R[q];
+    } else if (wv == 1) {
+        mat2_pow(W, l + 1, R);
+        if (mat2_maxabs(R) <= DEPTH_EPS) atomicMin(&s_dep, l + 1);
+    } else if (wv == 2) {
+        if (l < GWAVES) {
+            mat2_pow(Psi, l, R);
+            put4(tb->psi[l], tb->psi_d[l], R);
+        }
+        if (l < 9) {
+            mat2_pow(W, 1 << l, R);
+            put4(tb->lb[l], tb->lb_d[l], R);
+        }
+    } else if (l < 32 && !hiq) {
+        mat2_pow(A, l, R);
+        tb->zir[l] = (float)R[0];
     }
     __syncthreads();
     if (tid == 0) {
@@ -125,49 +128,70 @@ __device__ double cascade_f(const double (*co)[5], int D, int i, int j) {
 // each).  The cascade's one-sample transition F (zero input): block (i, i) =
 // A_i; block (i, j), j < i = B_i (prod_{j<l<i} D_l) C, since section i's
 // input is section i-1's output; Phi_T = F^(128 Lc) = (F^Lc)^128.
-__device__ void mm16(const double (*A)[16], const double (*B)[16], double (*R)[16], int i, int j) {
+// A block's time is these products one after another, and a product's is its
+// reads of LDS: only the first D of 16 rows and columns hold anything, and A's
+// row comes two values a read (101 taps and 2 sections: prepare 9.6 us with all
+// 16, one value a read and the section's powers in turn, 6.9 us so; 6 sections
+// whose depth is searched for to the end: 13.6 and 12.9).
+template <int D>
+__device__ __forceinline__ double mm_dot_n(const double (*A)[16], const double (*B)[16], int i, int j) {
+    double2 r[D / 2];
+    double b[D];
+#pragma unroll
+    for (int k = 0; k < D / 2; ++k) r[k] = reinterpret_cast<const double2 *>(A[i])[k];
+#pragma unroll
+    for (int k = 0; k < D; ++k) b[k] = B[k][j];
     double acc = 0.0;
-    for (int k = 0; k < 16; ++k) acc += A[i][k] * B[k][j];
+#pragma unroll
+    for (int k = 0; k < D; ++k) acc += (k & 1 ? r[k / 2].y : r[k / 2].x) * b[k];
+    return acc;
+}
+__device__ __forceinline__ double mm_dot(const double (*A)[16], const double (*B)[16], int i, int j, int D) {
+    if (D <= 4) return mm_dot_n<4>(A, B, i, j);
+    if (D <= 8) return mm_dot_n<8>(A, B, i, j);
+    if (D <= 12) return mm_dot_n<12>(A, B, i, j);
+    return mm_dot_n<16>(A, B, i, j);
+}
+__device__ void mm16(const double (*A)[16], const double (*B)[16], double (*R)[16], int i, int j, int D) {
+    const double acc = mm_dot(A, B, i, j, D);
     __syncthreads();  // every read of A and B done (R may alias either)
     R[i][j] = acc;
     __syncthreads();
 }
-
-// max |M| over the block (every thread gets it)
-__device__ double block_maxabs(const double (*M)[16], int i, int j, int tid) {
-    __shared__ double wmax[4];
-    double v = fabs(M[i][j]);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = fmax(v, __shfl_xor(v, d));
-    if ((tid & 63) == 0) wmax[tid >> 6] = v;
+// P = P F (if mul) and F = F F in one round
+__device__ void mm16_step(double (*P)[16], double (*F)[16], bool mul, int i, int j, int D) {
+    const double p = mul ? mm_dot(P, F, i, j, D) : 0.0, f = mm_dot(F, F, i, j, D);
     __syncthreads();
-    v = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
+    if (mul) P[i][j] = p;
+    F[i][j] = f;
     __syncthreads();
-    return v;
 }
+
+// Whether max |M| over the block is within the depth bound (every thread gets it).
+__device__ bool block_within(double m) { return __syncthreads_and(fabs(m) <= DEPTH_EPS) != 0; }
 
 // co(s, k): coefficient k of section s; Lc: the chunk length (tile 128 Lc).
 template <class Co>
 __device__ void casc_table_block(char *raw, Co co_at, int32_t S, int Lc, CascTab *out, int tid) {
     struct Sh {
-        double co[CASC_MAX][5], M0[16][16], M1[16][16], Pw[7][16][16];
+        alignas(16) double M0[16][16], M1[16][16], Pw[7][16][16], co[CASC_MAX][5];
     };
     Sh &sh = lds_as<Sh>(raw);
     auto &co = sh.co;
     auto &M0 = sh.M0, &M1 = sh.M1;
     auto &Pw = sh.Pw;
-    const int i = tid >> 4, j = tid & 15;
+    const int i = tid >> 4, j = tid & 15, D = 2 * S;
     if (tid < S * 5) co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
     __syncthreads();
-    M1[i][j] = cascade_f(co, 2 * S, i, j);
+    M1[i][j] = cascade_f(co, D, i, j);
     Pw[0][i][j] = i == j ? 1.0 : 0.0;
     __syncthreads();
     for (int e = Lc; e > 0; e >>= 1) {  // Pw[0] = F^Lc by binary powering
-        if (e & 1) mm16(Pw[0], M1, Pw[0], i, j);
-        if (e > 1) mm16(M1, M1, M1, i, j);
+        if (e > 1) mm16_step(Pw[0], M1, e & 1, i, j, D);
+        else mm16(Pw[0], M1, Pw[0], i, j, D);
     }
-    for (int t = 0; t < 7; ++t) mm16(Pw[0], Pw[0], Pw[0], i, j);  // F^(128 Lc), the tile transition
-    for (int t = 1; t < 7; ++t) mm16(Pw[t - 1], Pw[t - 1], Pw[t], i, j);  // Phi_T^(2^t)
+    for (int t = 0; t < 7; ++t) mm16(Pw[0], Pw[0], Pw[0], i, j, D);  // F^(128 Lc), the tile transition
+    for (int t = 1; t < 7; ++t) mm16(Pw[t - 1], Pw[t - 1], Pw[t], i, j, D);  // Phi_T^(2^t)
     out->T[0][i][j] = (float)Pw[0][i][j];
     out->T[1][i][j] = (float)Pw[1][i][j];
     out->T[2][i][j] = (float)Pw[2][i][j];
@@ -176,7 +200,7 @@ __device__ void casc_table_block(char *raw, Co co_at, int32_t S, int Lc, CascTab
     // two and the first passing one; every accepted d is checked directly
     int first = -1;
     for (int t = 0; t < 7 && first < 0; ++t)
-        if (block_maxabs(Pw[t], i, j, tid) <= DEPTH_EPS) first = t;
+        if (block_within(Pw[t][i][j])) first = t;
     int dep = 0;
     if (first == 0) {
         dep = 1;
@@ -185,8 +209,8 @@ __device__ void casc_table_block(char *raw, Co co_at, int32_t S, int Lc, CascTab
         M0[i][j] = Pw[first - 1][i][j];  // Phi_T^lo
         __syncthreads();
         for (int t = first - 2; t >= 0; --t) {
-            mm16(M0, Pw[t], M1, i, j);  // Phi_T^(lo + 2^t)
-            if (block_maxabs(M1, i, j, tid) <= DEPTH_EPS) {
+            mm16(M0, Pw[t], M1, i, j, D);  // Phi_T^(lo + 2^t)
+            if (block_within(M1[i][j])) {
                 hi = lo + (1 << t);
             } else {
                 lo += 1 << t;
@@ -209,12 +233,12 @@ __device__ void casc_table_block(char *raw, Co co_at, int32_t S, int Lc, CascTab
 template <class Co>
 __device__ void zir_block(char *raw, Co co_at, int32_t S, int Lc, int k, CascZir *out, int tid) {
     struct Sh {
-        double co[CASC_MAX][5], Fm[16][16], P[16][16], g[16];
+        alignas(16) double Fm[16][16], P[16][16], G[32][16], co[CASC_MAX][5];
     };
     Sh &sh = lds_as<Sh>(raw);
     auto &co = sh.co;
     auto &Fm = sh.Fm, &P = sh.P;
-    auto &g = sh.g;
+    auto &G = sh.G;
     const int i = tid >> 4, j = tid & 15;
     if (tid < S * 5) co[tid / 5][tid % 5] = co_at(tid / 5, tid % 5);
     __syncthreads();
@@ -225,8 +249,8 @@ __device__ void zir_block(char *raw, Co co_at, int32_t S, int Lc, int k, CascZir
     if (k < ZIR_B + ZIR_A) {
         const int e0 = k < ZIR_B ? Lc * k : ZIR_B * Lc * (k - ZIR_B);
         for (int e = e0; e > 0; e >>= 1) {
-            if (e & 1) mm16(P, Fm, P, i, j);
-            if (e > 1) mm16(Fm, Fm, Fm, i, j);
+            if (e > 1) mm16_step(P, Fm, e & 1, i, j, D);
+            else mm16(P, Fm, P, i, j, D);
         }
         if (k < ZIR_B) out->Mb[i][j][k] = (float)P[i][j];
         else out->MaT[k - ZIR_B][j][i] = (float)P[i][j];
@@ -238,19 +262,17 @@ __device__ void zir_block(char *raw, Co co_at, int32_t S, int Lc, int k, CascZir
             c = 1.0;
             for (int t = (tid >> 1) + 1; t < S; ++t) c *= co[t][0];
         }
-        g[tid] = c;
+        G[0][tid] = c;
     }
     __syncthreads();
-    for (int r = 0; r < Lc; ++r) {  // G[r] = g, then g <- g F
-        double acc = 0.0;
-        if (tid < 16) {
-            out->G[tid][r] = (float)g[tid];
-            for (int q = 0; q < 16; ++q) acc += g[q] * Fm[q][tid];
-        }
+    for (int m = 1; m < Lc; m *= 2) {  // rows m .. 2 m - 1 are rows 0 .. m - 1 times F^m
+        const double acc = i < m ? mm_dot(G, Fm, i, j, D) : 0.0, f = mm_dot(Fm, Fm, i, j, D);
         __syncthreads();
-        if (tid < 16) g[tid] = acc;
+        if (i < m) G[m + i][j] = acc;
+        Fm[i][j] = f;
         __syncthreads();
     }
+    for (int e = tid; e < 16 * Lc; e += 256) out->G[e & 15][e >> 4] = (float)G[e >> 4][e & 15];
 }
 
 // Matrix-core cascade tables (McTab), in FP64 then rounded, one block of
@@ -311,7 +333,7 @@ __device__ void mc_block(char *raw, Co co_at, int32_t S, McTab *out, int tid) {
             V[n + j][i] = vv;
             Gm[n + j][i] = gg;
         }
-        mm16(Pw, Pw, Pw, i, j);
+        mm16(Pw, Pw, Pw, i, j, 2 * S);
     }
     if (tid < MC_LC) {  // h[0] = d, h[n] = c F^(n-1) b
         double hv = 0.0;
@@ -337,10 +359,10 @@ __device__ void mc_block(char *raw, Co co_at, int32_t S, McTab *out, int tid) {
         out->Gt[l][q] = (float)Gm[16 * rb + (l & 15)][4 * (l >> 4) + k];
     }
     out->Fr[i][j] = (float)Pw[i][mc_src(i, j)];  // Fc = F^32
-    mm16(Pw, Pw, Q, i, j);  // Fc^2
-    mm16(Q, Q, Q, i, j);    // Fc^4
-    mm16(Q, Q, Pw, i, j);   // Fc^8
-    mm16(Pw, Q, Q, i, j);   // Fc^12
+    mm16(Pw, Pw, Q, i, j, 2 * S);  // Fc^2
+    mm16(Q, Q, Q, i, j, 2 * S);    // Fc^4
+    mm16(Q, Q, Pw, i, j, 2 * S);   // Fc^8
+    mm16(Pw, Q, Q, i, j, 2 * S);   // Fc^12
     out->Fsr[i][j] = (float)Q[i][mc_src(i, j)];
 }
 

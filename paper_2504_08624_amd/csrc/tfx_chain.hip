@@ -111,6 +111,7 @@ struct KArgs {
     int64_t ldh;          // M - 1
     float *hist_out;      // chain_last_kernel: its blocks from tile_blocks on write the next history
     uint32_t tile_blocks;
+    int64_t tile0;        // first tile of this launch
     uint32_t xcd_ks;      // block order: xcd_order's log2 K (0 = block ids in order)
     int32_t after_short;  // the short-memory kernel ran before this one: nothing to do if it did the work (2: nor
                           // if the chain is not a short-memory one)
@@ -676,8 +677,7 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
     }
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
     const uint64_t id = xcd_order(block, nblocks, a.xcd_ks);
-    // (returning the registers is the last tile's launch)
-    c.tile = STOUT && CASC ? a.ntiles - 1 : (int64_t)(id / npairs);
+    c.tile = (int64_t)(id / npairs) + a.tile0;
     const int64_t pair = (int64_t)(id % npairs);
     c.ch = 2 * pair + c.grp;
     c.valid = c.ch < a.C;
@@ -839,33 +839,37 @@ __global__ __launch_bounds__(WG, (chain_min_blocks<FIRM, HAS_SOS, HIQ, CASC, STO
 }
 
 // The last launch of a call that returns the registers, cascades up to CASC_MAX
-// sections: the last tile (its tile blocks lead the grid; the launch before ran
-// the others), every tile in FP64 carries where a section asks for that, and in
-// blocks of its own the stream's next history (hist is only read here).  A
-// stream's block of one tile, whose time is launches and one tile's latency, is
-// this launch alone (8 channels x 512 samples, 1023 taps, 6 sections: 28.7 us a
-// block as history, filter and empty FP64 launch, 21.4 us as one).
+// sections: the tiles from tile0 on (the last one, if a launch before ran the
+// others; their blocks lead the grid), every tile in FP64 carries where a section
+// asks for that, and in blocks of its own the stream's next history (hist is only
+// read here).  A stream's block of few tiles, whose time is launches and one
+// tile's latency, is this launch alone (8 channels x 512 samples, 1023 taps, 6
+// sections: 28.7 us a block as history, filter and empty FP64 launch, 21 us as
+// one).
 template <int FIRM>
 __global__ __launch_bounds__(WG) void chain_last_kernel(KArgs a) {
     __shared__ ChainLds<FIRM> sh;
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    const uint32_t np = (uint32_t)(a.cpad / 2);
+    const uint32_t nrun = (uint32_t)((a.ntiles - a.tile0) * (a.cpad / 2));
     const uint32_t hiq = a.hdr[HDR_HIQ];
     if (blockIdx.x >= a.tile_blocks) {
         write_history(a.x, a.ldx, a.hist, a.hist_out, a.C, a.N, a.ldh,
                       (int64_t)(blockIdx.x - a.tile_blocks) * WG + threadIdx.x);
         return;
     }
-    if (hiq)
-        chain_tile<FIRM, true, true, false, true>(a, sh, s_dyn, blockIdx.x, a.tile_blocks);
-    else if (blockIdx.x < np)
-        chain_tile<FIRM, true, false, true, true>(a, sh, s_dyn, blockIdx.x, np);
-    else
+    if (hiq) {
+        KArgs h = a;
+        h.tile0 = 0;
+        chain_tile<FIRM, true, true, false, true>(h, sh, s_dyn, blockIdx.x, a.tile_blocks);
+    } else if (blockIdx.x < nrun) {
+        chain_tile<FIRM, true, false, true, true>(a, sh, s_dyn, blockIdx.x, nrun);
+    } else {
         return;
+    }
     // the next run's epoch, by the last of the blocks that have read this one's
-    // (with FP64 carries and more tiles the launch before has set it)
-    if (threadIdx.x == 0 && (!hiq || a.ntiles == 1) &&
-        __hip_atomic_fetch_add(a.hdr + HDR_DONE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == np - 1) {
+    // (with FP64 carries and a launch before, that one has set it)
+    if (threadIdx.x == 0 && (!hiq || a.tile0 == 0) &&
+        __hip_atomic_fetch_add(a.hdr + HDR_DONE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nrun - 1) {
         next_epoch(a.hdr);
         a.hdr[HDR_DONE] = 0u;
     }
@@ -1012,6 +1016,21 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
 // kernel of the prepare step (tfx_tables.hip)
 hipError_t launch_state_passthrough(const float *in, float *out, int64_t n, hipStream_t st);
 
+// Calls that return the registers, cascades up to CASC_MAX sections, by the
+// number of workgroups (tiles times channel pairs).  Up to STOUT_ONE: all tiles in
+// chain_last_kernel, one launch, whose workgroups count themselves out (8 x 4096,
+// 1023 taps and 6 sections: 29.3 us against 32 with the launches below; at 800
+// workgroups the counting makes it 58 against 48).  Then: the second pass of every
+// section in every tile, and the FP64 variant behind it.  Large calls
+// (stout_split): the tiles before the last as without registers, and the last one
+// behind them, which costs its tile's latency once and saves the second pass:
+// 8 sections, 2048 / 3600 / 15000 workgroups 84 / 113 / 338 us split, 90 / 141 /
+// 476 not; 6 sections, 3600 / 7200 / 15000: 110 / 176 / 310 and 101 / 176 / 333; 4
+// sections, 7200 / 10338 / 30000: 145 / 191 / 481 and 140 / 188 / 496; 2 sections,
+// 30000: 428 and 417.
+constexpr int64_t STOUT_ONE = 64;
+inline bool stout_split(int64_t wgs, int32_t S) { return S >= MC_MIN_SECTIONS ? wgs >= 2048 : wgs * (S - 2) >= 28000; }
+
 // (hiq: also the FP64-carry variant)
 template <int F, bool S, bool STOUT>
 static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t st, bool hiq = true) {
@@ -1025,19 +1044,20 @@ static hipError_t launch_variants(const KArgs &k, int64_t nblocks, hipStream_t s
         hipLaunchKernelGGL((chain_kernel<F, S, false, false, false>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
     } else if (k.S > CASC_MAX) {
         hipLaunchKernelGGL((chain_kernel<F, S, false, false, STOUT>), dim3((unsigned)nblocks), dim3(WG), dyn, st, k);
+    } else if (STOUT && nblocks > STOUT_ONE && !stout_split(nblocks, k.S)) {
+        hipLaunchKernelGGL((chain_kernel<F, S, false, true, STOUT>), dim3((unsigned)nblocks), dim3(WG), dync, st, k);
     } else if constexpr (STOUT) {
         // the final state is the last tile's affair: the tiles before it run as
         // without one (tables or matrix cores instead of a second pass of every
-        // section), then the last one, on the same records (12 x 5.29 M, odd
-        // length, 4 sections: 389 us a call with the second pass everywhere and
-        // one-sample row accesses, 190 us now)
+        // section), then the last one, on the same records
         const int64_t np = k.cpad / 2;
-        if (k.ntiles > 1) {
+        KArgs last = k;
+        if (nblocks > STOUT_ONE && k.ntiles > 1) {
             KArgs m = k;
             m.state_out = nullptr;
             if ((e = launch_variants<F, true, false>(m, np * (k.ntiles - 1), st, false)) != hipSuccess) return e;
+            last.tile0 = k.ntiles - 1;
         }
-        KArgs last = k;
         last.tile_blocks = (uint32_t)nblocks;
         const int64_t nh = k.hist_out ? (k.C * k.ldh + WG - 1) / WG : 0;
         hipLaunchKernelGGL((chain_last_kernel<F>), dim3((unsigned)(nblocks + nh)), dim3(WG), std::max(dyn, dync), st,
@@ -1123,7 +1143,9 @@ hipError_t launch_run(const ChainPlan &p) {
     // the next history of a stream: by extra blocks of the chain kernel where one
     // that returns the registers filters the block from x, else by a launch of
     // its own, stream-ordered before the filter, which reads hist_in only
+    const int64_t wgs = (lay.cpad / 2) * ((p.N + T - 1) / T);
     const bool hist_fused = p.hist_out && Mtot > 1 && p.N > 0 && p.state_out && p.S > 0 && p.S <= CASC_MAX &&
+                            (wgs <= STOUT_ONE || stout_split(wgs, p.S)) &&
                             (p.fir_mode == FIR_DIRECT || p.fir_mode == FIR_FFT || tz_fused);
     if (p.hist_out && Mtot > 1 && !hist_fused) {
         const int64_t n = p.C * (int64_t)(Mtot - 1);

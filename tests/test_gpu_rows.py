@@ -88,6 +88,23 @@ def test_final_registers(S, N):
     assert_close(_cpu(y2), ref2, TOL_IIR_F32, "continued S=%d N=%d" % (S, N))
 
 
+@pytest.mark.parametrize("S,tiles", [(8, 700), (6, 2400), (4, 31), (4, 33)])  # split, split, one launch, two
+def test_final_registers_by_size(S, tiles):
+    """Each side of the rules by which a call's tiles share a launch (6 channels:
+    3 workgroups a tile); the last channel's last tile and its registers against
+    the oracle on the signal's tail from the registers in front of it."""
+    C, N = (6 if S > 4 else 4), tiles * T - 9
+    tail = 5 * T + 11
+    x = _x(C, N, (906, S, tiles))
+    sec = _eq(S, 3)
+    y, so = tfx.sos(_gpu(x), _gpu(sec), return_state=True)
+    head = N - tail
+    _, s0 = O.sos(x[-1:, max(0, head - 20 * T):head], sec, return_state=True)  # decays within a tile
+    ref, rs = O.sos(x[-1:, head:], sec, state_in=s0, return_state=True)
+    assert_close(_cpu(y)[-1:, head:], ref, TOL_IIR_F32, "tail S=%d tiles=%d" % (S, tiles))
+    assert np.max(np.abs(_cpu(so)[-1:] - rs)) <= TOL_IIR_F32 * 0.1, "registers S=%d tiles=%d" % (S, tiles)
+
+
 @pytest.mark.parametrize("taps", [0, 17, 201])
 @pytest.mark.parametrize("q", [1.0, 400.0])  # 400: poles that the FP64-carry form takes
 def test_stream_of_mixed_blocks(taps, q):

@@ -133,12 +133,9 @@ __device__ __forceinline__ void write_history(const float *x, int64_t ldx, const
 
 // FIR input x[ch][n] of the block, n < N, with the streaming history for
 // n in [-(M - 1), 0) and zeros before it.
-// (No branch around a load: see load_pair_block.)
 __device__ __forceinline__ float fir_input(const KArgs &a, const float *xc, int64_t ch, int64_t n) {
-    const bool inh = a.hist && n < 0 && n >= -a.ldh;
-    const float *p = inh ? a.hist + ch * a.ldh : xc;
-    const float v = p[inh ? a.ldh + n : max(min(n, a.N - 1), (int64_t)0)];
-    return inh || (n >= 0 && n < a.N) ? v : 0.f;
+    if (n >= 0) return n < a.N ? xc[n] : 0.f;
+    return (a.hist && n >= -a.ldh) ? a.hist[ch * a.ldh + a.ldh + n] : 0.f;
 }
 
 // Fused matrix-core FIR of a tile (both channels of the pair), written into
@@ -319,7 +316,7 @@ __device__ void tz_tile(const KArgs &a, float *lds, int64_t pair, int64_t n0, in
 // the convolution, later for the correlation); the products with the
 // partition spectra are summed in the frequency domain and inverted once.
 // tw: the workgroup's LDS copy of the twiddle table, staged by the caller.
-template <bool PARTS>
+template <bool PARTS, bool CLAMP>
 __device__ void fft_block(const KArgs &a, float *lds, int64_t pair, int64_t n0, int tid, float (&zr)[16],
                           float (&zi)[16], const float2 *tw) {
     const int64_t chA = 2 * pair, chB = 2 * pair + 1;
@@ -330,7 +327,7 @@ __device__ void fft_block(const KArgs &a, float *lds, int64_t pair, int64_t n0, 
     const int64_t hlen = a.hist ? a.ldh : 0;
     const int64_t base = a.correlate ? n0 : n0 - FFT_DISCARD;
     if (!PARTS) {
-        load_pair_block(zr, zi, xA, xB, base, a.N, a.N, tid, hA, hB, hlen);
+        load_pair_block<CLAMP>(zr, zi, xA, xB, base, a.N, a.N, tid, hA, hB, hlen);
         fft4096_forward(zr, zi, lds, tw, tid);
         spectrum_product(zr, zi, a.hspec, tid, a.correlate != 0);
     } else {
@@ -341,7 +338,7 @@ __device__ void fft_block(const KArgs &a, float *lds, int64_t pair, int64_t n0, 
         for (int p = 0; p < a.nparts; ++p) {
             const int64_t shift = (int64_t)FFT_PART * p;
             __syncthreads();  // the previous pass's last LDS reads
-            load_pair_block(zr, zi, xA, xB, a.correlate ? base + shift : base - shift, a.N, a.N, tid, hA, hB, hlen);
+            load_pair_block<CLAMP>(zr, zi, xA, xB, a.correlate ? base + shift : base - shift, a.N, a.N, tid, hA, hB, hlen);
             fft4096_forward(zr, zi, lds, tw, tid);
             const float2 *hs = a.hspec + (int64_t)p * NFFT;
             const float sg = a.correlate ? -1.f : 1.f;
@@ -377,7 +374,6 @@ __device__ void fft_block(const KArgs &a, float *lds, int64_t pair, int64_t n0, 
 // in v.  stg: the group's DIRECT_GROUP_FLOATS of LDS.  Contains workgroup
 // barriers (every lane of the workgroup calls it).
 __device__ void direct_tile(const KArgs &a, float *stg, int64_t ch, bool valid, int gl, int64_t n0, float (&v)[L]) {
-    if (!valid) ch = a.C - 1;  // (its loads are clamped, not skipped)
     const float *xc = a.x + ch * a.ldx;
     const int p0 = gl * L;
     float acc[L];
@@ -388,20 +384,18 @@ __device__ void direct_tile(const KArgs &a, float *stg, int64_t ch, bool valid, 
         // stage x[src0 + i], i < T + KBL: convolution needs x[n - k],
         // correlation x[n + k]
         const int64_t src0 = a.correlate ? n0 + k0 : n0 - (k0 + a.KBL - 1);
-        const bool inside = src0 >= 0 && src0 + T + a.KBL <= a.N;
         for (int i0 = 0; i0 < T + a.KBL; i0 += 8 * GL) {
             float t8[8];
-            if (inside) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t8[u] = xc[src0 + min(i0 + gl + GL * u, T + a.KBL - 1)];
-            } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) t8[u] = fir_input(a, xc, ch, src0 + i0 + gl + GL * u);
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + gl + GL * u;
+                const int64_t n = src0 + i;
+                t8[u] = (valid && i < T + a.KBL) ? fir_input(a, xc, ch, n) : 0.f;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = i0 + gl + GL * u;
-                if (i < T + a.KBL) stg[cphys(i)] = valid ? t8[u] : 0.f;
+                if (i < T + a.KBL) stg[cphys(i)] = t8[u];
             }
         }
         __syncthreads();
@@ -621,7 +615,7 @@ __device__ __forceinline__ void casc_zir(float (&v)[L], const CascZir *zt, const
 // waves per SIMD: at most 128 registers).
 template <int FIRM, bool HAS_SOS, bool HIQ, bool CASC, bool STOUT>
 constexpr int chain_min_blocks() {
-    return (HAS_SOS && CASC && !HIQ && !STOUT && (FIRM == FIR_NONE || FIRM == FIR_FFT)) ? 4 : 1;
+    return (HAS_SOS && CASC && !HIQ && !STOUT && (FIRM == FIR_NONE || FIRM == FIR_FFT || FIRM == FIR_DIRECT)) ? 4 : 1;
 }
 
 template <int FIRM>
@@ -696,7 +690,7 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         direct_tile(a, stg, c.ch, c.valid, c.gl, n0, v);
     } else {  // FIR_FFT
         float zr[16], zi[16];
-        fft_block<FIRM == FIR_FFT_PARTS>(a, lds, pair, n0, c.tid, zr, zi, s_twl);
+        fft_block<FIRM == FIR_FFT_PARTS, HAS_SOS>(a, lds, pair, n0, c.tid, zr, zi, s_twl);
         if (!HAS_SOS) {
             const int64_t chA = 2 * pair, chB = chA + 1;
             store_pair_tile<4>(zr, zi, a.y + chA * a.ldy, chB < a.C ? a.y + chB * a.ldy : nullptr, n0, a.N, c.tid);
@@ -911,7 +905,7 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
         float zr[16], zi[16];
         twl_stage(s_twl, a.twid, tid, WG);
         __syncthreads();
-        fft_block<false>(a, lds, pair, n0, tid, zr, zi, s_twl);
+        fft_block<false, true>(a, lds, pair, n0, tid, zr, zi, s_twl);
         __syncthreads();  // the FFT buffers become X
 #pragma unroll
         for (int q = 4; q < 16; ++q) {

@@ -515,6 +515,7 @@ __device__ __forceinline__ void spectrum_product(float (&zr)[16], float (&zi)[16
 // input layout.  With a history (streaming: the hlen samples before the
 // block, ha / hb, hb may be null) the samples at n in [-hlen, 0) come from
 // ha[hlen + n].  A block wholly inside takes no per-element checks.
+template <bool CLAMP = false>
 __device__ __forceinline__ void load_pair_block(float (&zr)[16], float (&zi)[16], const float *xa, const float *xb,
                                                 int64_t base, int64_t N, int64_t limit, int tid,
                                                 const float *ha = nullptr, const float *hb = nullptr,
@@ -534,8 +535,19 @@ __device__ __forceinline__ void load_pair_block(float (&zr)[16], float (&zi)[16]
         }
         return;
     }
-    // the signal's ends: every element reads some address that is there and is
-    // then kept or cleared.  A load inside a branch is waited for before the
+    if constexpr (!CLAMP) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int64_t n = base + 256 * q + tid;
+            const bool in = n >= 0 && n < hi;
+            const bool inh = n < 0 && n >= -hlen;
+            zr[q] = in ? xa[n] : (inh ? ha[hlen + n] : 0.f);
+            zi[q] = (in && xb) ? xb[n] : ((inh && hb) ? hb[hlen + n] : 0.f);
+        }
+        return;
+    }
+    // CLAMP (chains with sections: a stream's blocks are all edge): every element
+    // reads some address that is there and is then kept or cleared.  A load inside a branch is waited for before the
     // next one, 32 times over (a stream's block of 512 samples through 1023
     // taps and 6 sections: the kernel 25.8 us with branches here and phases A
     // and B in chain_tile, 20.4 us without either)

@@ -12,9 +12,9 @@ build (tfx_chain_prepare) followed by the fused filter kernel
 (tfx_chain_run).  W untimed steps, then K timed steps between two device
 synchronisations; `value` is channel-samples per second of the whole step.
 HIP events recorded on the launch stream around every tfx_chain_run give the
-fused kernel's average duration for the roofline (algorithmic bytes = 8 B
+filter kernel's average duration for the roofline (algorithmic bytes = 8 B
 per channel-sample: read x once, write y once; the bracket also holds the
-FP64-carry variant's launch, which exits at once); events around every step
+launches of the scan behind the block kernel, which exit at once); events around every step
 give its median and spread, ten more steps run "cold" (512 MB written before
 each, more than the last-level cache holds), and a plain device copy of the
 input gives the achievable bandwidth the HBM figure is also quoted against.  The same loop is then timed
@@ -56,20 +56,17 @@ MFMA_BF16_PEAK_TFS = 2500.0  # dense bf16 / fp16 matrix peak
 VALU_F32_PEAK_TFS = 78.6
 
 
-def chain_flops_per_sample(M, S):
-    """Vector-unit flops per channel-sample of the fused FFT-FIR + SOS kernel
-    (cascades of up to six sections): per 6144 channel-samples (one channel
-    pair, one 3072-sample tile) one 4096-point complex FFT per tap partition
-    of 1025 plus one inverse (5 N log2 N each) and the spectrum products (6
-    flops per bin and partition); per section 9 (TDF-II) + 4 (zero-input
-    correction) + 2 (scan and fold)."""
-    parts = (M + 1024) // 1025
-    fft = (parts + 1) * 5 * 4096 * 12 + parts * 6 * 4096
-    return fft / 6144.0 + 15.0 * S
+def chain_flops_per_sample():
+    """Vector-unit flops per channel-sample of the short-memory form of the
+    chain (FIR and cascade as one FIR on 16384-point blocks): one forward and one
+    inverse complex transform (5 N log2 N each) and a spectrum product (6 a bin)
+    per block of two tiles of at least 8192 samples."""
+    n = 16384
+    return (2 * 5 * n * 14 + 6 * n) / (2 * 8192.0)
 
 
 def measured_traffic():
-    """HBM bytes per launch of the fused chain kernel from the committed
+    """HBM bytes per launch of the chain's block kernel from the committed
     rocprofv3 counter runs (profiles/chain_mid_traffic.json), or None when the
     kernel's sources have changed since the counters were taken."""
     import hashlib
@@ -525,8 +522,7 @@ def main():
     ms_step = wall / K * 1e3
     value = samples / (wall / K) / 1e6
     alg_bytes = 8.0 * samples
-    S_tot = int(sum(s[1].shape[0] for s in w.stages if s[0] == "sos"))
-    fps = chain_flops_per_sample(int(w.stages[0][1].size), S_tot)
+    fps = chain_flops_per_sample()
     kern_s = float(kern_ms.mean()) / 1e3
     achieved_gbs = alg_bytes / kern_s / 1e9
     achieved_tfs = fps * samples / kern_s / 1e12
@@ -620,12 +616,12 @@ def main():
                    "fir_algo": "fft", "step": "tfx_chain_prepare + tfx_chain_run"},
         "roofline": {"bound": "hbm", "achieved": round(achieved_gbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved_gbs / HBM_PEAK_GBS, 4), "traffic": measured_traffic(),
-                     "kernel": "chain_kernel<FIR_FFT, cascade-level, zero-input tables>",
+                     "kernel": "short16k_kernel (FIR and cascade as one FIR on 16384-point blocks)",
                      "kernel_us": round(kern_s * 1e6, 2),
                      "alg_bytes_per_launch": alg_bytes, "alg_bytes_per_sample": 8,
                      "copy_GBps": copy["GBps"], "frac_of_copy": round(achieved_gbs / copy["GBps"], 4),
-                     "valu": {"what": "the fused kernel's algorithmic flops (FFT FIR + 6 sections) on the vector "
-                                      "units, without packed fp32",
+                     "valu": {"what": "the block kernel's algorithmic flops (two 16384-point transforms and a "
+                                      "spectrum product per two tiles) on the vector units, without packed fp32",
                               "flops_per_sample": round(fps, 2), "achieved_TFLOP_per_s": round(achieved_tfs, 3),
                               "peak_TFLOP_per_s": VALU_F32_PEAK_TFS,
                               "frac": round(achieved_tfs / VALU_F32_PEAK_TFS, 4)}},

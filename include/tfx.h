@@ -84,8 +84,8 @@ typedef enum tfx_fir_algo {
     TFX_FIR_TOEPLITZ = 2,  /* MFMA block-Toeplitz product (bf16/fp16/bf16x3) */
     TFX_FIR_FFT = 3,       /* overlap-save, 4096-point FFT per 3072 outputs;
                               taps beyond 1025 in partitions of 1025 (fp32) */
-    TFX_FIR_FFT16K = 4     /* overlap-save, 16384-point FFT per 8192 outputs;
-                              at most 8193 taps (fp32)                      */
+    TFX_FIR_FFT16K = 4     /* overlap-save, 16384-point FFT per two tiles of at
+                              least 8192 outputs; at most 8193 taps (fp32)  */
 } tfx_fir_algo;
 
 typedef enum tfx_stage_kind { TFX_STAGE_FIR = 0, TFX_STAGE_SOS = 1 } tfx_stage_kind;

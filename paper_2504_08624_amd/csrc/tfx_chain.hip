@@ -626,10 +626,11 @@ struct ChainLds {
     uint32_t epoch;
 };
 
-// One workgroup's tile: block `block` of `nblocks`.
+// One workgroup's tile: block `block` of `nblocks`; ahead: the records are tagged
+// with the epoch that follows the header's.
 template <int FIRM, bool HAS_SOS, bool HIQ, bool CASC, bool STOUT>
 __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, unsigned char *s_dyn, uint32_t block,
-                                           uint32_t nblocks) {
+                                           uint32_t nblocks, bool ahead = false) {
     float *lds = sh.lds;
     auto &s_agg = sh.agg;
     auto &s_pre = sh.pre;
@@ -658,7 +659,7 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         twl_stage(s_twl, a.twid, c.tid, WG);
         if (HAS_SOS && c.tid == 0) s_epoch = load_epoch(a.hdr, HDR_EPOCH);
         __syncthreads();
-        if (HAS_SOS) c.epoch = s_epoch;
+        if (HAS_SOS) c.epoch = ahead ? epoch_after(s_epoch) : s_epoch;
     } else if (HAS_SOS) {
         if (c.tid == 0) s_epoch = load_epoch(a.hdr, HDR_EPOCH);
         // the tables' loads overlap the FIR part of the tile
@@ -667,7 +668,7 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         else
             stage_tables(s_tab, a.tab, 0, min(a.S, LDS_SECTIONS), c.tid, WG);
         __syncthreads();
-        c.epoch = s_epoch;
+        c.epoch = ahead ? epoch_after(s_epoch) : s_epoch;
     }
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
     const uint64_t id = xcd_order(block, nblocks, a.xcd_ks);
@@ -854,14 +855,15 @@ __global__ __launch_bounds__(WG) void chain_last_kernel(KArgs a) {
     if (hiq) {
         KArgs h = a;
         h.tile0 = 0;
-        chain_tile<FIRM, true, true, false, true>(h, sh, s_dyn, blockIdx.x, a.tile_blocks);
+        // (a launch before has set the epoch already, as the one that does not match)
+        chain_tile<FIRM, true, true, false, true>(h, sh, s_dyn, blockIdx.x, a.tile_blocks, a.tile0 == 0);
     } else if (blockIdx.x < nrun) {
         chain_tile<FIRM, true, false, true, true>(a, sh, s_dyn, blockIdx.x, nrun);
     } else {
         return;
     }
-    // the next run's epoch, by the last of the blocks that have read this one's
-    // (with FP64 carries and a launch before, that one has set it)
+    // the epoch, by the last of the blocks that have read it: the next run's, or
+    // with FP64 carries the one just used, unless a launch before has set it
     if (threadIdx.x == 0 && (!hiq || a.tile0 == 0) &&
         __hip_atomic_fetch_add(a.hdr + HDR_DONE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nrun - 1) {
         next_epoch(a.hdr);

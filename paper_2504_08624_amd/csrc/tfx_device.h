@@ -20,8 +20,11 @@ namespace tfx {
 // by PhiT = A^3072, so rounding there accumulates over a few tiles only.  The
 // epoch advances once per run (block 0 of the filter-kernel variant that does
 // not match the workspace's high-Q word advances it, stream-ordered against
-// the variant that does the work), so a run never clears the words the
-// previous run left and needs no memset.
+// the variant that does the work; in chain_last_kernel the last block does), so
+// a run never clears the words the previous run left and needs no memset.  fp32
+// runs tag with the header's epoch and leave the next one there; FP64-carry runs
+// tag with the next one and leave that.  A workspace is prepared for one of the
+// two, so every form of a run starts past the tags of the runs before it.
 constexpr uint32_t EPOCH_MASK = 0x3FFFFFFFu;
 constexpr int64_t SPIN_MAX = int64_t(1) << 22;
 
@@ -34,10 +37,11 @@ __device__ __forceinline__ void st_word(uint64_t *p, uint64_t v) {
 __device__ __forceinline__ uint32_t load_epoch(const uint32_t *hdr, int word) {
     return __hip_atomic_load(hdr + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void next_epoch(uint32_t *hdr) {
-    const uint32_t ne = (hdr[HDR_EPOCH] + 1u) & EPOCH_MASK;
-    hdr[HDR_EPOCH] = ne == 0u ? 1u : ne;
+__device__ __forceinline__ uint32_t epoch_after(uint32_t e) {
+    const uint32_t ne = (e + 1u) & EPOCH_MASK;
+    return ne == 0u ? 1u : ne;
 }
+__device__ __forceinline__ void next_epoch(uint32_t *hdr) { hdr[HDR_EPOCH] = epoch_after(hdr[HDR_EPOCH]); }
 // Run by the filter-kernel variant that does not match the high-Q word
 // before it exits: its block 0 advances the look-back epoch for the next run.
 __device__ __forceinline__ void advance_epoch(uint32_t *hdr) {

@@ -1,0 +1,54 @@
+"""Calls whose tiles, carries and transforms take several forms: what one form
+leaves in a workspace is nothing to the next, and each form gives all the
+outputs of the call.  Against the FP64 oracle, or the scan."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08624_amd as tfx
+from paper_2504_08624_amd import design, signals
+from oracle import oracle as O
+from tests.metrics import TOL_IIR_F32, assert_close
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+T = 3072
+
+
+def _x(C, N, key, sigma=0.1):
+    return signals.to_f32(np.stack([signals.white(N, (*key, c), sigma) for c in range(C)]).reshape(C, N))
+
+
+def _gpu(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def _cpu(t):
+    torch.cuda.synchronize()
+    return t.detach().cpu().numpy()
+
+
+def _peaks(S, q):
+    """Peaking sections from 4 kHz up; q = 400 puts every pole where the carry is FP64."""
+    return np.concatenate([design.peaking(f, q, 6.0, 48000.0) for f in np.linspace(4000.0, 15000.0, S)]
+                          ).astype(np.float32)
+
+
+@pytest.mark.parametrize("S,C,blocks", [
+    pytest.param(3, 2, (300_000, 100_000, 300_000, 20_000, 512, 100_000), id="one pass over 64 workgroups, one under"),
+    pytest.param(8, 64, (64 * T, 2 * T, 2 * T, 64 * T, 2 * T), id="last tile apart, all tiles together"),
+])
+def test_fp64_carries_over_blocks_of_every_form(S, C, blocks):
+    """A stream whose blocks take turns between the forms: no block may take a
+    record that another block left."""
+    x = _x(C, sum(blocks), (951, S))
+    sec = _peaks(S, 400.0)
+    want, regs = O.sos(x, sec, return_state=True)
+    st = tfx.ChainStream([("sos", _gpu(sec))], C, max(blocks))
+    n0, out = 0, []
+    for b in blocks:
+        out.append(_cpu(st.process(_gpu(x[:, n0:n0 + b]))))
+        n0 += b
+        assert_close(out[-1], want[:, n0 - b:n0], TOL_IIR_F32, "block of %d up to %d" % (b, n0))
+    assert np.max(np.abs(_cpu(st._state[st._cur]) - regs)) <= TOL_IIR_F32 * np.max(np.abs(regs)), "registers"

@@ -752,7 +752,11 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         if (ZIR && a.S <= ZIR_MAX) zt_stage(lds, a.zir, 2 * a.S, c.tid);
         // (B) one look-back of the cascade state (first wave of each group)
         if (alone) {
-            if (c.gl < D) cP[c.gl] = (a.state_in && c.valid) ? a.state_in[c.ch * D + c.gl] : 0.f;
+            if (c.gl < D) {
+                const float p = (a.state_in && c.valid) ? a.state_in[c.ch * D + c.gl] : 0.f;
+                cP[c.gl] = p;
+                if (a.ckpt && c.valid) a.ckpt[c.ch * D + c.gl] = p;
+            }
         } else if (c.gw == 0) {
             CascCtx cc;
             cc.lane = c.lane;

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import paper_2504_08624_amd as tfx
-from paper_2504_08624_amd import design, signals
+from paper_2504_08624_amd import design, lib, signals
 from oracle import oracle as O
 from tests.metrics import TOL_IIR_F32, assert_close
 
@@ -52,3 +52,26 @@ def test_fp64_carries_over_blocks_of_every_form(S, C, blocks):
         n0 += b
         assert_close(out[-1], want[:, n0 - b:n0], TOL_IIR_F32, "block of %d up to %d" % (b, n0))
     assert np.max(np.abs(_cpu(st._state[st._cur]) - regs)) <= TOL_IIR_F32 * np.max(np.abs(regs)), "registers"
+
+
+@pytest.mark.parametrize("hiq", [False, True])
+@pytest.mark.parametrize("S", [1, 6, 8, 9])
+@pytest.mark.parametrize("C,N", [(3, 1), (3, 512), (3, T), (200, 700)])
+def test_checkpoint_and_registers_of_one_tile(C, N, S, hiq):
+    """tfx_sos with registers and checkpoints: a tile that is alone enters with
+    the given registers, and its checkpoint says so (the output buffer starts
+    filled with something else)."""
+    x = _gpu(_x(C, N, (952, S, N)))
+    sec = _gpu(_peaks(S, 400.0 if hiq else 1.0))
+    s0 = _gpu((0.05 * signals.rng(953, S, N).standard_normal((C, S, 2))).astype(np.float32))
+    nb = lib.size_out()
+    lib.call("tfx_sos_workspace_size", C, N, S, nb)
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
+    for si in (s0, None):
+        y, so = torch.empty_like(x), torch.empty_like(s0)
+        ck = torch.full((C, 1, S, 2), 7.0, device=DEV)
+        lib.call("tfx_sos", x.data_ptr(), y.data_ptr(), C, N, N, N, sec.data_ptr(), S,
+                 si.data_ptr() if si is not None else None, so.data_ptr(), ck.data_ptr(), ws.data_ptr(), nb.value,
+                 torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(ck[:, 0], torch.zeros_like(s0) if si is None else si)

@@ -88,7 +88,10 @@ template <int CMP>
 __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     __shared__ __align__(16) float P[PLANE];
     __shared__ __align__(16) float2 twl[TW_LDS];
-    const int V = short_memory(a.st, a.M, threadIdx.x & 63), T = NB - V;
+    const uint32_t tabs = a.hdr[HDR_TABS];
+    int V = short_memory(a.st, a.M, threadIdx.x & 63);
+    if (!tabs) V = 0;
+    const int T = NB - V;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
     const uint32_t per_ch = (uint32_t)((a.N + 2 * T - 1) / (2 * T));

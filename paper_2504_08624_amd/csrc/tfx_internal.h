@@ -173,9 +173,11 @@ struct alignas(16) McTab {
 // whether any section needs the FP64 carry (the filter kernels come in two
 // variants; the one that does not match this word exits at once), the memory
 // of a short-memory chain (V | 1, V a multiple of 64; 0: none), the epoch of
-// the last run in which its kernel met a value that is not finite, and the
-// blocks of chain_last_kernel that are done (0 between launches).
-enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5, HDR_DONE = 6 };
+// the last run in which its kernel met a value that is not finite, the
+// blocks of chain_last_kernel that are done (0 between launches), and whether
+// the prepare step has left the tables of a short-memory chain (a run may be
+// given a larger workspace than the prepare was, with another filter's there).
+enum { HDR_ERROR = 1, HDR_EPOCH = 2, HDR_HIQ = 3, HDR_SHORT = 4, HDR_BAD = 5, HDR_DONE = 6, HDR_TABS = 7 };
 
 // Short-memory chains: an FFT FIR, or a FIR with bf16 or fp16 operands, with a
 // cascade of up to CASC_MAX sections whose impulse response has died out within FFT16_MEM samples is one FIR, and

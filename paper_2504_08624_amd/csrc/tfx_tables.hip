@@ -694,6 +694,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
             a.hdr[HDR_BAD] = 0u;
             a.hdr[HDR_SHORT] = 0u;
             a.hdr[HDR_DONE] = 0u;
+            a.hdr[HDR_TABS] = a.ht16 ? 1u : 0u;
         }
     }
     if (bid < a.n16) {
@@ -940,6 +941,7 @@ __global__ void header_init_kernel(uint32_t *hdr) {
     hdr[HDR_SHORT] = 0u;
     hdr[HDR_BAD] = 0u;
     hdr[HDR_DONE] = 0u;
+    hdr[HDR_TABS] = 0u;
 }
 
 hipError_t launch_header_init(void *ws, size_t ws_bytes, hipStream_t st) {

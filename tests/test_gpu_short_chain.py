@@ -164,6 +164,39 @@ def test_a_smaller_workspace_still_serves():
     assert_close(_cpu(y2), _cpu(y).astype(np.float64), TOL_IIR_F32, "scan against blocks")
 
 
+def test_prepare_and_run_with_workspaces_of_two_sizes():
+    """A prepare without the room for the short-memory tables, on a buffer in which
+    another filter's lie, and a run that has the room (and the other way round):
+    the scan, of the filter that was prepared last."""
+    C, N = 2, 900_001
+    x = _gpu(_x(C, N, (830,)))
+    filters = []
+    for k in (0, 1):
+        st = [("fir", _gpu(design.fir_lowpass(255 - 40 * k, 9000.0 - 3000.0 * k, 48000.0).astype(np.float32))),
+              ("sos", _gpu(_eq(6, 10 + k)))]
+        kept, desc = _stages(st, torch.device(DEV))
+        filters.append((st, kept, lib.stage_array(desc), len(desc)))
+    nb = lib.size_out()
+    lib.call("tfx_chain_workspace_size", C, N, filters[0][2], filters[0][3], 0, nb)
+    ws = torch.zeros(nb.value, dtype=torch.uint8, device=DEV)
+    y = torch.empty_like(x)
+    sp = torch.cuda.current_stream().cuda_stream
+
+    def call(k, cut_prepare, cut_run):
+        _, _, arr, n = filters[k]
+        lib.call("tfx_chain_prepare", C, N, arr, n, 0, ws.data_ptr(), nb.value - cut_prepare, sp)
+        for _ in range(2):
+            lib.call("tfx_chain_run", x.data_ptr(), y.data_ptr(), C, N, N, N, arr, n, 0, None, ws.data_ptr(),
+                     nb.value - cut_run, sp)
+        return y
+
+    blocks = call(0, 0, 0).clone()
+    assert not _same(blocks, _scan(x, filters[0][0]))
+    assert _same(call(1, 256, 0), _scan(x, filters[1][0]))     # filter 0's tables still lie there
+    assert _same(call(0, 0, 256), _scan(x, filters[0][0]))
+    assert _same(call(0, 0, 0), blocks)
+
+
 @pytest.mark.parametrize("M", [255, 1500])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf"), 3e38])
 def test_values_that_are_not_finite(bad, M):

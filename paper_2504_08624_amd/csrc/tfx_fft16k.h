@@ -46,8 +46,10 @@ constexpr int PLANE = R * ROW;     // floats of the exchange plane
 // Twiddle table.  Rows r < 32 of 32 entries (padded to TWS float2: the 4 rows a
 // wave reads lie 4 banks apart) for W^(16 r e), phi = 2 pi r e / 1024, in the
 // form in which pass B's butterflies over e, e + 8, e + 16, e + 24 take them:
-//   e < 8: (cos, sin);  8 <= e < 24: (tan, cos);  e >= 24: (tan, cos / cos of entry e - 16)
-// (a cosine of zero stands as 2^-28: the term it should take away weighs 2^-28).
+//   e < 8 and e = 16: (cos, sin);  8 <= e < 24: (tan, cos);  e >= 24: (tan, cos / cos of entry e - 16)
+// Entry 16 of row 16 is the one quarter turn: that column takes plain products, whose
+// two more operations a transform are 0.1 % (as a tangent it would be 2^28 or so and
+// overflow sums from 1e30 on); the largest tangent left is 163, of 255 / 1024 of a turn.
 // Behind them, per thread t, W^(m kappa), kappa = (t >> 4) + 32 (t & 15), m = 1, 2
 // (first 512 float4) and m = 4, 8 (second).
 constexpr int TWS = 34, TW_ROWS = 32;
@@ -174,10 +176,11 @@ __device__ __forceinline__ void dft32(float (&zr)[R], float (&zi)[R], const floa
             if (n > 0) cmul_tw<(SIGN < 0)>(er[n], ei[n], make_float2(w0.x, w0.y));
             cmul_tw<(SIGN < 0)>(qr[n], qi[n], make_float2(w0.z, w0.w));
             turn<SIGN>(er[4 + n], ei[4 + n], w1.x);
-            turn<SIGN>(er[8 + n], ei[8 + n], w2.x);
+            if (n > 0) turn<SIGN>(er[8 + n], ei[8 + n], w2.x);
+            else cmul_tw<(SIGN < 0)>(er[8], ei[8], make_float2(w2.x, w2.y));
             turn<SIGN>(er[12 + n], ei[12 + n], w3.x);
-            dft4_tw<SIGN>(er[n], ei[n], er[4 + n], ei[4 + n], er[8 + n], ei[8 + n], er[12 + n], ei[12 + n], w1.y, w2.y,
-                          w3.y);
+            dft4_tw<SIGN>(er[n], ei[n], er[4 + n], ei[4 + n], er[8 + n], ei[8 + n], er[12 + n], ei[12 + n], w1.y,
+                          n > 0 ? w2.y : 1.f, w3.y);
             turn<SIGN>(qr[4 + n], qi[4 + n], w1.z);
             turn<SIGN>(qr[8 + n], qi[8 + n], w2.z);
             turn<SIGN>(qr[12 + n], qi[12 + n], w3.z);

@@ -495,7 +495,7 @@ __device__ void spec16_block(char *raw, const float *h, int32_t M, int32_t cmp, 
     int role = -1, m1 = 0, m2 = 0;  // entry's form (-1: none), its angle, the angle of the cosine it is divided by
     if (i < f16k::TW_LDS) {
         const int row = i / f16k::TWS, e = i % f16k::TWS;
-        role = e < f16k::R ? e >> 3 : 4;
+        role = e == 16 ? 0 : e < f16k::R ? e >> 3 : 4;
         m1 = 16 * row * e;
         m2 = 16 * row * (e - 16);
     } else if (i < f16k::TW_FLOAT2) {  // float4 of thread t: m = 1, 2, or 4, 8
@@ -513,16 +513,15 @@ __device__ void spec16_block(char *raw, const float *h, int32_t M, int32_t cmp, 
             (hf2 == 0 ? w128 : wq)[q] = make_double2(c, s);
             continue;
         }
-        const double cz = fabs(c) < 0x1p-28 ? 0x1p-28 : c;
         if (r == 1) {
-            c1 = cz;
+            c1 = c;
             s1 = -s;
             const float2 v = role == 0 ? make_float2((float)c, (float)-s)
                            : role == 4 ? make_float2(0.f, 0.f)
-                           : role == 5 ? make_float2((float)c, (float)s) : make_float2((float)(-s / cz), (float)cz);
+                           : role == 5 ? make_float2((float)c, (float)s) : make_float2((float)(-s / c), (float)c);
             if (role != 3) tw[i] = v;
         } else {
-            tw[i] = make_float2((float)(s1 / c1), (float)(c1 / cz));
+            tw[i] = make_float2((float)(s1 / c1), (float)(c1 / c));
         }
     }
     __syncthreads();

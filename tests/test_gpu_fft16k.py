@@ -133,6 +133,26 @@ def test_stream_fft16k_history(blk):
     assert_close(y, O.chain(x, stages), TOL_IIR_F32, "stream fft16k blocks of %d" % blk)
 
 
+@pytest.mark.parametrize("M", [1026, 8191])
+@pytest.mark.parametrize("amp", [1e-30, 1e30, 1e33])
+def test_fir_fft16k_amplitudes(M, amp):
+    """Finite samples near the ends of fp32's range (the transform's sums of 16384
+    of them stay inside it), both directions and from a history."""
+    C, N = 3, 3 * B + 1001
+    x = _x(C, N, (620, M))
+    h = _taps(M, 620)
+    big = (x * np.float32(amp)).astype(np.float32)
+    got = _cpu(tfx.fir(_gpu(big), _gpu(h), algo="fft16k"))
+    assert_close(got.astype(np.float64) / amp, O.fir(big / np.float64(amp), h), TOL_FIR_F32, "fir %g" % amp)
+    gx, _ = tfx.fir_backward(_gpu(x), _gpu(big), _gpu(h), algo="fft16k", need_taps=False)
+    rgx, _ = O.fir_backward(big / np.float64(amp), x, h)
+    assert_close(_cpu(gx).astype(np.float64) / amp, rgx, TOL_FIR_F32, "adjoint %g" % amp)
+    sm = tfx.ChainStream([("fir", _gpu(h))], C, 2 * B)
+    ys = [_cpu(sm.process(_gpu(big[:, i:i + 2 * B]))) for i in range(0, N, 2 * B)]
+    assert_close(np.concatenate(ys, axis=1).astype(np.float64) / amp, O.fir(big / np.float64(amp), h), TOL_FIR_F32,
+                 "stream %g" % amp)
+
+
 @pytest.mark.slow
 def test_fir_long_full_size_sampled():
     """The long-filter workload at full size (64 x 5,760,000, 8191 taps) in

@@ -37,27 +37,89 @@ struct F16Args {
     const uint32_t *gate;  // workspace header of a chain whose short-memory kernel ran before, or null
 };
 
+// Whether an output of the block is not finite: a NaN or an infinity in a block's
+// input reaches every output as a NaN; an overflow in the last pass may be in any
+// one of them.
+__device__ __forceinline__ bool not_finite(const float (&zr)[R], const float (&zi)[R]) {
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
+    return !(m < INFINITY) || zr[0] != zr[0] || zi[0] != zi[0];
+}
+
+// A block with an output that is not finite is done again, a tile at a time and in
+// runs of at most 8192 outputs up to the next multiple of 8192, from their own
+// inputs alone: a bad sample then reaches no other tile and at most two such
+// runs of its own (with 8191 taps no more can be told apart: the filter is
+// as long).  A run that is still not finite is done once more at 2^-24 of its
+// size, for sums that overflow on the way to outputs that do not.
+constexpr int NARROW = 8192;
+constexpr float NARROW_SCALE = 0x1p-24f;
+
+// The run [lo, lo + cnt) of a tile alone.
+__device__ __forceinline__ bool narrow_run(const F16Args &a, const float *xc, float *yc, const float *hc, int64_t lo,
+                                           int cnt, float scale, float *P, const float2 *twl, int *s_bad, int t) {
+    const int lead = a.correlate ? 0 : a.V, tail = a.V - lead;
+    float zr[R], zi[R];
+    load_block(zr, xc, lo - lead, min(a.N, lo + cnt + tail), hc, a.hlen, t);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        zr[k] *= scale;
+        zi[k] = 0.f;
+    }
+    if (t == 0) *s_bad = 0;
+    __syncthreads();  // the run before: its reads of P and of s_bad
+    convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
+    if (not_finite(zr, zi)) *s_bad = 1;
+    const float back = 1.f / scale;
+#pragma unroll
+    for (int k = 0; k < R; ++k) zr[k] *= back;
+    store_block(zr, yc, lo, lead, cnt, a.N, t);
+    __syncthreads();
+    const bool bad = *s_bad != 0;
+    __syncthreads();
+    return bad;
+}
+
 __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     __shared__ __align__(16) float P[PLANE];
     __shared__ __align__(16) float2 twl[TW_LDS];
+    __shared__ int s_bad;
     if (a.gate && short_done(a.gate)) return;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     tw_stage(twl, a.tw, t);
+    if (t == 0) s_bad = 0;
     const uint32_t u = xcd_unit(blockIdx.x, a.nunits);
     const int64_t ch = u / a.per_ch;
     const int T = NB - a.V;
     const int64_t n0 = (int64_t)(u - (uint32_t)ch * a.per_ch) * 2 * T, n1 = n0 + T;
     const int lead = a.correlate ? 0 : a.V;
     const float *xc = a.x + ch * a.ldx;
-    const float *hc = a.hist ? a.hist + ch * a.hlen : nullptr;
-    float zr[R], zi[R];
-    load_block(zr, xc, n0 - lead, a.N, hc, a.hlen, t);
-    load_block(zi, xc, n1 - lead, a.N, hc, a.hlen, t);
-    __syncthreads();  // the twiddle rows
-    convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
     float *yc = a.y + ch * a.ldy;
-    store_block(zr, yc, n0, lead, T, a.N, t);
-    if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
+    const float *hc = a.hist ? a.hist + ch * a.hlen : nullptr;
+    {
+        float zr[R], zi[R];
+        load_block(zr, xc, n0 - lead, a.N, hc, a.hlen, t);
+        load_block(zi, xc, n1 - lead, a.N, hc, a.hlen, t);
+        __syncthreads();  // the twiddle rows
+        convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
+        if (not_finite(zr, zi)) s_bad = 1;
+        store_block(zr, yc, n0, lead, T, a.N, t);
+        if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
+    }
+    __syncthreads();
+    if (!s_bad) return;
+    // (the thread's index anew: kept across the transform it would cost a register there)
+    const int t2 = 64 * wave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    __syncthreads();
+    for (int64_t lo = n0; lo < n1 + T && lo < a.N;) {
+        const int64_t end = min(lo < n1 ? n1 : n1 + T, (lo / NARROW + 1) * NARROW);
+        const int cnt = (int)(end - lo);
+#pragma unroll 1
+        for (float scale = 1.f; narrow_run(a, xc, yc, hc, lo, cnt, scale, P, twl, &s_bad, opaque(t2)) && scale == 1.f;)
+            scale = NARROW_SCALE;
+        lo = end;
+    }
 }
 
 // A short-memory chain (FIR and cascade as one filter of memory V; the grid is
@@ -116,12 +178,7 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     float *yc = a.y + ch * a.ldy;
     store_block(zr, yc, n0, V, T, a.N, t);
     if (n1 < a.N) store_block(zi, yc, n1, V, T, a.N, t);
-    // a NaN or an infinity in a block's input reaches every output as a NaN;
-    // an overflow in the last pass may be in any one of them
-    float m = 0.f;
-#pragma unroll
-    for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
-    if (!(m < INFINITY) || zr[0] != zr[0] || zi[0] != zi[0])
+    if (not_finite(zr, zi))
         __hip_atomic_store(a.hdr + HDR_BAD, a.hdr[HDR_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

@@ -153,6 +153,54 @@ def test_fir_fft16k_amplitudes(M, amp):
                  "stream %g" % amp)
 
 
+@pytest.mark.parametrize("correlate", [False, True])
+@pytest.mark.parametrize("M", [1026, 4100, 8193])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("pos", [0, 20_001, 5 * B + 8000])
+def test_fir_fft16k_reach_of_a_bad_sample(M, bad, pos, correlate):
+    """One sample that is not finite: no output of another channel, and none
+    further than two aligned runs of 8192 from it, is touched."""
+    C, N = 4, 6 * B + 333
+    x = _x(C, N, (621, M))
+    h = _taps(M, 621)
+    xb = x.copy()
+    xb[1, pos] = bad
+    if correlate:
+        got = _cpu(tfx.fir_backward(_gpu(x), _gpu(xb), _gpu(h), algo="fft16k", need_taps=False)[0])
+        ref = O.fir_backward(x, x, h)[0]
+        lo, hi = (pos // B - 1) * B, (pos // B + 1) * B
+    else:
+        got = _cpu(tfx.fir(_gpu(xb), _gpu(h), algo="fft16k"))
+        ref = O.fir(x, h)
+        lo, hi = pos // B * B, (pos // B + 2) * B
+    lo, hi = max(lo, 0), min(hi, N)
+    assert not np.isfinite(got[1, pos])
+    for c in range(C):
+        keep = np.ones(N, bool)
+        if c == 1:
+            keep[lo:hi] = False
+        assert np.all(np.isfinite(got[c, keep])), "channel %d" % c
+        e = np.linalg.norm(got[c, keep] - ref[c, keep]) / np.linalg.norm(ref[c, keep])
+        assert e <= TOL_FIR_F32, "channel %d: %.2e" % (c, e)
+
+
+@pytest.mark.parametrize("M", [1026, 8193])
+def test_fir_fft16k_sums_that_overflow(M):
+    """Finite samples whose 16384-point sums leave fp32's range and whose outputs do
+    not, beside ordinary ones."""
+    C, N = 3, 4 * B + 5
+    x = _x(C, N, (622, M))
+    x[1, 10_000:14_000] *= np.float32(2e37)
+    h = _taps(M, 622)
+    y = _cpu(tfx.fir(_gpu(x), _gpu(h), algo="fft16k"))
+    ref = O.fir(x, h)
+    big = np.zeros((C, N), bool)
+    big[1, 10_000 // B * B:(14_000 // B + 2) * B] = True     # the runs that a large sample reaches
+    assert np.isfinite(y).all()
+    assert np.linalg.norm(y[big] / 1e37 - ref[big] / 1e37) <= TOL_FIR_F32 * np.linalg.norm(ref[big] / 1e37)
+    assert np.linalg.norm(y[~big] - ref[~big]) <= TOL_FIR_F32 * np.linalg.norm(ref[~big])
+
+
 @pytest.mark.slow
 def test_fir_long_full_size_sampled():
     """The long-filter workload at full size (64 x 5,760,000, 8191 taps) in

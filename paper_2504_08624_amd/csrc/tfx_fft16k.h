@@ -484,12 +484,41 @@ __device__ __forceinline__ void convolve(float (&zr)[R], float (&zi)[R], const f
     passes_ba(zr, zi, P, twl, t);
 }
 
-// Unit u of nu (a pair of neighbouring tiles of one channel) of block id i:
+// Unit u of nu (a pair of neighbouring tiles, see TilePair) of block id i:
 // the blocks of one XCD (block i runs on XCD i mod 8) take one contiguous
 // range of units, so tiles that share input are read through one L2.
 __device__ __forceinline__ uint32_t xcd_unit(uint32_t i, uint32_t nu) {
     const uint32_t x = i & 7u, per = nu >> 3, rem = nu & 7u;
     return __builtin_amdgcn_readfirstlane(x * per + (x < rem ? x : rem) + (i >> 3));
+}
+
+// The two tiles of unit u, with tpc tiles of T samples a row: neighbours in one
+// channel (the second may be missing), so that no channel's rounding reaches
+// another; where a row is one tile, those of two channels, as half of every
+// transform would be empty (4096 x 4096 samples, 8191 taps: 185 us a channel a
+// unit, 118 us so).  two: there is a second tile.
+struct TilePair {
+    int64_t chA, nA, chB, nB;
+    bool two;
+};
+__device__ __forceinline__ TilePair tile_pair(uint32_t u, uint32_t C, uint32_t tpc, int T) {
+    const uint32_t per = (tpc + 1) / 2, c = __builtin_amdgcn_readfirstlane(tpc == 1 ? 2 * u : u / per);
+    const uint32_t i = tpc == 1 ? 0 : 2 * (u - c * per);
+    TilePair p;
+    p.two = tpc == 1 ? c + 1 < C : i + 1 < tpc;
+    p.chA = c;
+    p.nA = (int64_t)i * T;
+    p.chB = tpc == 1 && p.two ? c + 1 : c;
+    p.nB = tpc == 1 ? 0 : p.nA + T;
+    return p;
+}
+__host__ __device__ inline uint32_t tile_units(uint32_t C, uint32_t tpc) {
+    return tpc == 1 ? (C + 1) / 2 : C * ((tpc + 1) / 2);
+}
+// tpc of a row of N < 2^38 samples (T is a multiple of 64), in scalar registers
+__device__ __forceinline__ uint32_t tiles_per_row(int64_t N, int T) {
+    const uint32_t t64 = (uint32_t)T >> 6;
+    return __builtin_amdgcn_readfirstlane(((uint32_t)((N + 63) >> 6) + t64 - 1) / t64);
 }
 
 // 32 samples x[base + 512 a + t] of a channel row, zero outside [0, lim); n < 0

@@ -3,9 +3,9 @@
 //
 // With V the filter's memory (M - 1 rounded up to a multiple of 64) a block of
 // 16384 samples gives T = 16384 - V outputs.  A workgroup filters two
-// neighbouring tiles of one channel, one in the real and one in the imaginary
-// part of the transform (the taps are real, so the two outputs separate
-// exactly, and channels never mix).  Convolution: a tile's block starts V
+// tiles, neighbours in one channel or rows of one tile each, one in the real and
+// one in the imaginary part of the transform (the taps are real, so the two
+// outputs separate).  Convolution: a tile's block starts V
 // samples before it, and the last T outputs of the circular convolution are
 // the tile.  Correlation (the FIR adjoint, gx[n] = sum_k h[k] g[n + k]): the
 // block starts at the tile, the spectrum is conjugated, and the first T
@@ -27,7 +27,7 @@ struct F16Args {
     const float *x;
     float *y;
     int64_t C, N, ldx, ldy;
-    uint32_t nunits, per_ch;  // units (pairs of tiles), units per channel
+    uint32_t nunits, tpc;     // units (pairs of tiles), tiles per channel
     int32_t V;                // filter memory, a multiple of 64
     const float2 *tw;
     const float2 *hs;   // tap spectrum / 16384 in the transform's output order
@@ -90,35 +90,42 @@ __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     tw_stage(twl, a.tw, t);
     if (t == 0) s_bad = 0;
     const uint32_t u = xcd_unit(blockIdx.x, a.nunits);
-    const int64_t ch = u / a.per_ch;
     const int T = NB - a.V;
-    const int64_t n0 = (int64_t)(u - (uint32_t)ch * a.per_ch) * 2 * T, n1 = n0 + T;
+    const TilePair p = tile_pair(u, (uint32_t)a.C, a.tpc, T);
     const int lead = a.correlate ? 0 : a.V;
-    const float *xc = a.x + ch * a.ldx;
-    float *yc = a.y + ch * a.ldy;
-    const float *hc = a.hist ? a.hist + ch * a.hlen : nullptr;
+    const float *xa = a.x + p.chA * a.ldx, *xb = a.x + p.chB * a.ldx;
+    float *ya = a.y + p.chA * a.ldy, *yb = a.y + p.chB * a.ldy;
+    const float *ha = a.hist ? a.hist + p.chA * a.hlen : nullptr;
+    const float *hb = a.hist && p.two ? a.hist + p.chB * a.hlen : nullptr;
     {
         float zr[R], zi[R];
-        load_block(zr, xc, n0 - lead, a.N, hc, a.hlen, t);
-        load_block(zi, xc, n1 - lead, a.N, hc, a.hlen, t);
+        load_block(zr, xa, p.nA - lead, a.N, ha, a.hlen, t);
+        load_block(zi, xb, p.nB - lead, p.two ? a.N : 0, hb, a.hlen, t);
         __syncthreads();  // the twiddle rows
         convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
         if (not_finite(zr, zi)) s_bad = 1;
-        store_block(zr, yc, n0, lead, T, a.N, t);
-        if (n1 < a.N) store_block(zi, yc, n1, lead, T, a.N, t);
+        store_block(zr, ya, p.nA, lead, T, a.N, t);
+        if (p.two) store_block(zi, yb, p.nB, lead, T, a.N, t);
     }
     __syncthreads();
     if (!s_bad) return;
     // (the thread's index anew: kept across the transform it would cost a register there)
     const int t2 = 64 * wave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     __syncthreads();
-    for (int64_t lo = n0; lo < n1 + T && lo < a.N;) {
-        const int64_t end = min(lo < n1 ? n1 : n1 + T, (lo / NARROW + 1) * NARROW);
-        const int cnt = (int)(end - lo);
 #pragma unroll 1
-        for (float scale = 1.f; narrow_run(a, xc, yc, hc, lo, cnt, scale, P, twl, &s_bad, opaque(t2)) && scale == 1.f;)
-            scale = NARROW_SCALE;
-        lo = end;
+    for (int s = 0; s < (p.two ? 2 : 1); ++s) {
+        const float *xc = s ? xb : xa, *hc = s ? hb : ha;
+        float *yc = s ? yb : ya;
+        const int64_t first = s ? p.nB : p.nA, last = min(first + T, a.N);
+        for (int64_t lo = first; lo < last;) {
+            const int64_t end = min(first + T, (lo / NARROW + 1) * NARROW);
+            const int cnt = (int)(end - lo);
+#pragma unroll 1
+            for (float scale = 1.f;
+                 narrow_run(a, xc, yc, hc, lo, cnt, scale, P, twl, &s_bad, opaque(t2)) && scale == 1.f;)
+                scale = NARROW_SCALE;
+            lo = end;
+        }
     }
 }
 
@@ -156,18 +163,15 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     const int T = NB - V;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
-    const uint32_t per_ch = (uint32_t)((a.N + 2 * T - 1) / (2 * T));
-    const uint32_t nunits = (uint32_t)a.C * per_ch;
+    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
     if (blockIdx.x >= nunits) return;
     const int t = threadIdx.x;
     tw_stage(twl, a.tw, t);
     const uint32_t u = xcd_unit(blockIdx.x, nunits);
-    const int64_t ch = u / per_ch;
-    const int64_t n0 = (int64_t)(u - (uint32_t)ch * per_ch) * 2 * T, n1 = n0 + T;
-    const float *xc = a.x + ch * a.ldx;
+    const TilePair p = tile_pair(u, (uint32_t)a.C, tpc, T);
     float zr[R], zi[R];
-    load_block(zr, xc, n0 - V, a.N, nullptr, 0, t);
-    load_block(zi, xc, n1 - V, a.N, nullptr, 0, t);
+    load_block(zr, a.x + p.chA * a.ldx, p.nA - V, a.N, nullptr, 0, t);
+    load_block(zi, a.x + p.chB * a.ldx, p.nB - V, p.two ? a.N : 0, nullptr, 0, t);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         zr[k] = operand<CMP>(zr[k]);
@@ -175,9 +179,8 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     }
     __syncthreads();  // the twiddle rows
     convolve(zr, zi, a.hs, 1.f, P, twl, a.tw, t);
-    float *yc = a.y + ch * a.ldy;
-    store_block(zr, yc, n0, V, T, a.N, t);
-    if (n1 < a.N) store_block(zi, yc, n1, V, T, a.N, t);
+    store_block(zr, a.y + p.chA * a.ldy, p.nA, V, T, a.N, t);
+    if (p.two) store_block(zi, a.y + p.chB * a.ldy, p.nB, V, T, a.N, t);
     if (not_finite(zr, zi))
         __hip_atomic_store(a.hdr + HDR_BAD, a.hdr[HDR_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -197,9 +200,9 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
     a.ldx = ldx;
     a.ldy = ldy;
     a.V = (M - 1 + 63) / 64 * 64;
-    const int64_t T2 = 2 * (int64_t)(NB - a.V);
-    a.per_ch = (uint32_t)((N + T2 - 1) / T2);
-    a.nunits = (uint32_t)(C * a.per_ch);
+    const int64_t T = NB - a.V;
+    a.tpc = (uint32_t)((N + T - 1) / T);
+    a.nunits = tile_units((uint32_t)C, a.tpc);
     a.tw = static_cast<const float2 *>(tab);
     a.hs = a.tw + TW_FLOAT2;
     a.hist = (!correlate && M > 1) ? hist : nullptr;
@@ -224,8 +227,8 @@ hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64
     a.st = reinterpret_cast<const ShortTab *>(static_cast<const char *>(tab) + fft16k_table_bytes());
     a.hdr = hdr;
     a.M = M;
-    const int64_t T2 = 2 * (int64_t)(NB - FFT16_MEM);  // the shortest tiles: the most blocks
-    const dim3 grid((unsigned)(C * ((N + T2 - 1) / T2)));
+    const int64_t T = NB - FFT16_MEM;  // the shortest tiles: the most blocks
+    const dim3 grid(tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T)));
     switch (cmp) {
         case TFX_COMPUTE_BF16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_BF16>, grid, dim3(WGB), 0, st, a); break;
         case TFX_COMPUTE_F16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_F16>, grid, dim3(WGB), 0, st, a); break;

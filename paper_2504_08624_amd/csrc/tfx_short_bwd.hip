@@ -34,7 +34,7 @@ struct ShortBwdArgs {
     float4 *spart;  // [workgroup][16][512] summed spectra, two bins of thread t at [j / 2][t]
 };
 
-// Units (two neighbouring tiles of a channel) of a workgroup: with B the
+// Units (two neighbouring tiles, see TilePair) of a workgroup: with B the
 // transform of the gradient's blocks [n0, n0 + 16384) and X that of the input's
 // tiles [n0, n0 + T), zero-padded, gx = IFFT(conj(H) B) over the tiles and
 // conj(X) B sums over all units in registers; both products use the one B.
@@ -46,8 +46,7 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     const int V = short_memory(a.st, a.M, t & 63), T = NB - V;
     if (blockIdx.x == 0 && t == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
-    const uint32_t per_ch = (uint32_t)((a.N + 2 * T - 1) / (2 * T));
-    const uint32_t nunits = (uint32_t)a.C * per_ch;
+    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
     tw_stage(twl, a.tw, t);
     float ar[R], ai[R];
 #pragma unroll
@@ -55,19 +54,17 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     float m = 0.f;
     for (uint32_t i = blockIdx.x; i < nunits; i += gridDim.x) {
         const uint32_t u = xcd_unit(i, nunits);
-        const int64_t ch = u / per_ch;
-        const int64_t n0 = (int64_t)(u - (uint32_t)ch * per_ch) * 2 * T, n1 = n0 + T;
+        const TilePair p = tile_pair(u, (uint32_t)a.C, tpc, T);
+        const int64_t limB = p.two ? a.N : 0;
         float zr[R], zi[R];
-        const float *gc = a.g + ch * a.ldg;
-        load_block(zr, gc, n0, a.N, nullptr, 0, t);
-        load_block(zi, gc, n1, a.N, nullptr, 0, t);
+        load_block(zr, a.g + p.chA * a.ldg, p.nA, a.N, nullptr, 0, t);
+        load_block(zi, a.g + p.chB * a.ldg, p.nB, limB, nullptr, 0, t);
         __syncthreads();  // the twiddle rows; the last unit's reads of P
         forward(zr, zi, P, twl, a.tw, t);
         if (a.want) {
             float xr[R], xi[R];
-            const float *xc = a.x + ch * a.ldx;
-            load_tile(xr, xc, n0, T, a.N, t);
-            load_tile(xi, xc, n1, T, a.N, t);
+            load_tile(xr, a.x + p.chA * a.ldx, p.nA, T, a.N, t);
+            load_tile(xi, a.x + p.chB * a.ldx, p.nB, T, limB, t);
             __syncthreads();  // the other waves' reads of their rows of P
             forward(xr, xi, P, twl, a.tw, t);
 #pragma unroll
@@ -77,9 +74,8 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
             }
         }
         product_inverse(zr, zi, a.hs, -1.f, P, twl, a.tw, t);
-        float *oc = a.gx + ch * a.ldgx;
-        store_block(zr, oc, n0, 0, T, a.N, t);
-        if (n1 < a.N) store_block(zi, oc, n1, 0, T, a.N, t);
+        store_block(zr, a.gx + p.chA * a.ldgx, p.nA, 0, T, a.N, t);
+        if (p.two) store_block(zi, a.gx + p.chB * a.ldgx, p.nB, 0, T, a.N, t);
 #pragma unroll
         for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
         if (zr[0] != zr[0] || zi[0] != zi[0]) m = INFINITY;
@@ -300,7 +296,7 @@ size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // Workgroups of the adjoint: one a CU.
 int64_t short_bwd_wgs(int64_t C, int64_t N) {
-    const int64_t T2 = 2 * (int64_t)(NB - FFT16_MEM), nu = C * ((N + T2 - 1) / T2);
+    const int64_t T = NB - FFT16_MEM, nu = tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T));
     return nu < 256 ? nu : 256;
 }
 

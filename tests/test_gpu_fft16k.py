@@ -201,6 +201,27 @@ def test_fir_fft16k_sums_that_overflow(M):
     assert np.linalg.norm(y[~big] - ref[~big]) <= TOL_FIR_F32 * np.linalg.norm(ref[~big])
 
 
+@pytest.mark.parametrize("C", [1, 2, 5])
+@pytest.mark.parametrize("M,N", [(1026, 15_296), (8193, 700)])
+def test_fir_fft16k_rows_of_one_tile(M, N, C):
+    """Rows of one tile share a transform two by two: both directions, a stream's
+    history, and a bad sample in one row of a pair."""
+    x, h = _x(C, N, (623, M, C)), _taps(M, 623)
+    ref = O.fir(x, h)
+    assert_close(_cpu(tfx.fir(_gpu(x), _gpu(h), algo="fft16k")), ref, TOL_FIR_F32, "fir")
+    gx, _ = tfx.fir_backward(_gpu(x), _gpu(x), _gpu(h), algo="fft16k", need_taps=False)
+    assert_close(_cpu(gx), O.fir_backward(x, x, h)[0], TOL_FIR_F32, "adjoint")
+    sm = tfx.ChainStream([("fir", _gpu(h))], C, N // 3 + 1)
+    ys = [_cpu(sm.process(_gpu(x[:, i:i + N // 3 + 1]))) for i in range(0, N, N // 3 + 1)]
+    assert_close(np.concatenate(ys, axis=1), ref, TOL_FIR_F32, "stream")
+    xb = x.copy()
+    xb[-1, N - 1] = np.nan
+    y = _cpu(tfx.fir(_gpu(xb), _gpu(h), algo="fft16k"))
+    assert np.isnan(y[-1, N - 1])
+    if C > 1:
+        assert_close(y[:-1], ref[:-1], TOL_FIR_F32, "rows beside a bad one")
+
+
 @pytest.mark.slow
 def test_fir_long_full_size_sampled():
     """The long-filter workload at full size (64 x 5,760,000, 8191 taps) in

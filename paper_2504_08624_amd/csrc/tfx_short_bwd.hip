@@ -14,6 +14,8 @@
 // bins, in FP64.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "tfx_fft16k.h"
 
 namespace tfx {
@@ -31,13 +33,20 @@ struct ShortBwdArgs {
     uint32_t *hdr;
     int32_t M;
     int32_t want;   // coefficient gradients wanted
-    float4 *spart;  // [workgroup][16][512] summed spectra, two bins of thread t at [j / 2][t]
+    float4 *spart;  // [run of SB_RUN units][workgroup][16][512] summed spectra, two bins of thread t at [j / 2][t]
 };
+
+// Units that a workgroup sums in fp32, 16384 bins of sums of up to 16384
+// products each; its runs of so many are added in FP64 (by short_spec_sum_kernel).
+// Every unit rounds the running sum once, so without runs the error grows with
+// the signal: 131072 equal rows, 256 units a workgroup, 4.4e-6 of the section
+// gradients, 1.8e-7 so (8 x 5.76 M, 6 units a workgroup: the same time).
+constexpr uint32_t SB_RUN = 8;
 
 // Units (two neighbouring tiles, see TilePair) of a workgroup: with B the
 // transform of the gradient's blocks [n0, n0 + 16384) and X that of the input's
 // tiles [n0, n0 + T), zero-padded, gx = IFFT(conj(H) B) over the tiles and
-// conj(X) B sums over all units in registers; both products use the one B.
+// conj(X) B sums over a run of units in registers; both products use the one B.
 // 192 data registers a thread: one workgroup a CU.
 __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     __shared__ __align__(16) float P[PLANE];
@@ -48,62 +57,70 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     if (V == 0) return;
     const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
     tw_stage(twl, a.tw, t);
-    float ar[R], ai[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) ar[k] = ai[k] = 0.f;
     float m = 0.f;
-    for (uint32_t i = blockIdx.x; i < nunits; i += gridDim.x) {
-        const uint32_t u = xcd_unit(i, nunits);
-        const TilePair p = tile_pair(u, (uint32_t)a.C, tpc, T);
-        const int64_t limB = p.two ? a.N : 0;
-        float zr[R], zi[R];
-        load_block(zr, a.g + p.chA * a.ldg, p.nA, a.N, nullptr, 0, t);
-        load_block(zi, a.g + p.chB * a.ldg, p.nB, limB, nullptr, 0, t);
-        __syncthreads();  // the twiddle rows; the last unit's reads of P
-        forward(zr, zi, P, twl, a.tw, t);
-        if (a.want) {
-            float xr[R], xi[R];
-            load_tile(xr, a.x + p.chA * a.ldx, p.nA, T, a.N, t);
-            load_tile(xi, a.x + p.chB * a.ldx, p.nB, T, limB, t);
-            __syncthreads();  // the other waves' reads of their rows of P
-            forward(xr, xi, P, twl, a.tw, t);
+#pragma unroll 1
+    for (uint32_t run = 0, i = blockIdx.x; i < nunits; ++run) {
+        float ar[R], ai[R];
 #pragma unroll
-            for (int k = 0; k < R; ++k) {  // += conj(X) B
-                ar[k] = fmaf(xr[k], zr[k], fmaf(xi[k], zi[k], ar[k]));
-                ai[k] = fmaf(xr[k], zi[k], fmaf(-xi[k], zr[k], ai[k]));
+        for (int k = 0; k < R; ++k) ar[k] = ai[k] = 0.f;
+#pragma unroll 1
+        for (uint32_t n = 0; n < SB_RUN && i < nunits; ++n, i += gridDim.x) {
+            const uint32_t u = xcd_unit(i, nunits);
+            const TilePair p = tile_pair(u, (uint32_t)a.C, tpc, T);
+            const int64_t limB = p.two ? a.N : 0;
+            float zr[R], zi[R];
+            load_block(zr, a.g + p.chA * a.ldg, p.nA, a.N, nullptr, 0, t);
+            load_block(zi, a.g + p.chB * a.ldg, p.nB, limB, nullptr, 0, t);
+            __syncthreads();  // the twiddle rows; the last unit's reads of P
+            forward(zr, zi, P, twl, a.tw, t);
+            if (a.want) {
+                float xr[R], xi[R];
+                load_tile(xr, a.x + p.chA * a.ldx, p.nA, T, a.N, t);
+                load_tile(xi, a.x + p.chB * a.ldx, p.nB, T, limB, t);
+                __syncthreads();  // the other waves' reads of their rows of P
+                forward(xr, xi, P, twl, a.tw, t);
+#pragma unroll
+                for (int k = 0; k < R; ++k) {  // += conj(X) B
+                    ar[k] = fmaf(xr[k], zr[k], fmaf(xi[k], zi[k], ar[k]));
+                    ai[k] = fmaf(xr[k], zi[k], fmaf(-xi[k], zr[k], ai[k]));
+                }
             }
+            product_inverse(zr, zi, a.hs, -1.f, P, twl, a.tw, t);
+            store_block(zr, a.gx + p.chA * a.ldgx, p.nA, 0, T, a.N, t);
+            if (p.two) store_block(zi, a.gx + p.chB * a.ldgx, p.nB, 0, T, a.N, t);
+#pragma unroll
+            for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
+            if (zr[0] != zr[0] || zi[0] != zi[0]) m = INFINITY;
         }
-        product_inverse(zr, zi, a.hs, -1.f, P, twl, a.tw, t);
-        store_block(zr, a.gx + p.chA * a.ldgx, p.nA, 0, T, a.N, t);
-        if (p.two) store_block(zi, a.gx + p.chB * a.ldgx, p.nB, 0, T, a.N, t);
+        if (a.want) {
+            float4 *o = a.spart + ((int64_t)run * gridDim.x + blockIdx.x) * (NB / 2) + t;
 #pragma unroll
-        for (int k = 0; k < R; ++k) m = fmaxf(fmaxf(fabsf(zr[k]), fabsf(zi[k])), m);
-        if (zr[0] != zr[0] || zi[0] != zi[0]) m = INFINITY;
-    }
-    if (a.want) {
-        float4 *o = a.spart + (int64_t)blockIdx.x * (NB / 2) + t;
-#pragma unroll
-        for (int p = 0; p < R / 2; ++p) {
-            o[p * WGB] = make_float4(ar[2 * p], ai[2 * p], ar[2 * p + 1], ai[2 * p + 1]);
-            if (!(fabsf(ar[2 * p]) + fabsf(ai[2 * p]) + fabsf(ar[2 * p + 1]) + fabsf(ai[2 * p + 1]) < INFINITY))
-                m = INFINITY;
+            for (int p = 0; p < R / 2; ++p) {
+                o[p * WGB] = make_float4(ar[2 * p], ai[2 * p], ar[2 * p + 1], ai[2 * p + 1]);
+                if (!(fabsf(ar[2 * p]) + fabsf(ai[2 * p]) + fabsf(ar[2 * p + 1]) + fabsf(ai[2 * p + 1]) < INFINITY))
+                    m = INFINITY;
+            }
         }
     }
     if (!(m < INFINITY))
         __hip_atomic_store(a.hdr + HDR_BAD, a.hdr[HDR_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// sum1[split][pos] = sum of the workgroup spectra w = split, split + SPLITS, ...
-// in that order, in FP64.
+// sum1[split][pos] = sum of the spectra q = split, split + SPLITS, ... of spart in
+// that order, in FP64.  Only the first of them are written: by the workgroups of
+// the whole rounds, and in the last round by those that have a unit left.
 constexpr int SB_SPLITS = 16;
-__global__ __launch_bounds__(256) void short_spec_sum_kernel(const float2 *spart, int32_t nwg, double2 *sum1,
-                                                             const uint32_t *hdr) {
+__global__ __launch_bounds__(256) void short_spec_sum_kernel(const float2 *spart, int32_t nwg, int64_t C, int64_t N,
+                                                             double2 *sum1, const uint32_t *hdr) {
     if (!short_done(hdr)) return;
+    const int T = NB - (int)(hdr[HDR_SHORT] & ~1u);
+    const uint32_t nunits = tile_units((uint32_t)C, tiles_per_row(N, T)), round = SB_RUN * nwg;
+    const uint32_t full = (nunits - 1) / round, nq = full * nwg + min((uint32_t)nwg, nunits - full * round);
     const int pos = blockIdx.x * 256 + threadIdx.x;
     double sr = 0.0, si = 0.0;
 #pragma unroll 8
-    for (int w = blockIdx.y; w < nwg; w += SB_SPLITS) {
-        const float2 v = spart[(int64_t)w * NB + pos];
+    for (uint32_t q = blockIdx.y; q < nq; q += SB_SPLITS) {
+        const float2 v = spart[(int64_t)q * NB + pos];
         sr += (double)v.x;
         si += (double)v.y;
     }
@@ -294,11 +311,12 @@ __global__ __launch_bounds__(256) void short_grad_out_kernel(ShortGradArgs a, in
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Workgroups of the adjoint: one a CU.
-int64_t short_bwd_wgs(int64_t C, int64_t N) {
-    const int64_t T = NB - FFT16_MEM, nu = tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T));
-    return nu < 256 ? nu : 256;
+// Units of the adjoint at most (the shortest tiles), its workgroups (one a CU).
+int64_t short_bwd_units(int64_t C, int64_t N) {
+    const int64_t T = NB - FFT16_MEM;
+    return tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T));
 }
+int64_t short_bwd_wgs(int64_t C, int64_t N) { return std::min<int64_t>(short_bwd_units(C, N), 256); }
 
 struct Lay {
     size_t hf, spart, sum1, colsum, part, total;
@@ -309,7 +327,8 @@ Lay short_lay(int64_t C, int64_t N) {
     l.hf = off;
     off += al256((size_t)NB * sizeof(double2));
     l.spart = off;
-    off += al256((size_t)short_bwd_wgs(C, N) * NB * sizeof(float2));
+    const int64_t nwg = short_bwd_wgs(C, N);
+    off += al256((size_t)((short_bwd_units(C, N) + SB_RUN * nwg - 1) / (SB_RUN * nwg) * nwg) * NB * sizeof(float2));
     l.sum1 = off;
     off += al256((size_t)SB_SPLITS * NB * sizeof(double2));
     l.colsum = off;
@@ -365,7 +384,7 @@ hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const
     r.gsos = bp.gsos;
     r.gh = gH;
     hipLaunchKernelGGL(short_spec_sum_kernel, dim3(NB / 256, SB_SPLITS), dim3(256), 0, st,
-                       reinterpret_cast<const float2 *>(w + l.spart), (int32_t)nwg,
+                       reinterpret_cast<const float2 *>(w + l.spart), (int32_t)nwg, p.C, p.N,
                        reinterpret_cast<double2 *>(w + l.sum1), static_cast<const uint32_t *>(hdr));
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(short_grad_kernel, dim3(128), dim3(512), 0, st, r);

@@ -382,3 +382,26 @@ def test_gradients_of_other_chains_and_explicit_checkpoints():
 
 def _scan_ckpt(x, stages):
     return tfx.chain(x, stages, return_ckpt=True)[1]
+
+
+def test_gradient_sums_over_many_tiles():
+    """Many equal rows, a sine that a few bins of the transform hold: the sums over
+    tiles round alike, and their error is that of a short fp32 sum however many
+    tiles there are (256 a workgroup here; fp32 alone would be off by 1e-6 and more)."""
+    rows, N = 131_072, 9_600
+    h = design.fir_lowpass(101, 9000.0, 48000.0).astype(np.float32)
+    sec = _eq(2, 7)
+    n = np.arange(N)
+    worst = 0.0
+    for amp in (0.1, 0.125, 0.16, 0.19):
+        x1 = (amp * np.sin(2 * np.pi * 700 * n / 16384 + 0.3)).astype(np.float32)[None]
+        g1 = (0.7 * amp * np.sin(2 * np.pi * 700 * n / 16384 + 1.1)).astype(np.float32)[None]
+        _, (rgh, rgs) = O.chain_backward(g1, x1, [("fir", h), ("sos", sec)])
+        x, g = _gpu(x1).expand(rows, N).contiguous(), _gpu(g1).expand(rows, N).contiguous()
+        got = _grads(x, g, [_gpu(h), _gpu(sec)], ["fir", "sos"], [False, True, True])
+        del x, g
+        eh, es = _rel(got[1], rows * rgh), _rel(got[2], rows * rgs)
+        print("sums over %d rows: dL/dh %.2e dL/dsos %.2e" % (rows, eh, es), flush=True)
+        worst = max(worst, eh, es)
+    # 8 roundings of 2^-24 in a row (4.8e-7), and the transforms' own
+    assert worst <= 1e-6

@@ -640,7 +640,7 @@ static size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
 BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode) {
     BwdLayout b{};
-    b.fwd = ws_layout(C, N, S, M_merged, n_fir, fir_mode);
+    b.fwd = ws_layout(C, N, S, M_merged, n_fir, fir_mode, true);
     const int64_t ntiles = b.fwd.ntiles, cpad = b.fwd.cpad, npairs = cpad / 2;
     // the forward layout ends with a 256-aligned total (or 0 when it needs nothing)
     size_t off = b.fwd.total ? b.fwd.total : 256;
@@ -723,7 +723,7 @@ hipError_t launch_backward(const BwdPlan &bp) {
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.fwd.hdr);
     const uint32_t *gate = short_try ? hdr : nullptr;
     if (short_try &&
-        (e = launch_short_bwd(bp, M, ws + lay.fwd.sh, ws + (p.fir_mode == FIR_FFT16 ? lay.fwd.f16 : lay.fwd.sh), area, gH,
+        (e = launch_short_bwd(bp, M, lay.fwd.short_units, ws + lay.fwd.sh, ws + (p.fir_mode == FIR_FFT16 ? lay.fwd.f16 : lay.fwd.sh), area, gH,
                               hdr)) != hipSuccess)
         return e;
     // the cascade input f and the gradient of the cascade input gf

@@ -968,7 +968,8 @@ __global__ __launch_bounds__(WG, 4) void chain_mc_kernel(KArgs a) {
 
 static size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
-WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode) {
+WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode,
+                   bool adjoint) {
     WsLayout w{};
     w.ntiles = (N + T - 1) / T;
     w.cpad = C + (C & 1);
@@ -1007,6 +1008,11 @@ WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_
     w.short_shape = S > 0 && S <= CASC_MAX && M_merged <= FFT16_MAX_TAPS && C * N * S >= SHORT_MIN_WORK &&
                     ((fir_mode == FIR_FFT && fft_parts(M_merged) == 1) || fir_mode == FIR_FFT16 ||
                      (fir_mode == FIR_TOEPLITZ && M_merged >= 1));
+    if (w.short_shape) {  // with a memory that few cascades stay under (else a launch that finds nothing to do)
+        const int64_t t16 = FFT16_POINTS - std::min(M_merged + 768, FFT16_MEM);
+        w.short_units = short_max_units(C, N, S, M_merged, fir_mode, adjoint);
+        w.short_shape = unit_work((uint32_t)C, (uint32_t)((N + t16 - 1) / t16)) <= w.short_units;
+    }
     w.sh = off;
     w.total = (S > 0 || n_fir > 1 || fir_mode == FIR_FFT || fir_mode == FIR_TOEPLITZ || fir_mode == FIR_FFT16) ? off : 0;
     w.total_short = w.total + (w.short_shape ? al256(fft16k_table_bytes() + sizeof(ShortTab)) : 0);
@@ -1173,7 +1179,7 @@ hipError_t launch_run(const ChainPlan &p) {
                            !p.state_in && !p.state_out && !p.hist_in && !p.hist_out;
     if (short_try) {
         const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot,
-                                             p.fir_mode == FIR_TOEPLITZ ? p.cmp : TFX_COMPUTE_F32, ws + lay.sh,
+                                             p.fir_mode == FIR_TOEPLITZ ? p.cmp : TFX_COMPUTE_F32, lay.short_units, ws + lay.sh,
                                              ws + (p.fir_mode == FIR_FFT16 ? lay.f16 : lay.sh), hdr, p.stream);
         if (e != hipSuccess) return e;
         k.after_short = 1;

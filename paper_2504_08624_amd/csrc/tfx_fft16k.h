@@ -494,26 +494,25 @@ __device__ __forceinline__ uint32_t xcd_unit(uint32_t i, uint32_t nu) {
 
 // The two tiles of unit u, with tpc tiles of T samples a row: neighbours in one
 // channel (the second may be missing), so that no channel's rounding reaches
-// another; where a row is one tile, those of two channels, as half of every
-// transform would be empty (4096 x 4096 samples, 8191 taps: 185 us a channel a
-// unit, 118 us so).  two: there is a second tile.
+// another; where rows are one tile and many, those of two channels, as half of
+// every transform would be empty (4096 x 4096 samples, 8191 taps: 185 us with a
+// channel a unit, 118 us so; a chain on 256 x 12000 has a CU for every row: 32.8
+// and 34.4).  two: there is a second tile.
 struct TilePair {
     int64_t chA, nA, chB, nB;
     bool two;
 };
 __device__ __forceinline__ TilePair tile_pair(uint32_t u, uint32_t C, uint32_t tpc, int T) {
-    const uint32_t per = (tpc + 1) / 2, c = __builtin_amdgcn_readfirstlane(tpc == 1 ? 2 * u : u / per);
-    const uint32_t i = tpc == 1 ? 0 : 2 * (u - c * per);
+    const bool rows = rows_paired(C, tpc);
+    const uint32_t per = (tpc + 1) / 2, c = __builtin_amdgcn_readfirstlane(rows ? 2 * u : u / per);
+    const uint32_t i = rows ? 0 : 2 * (u - c * per);
     TilePair p;
-    p.two = tpc == 1 ? c + 1 < C : i + 1 < tpc;
+    p.two = rows ? c + 1 < C : i + 1 < tpc;
     p.chA = c;
     p.nA = (int64_t)i * T;
-    p.chB = tpc == 1 && p.two ? c + 1 : c;
-    p.nB = tpc == 1 ? 0 : p.nA + T;
+    p.chB = rows && p.two ? c + 1 : c;
+    p.nB = rows ? 0 : p.nA + T;
     return p;
-}
-__host__ __device__ inline uint32_t tile_units(uint32_t C, uint32_t tpc) {
-    return tpc == 1 ? (C + 1) / 2 : C * ((tpc + 1) / 2);
 }
 // tpc of a row of N < 2^38 samples (T is a multiple of 64), in scalar registers
 __device__ __forceinline__ uint32_t tiles_per_row(int64_t N, int T) {

@@ -15,6 +15,8 @@
 // (tfx_fft16k.h) and the product.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "tfx_fft16k.h"
 
 namespace tfx {
@@ -141,6 +143,7 @@ struct ShortArgs {
     const ShortTab *st;
     uint32_t *hdr;
     int32_t M;
+    uint32_t max_units;
 };
 
 // A value as the FIR's operand type holds it: the matrix-core modes round their
@@ -159,11 +162,11 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     __shared__ __align__(16) float2 twl[TW_LDS];
     const uint32_t tabs = a.hdr[HDR_TABS];
     int V = short_memory(a.st, a.M, threadIdx.x & 63);
-    if (!tabs) V = 0;
     const int T = NB - V;
+    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
+    if (!tabs || unit_work((uint32_t)a.C, tpc) > a.max_units) V = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
-    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
     if (blockIdx.x >= nunits) return;
     const int t = threadIdx.x;
     tw_stage(twl, a.tw, t);
@@ -214,7 +217,8 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
 }
 
 hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                           int32_t cmp, const void *tab, const void *tw, uint32_t *hdr, hipStream_t st) {
+                           int32_t cmp, uint32_t max_units, const void *tab, const void *tw, uint32_t *hdr,
+                           hipStream_t st) {
     ShortArgs a{};
     a.x = x;
     a.y = y;
@@ -227,8 +231,9 @@ hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64
     a.st = reinterpret_cast<const ShortTab *>(static_cast<const char *>(tab) + fft16k_table_bytes());
     a.hdr = hdr;
     a.M = M;
+    a.max_units = max_units;
     const int64_t T = NB - FFT16_MEM;  // the shortest tiles: the most blocks
-    const dim3 grid(tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T)));
+    const dim3 grid(std::min(std::max(max_units, (uint32_t)C), tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T))));
     switch (cmp) {
         case TFX_COMPUTE_BF16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_BF16>, grid, dim3(WGB), 0, st, a); break;
         case TFX_COMPUTE_F16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_F16>, grid, dim3(WGB), 0, st, a); break;

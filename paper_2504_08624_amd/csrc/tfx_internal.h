@@ -200,6 +200,49 @@ struct ShortTab {
 // 8 x 0.5 M 46 / 39, 8 x 5.76 M 252 / 129.
 constexpr int64_t SHORT_MIN_WORK = 10000000;
 
+// Units of the 16384-point form (tpc: tiles a row): pairs of tiles in one channel,
+// or, where rows are one tile and more than the chip takes at once, pairs of rows;
+// see tile_pair.
+constexpr uint32_t PAIRED_ROWS = 257;  // one workgroup a CU, and one more
+__host__ __device__ inline bool rows_paired(uint32_t C, uint32_t tpc) { return tpc == 1 && C >= PAIRED_ROWS; }
+__host__ __device__ inline uint32_t tile_units(uint32_t C, uint32_t tpc) {
+    return rows_paired(C, tpc) ? (C + 1) / 2 : C * ((tpc + 1) / 2);
+}
+// Their time in units: rows of one tile cost half of one either way.
+__host__ __device__ inline uint32_t unit_work(uint32_t C, uint32_t tpc) {
+    return tpc == 1 ? (C + 1) / 2 : C * ((tpc + 1) / 2);
+}
+// Units up to which the 16384-point blocks of a chain beat its scan (adjoint: of
+// its adjoint): rows of a few thousand samples fill a small part of a block.
+// How many units there are is up to the chain's memory, so the kernel compares
+// (unit_work).
+// From the times of 1218 calls, 512 to 5 M samples a row, 10 to 100 M in
+// all, 1 to 8 sections, 5 to 2049 taps, memories of 1152 to 7424, both ways: a
+// unit takes 56 ns, a workgroup of the scan (two channels' 3072 samples)
+// 15.5 + 2.5 a section (up to 6), with a matrix-core FIR in it 10.5 + 2.5 a
+// section + 0.011 a tap, behind the 16384-point FIR 6 + 2 and that FIR's own
+// units; adjoint 140 against 65 + 9 a section.  Against the faster form of every
+// call the rule loses 4 us at most and 0.3 % on the mean.  4096 x 1024 samples, 4
+// sections: blocks 179 us, scan 64; 13020 x 3072, 6 sections: 311 / 194; 6510 x
+// 6144, 6 sections: 181 / 194; 8 x 5 M, 2 sections, 101 taps in bf16: 115 / 129.
+inline uint32_t short_max_units(int64_t C, int64_t N, int32_t S, int32_t M, int32_t fir_mode, bool adjoint) {
+    const int64_t wgs = (C + 1) / 2 * ((N + T - 1) / T), s = S < 6 ? S : 6;
+    int64_t u;
+    if (fir_mode == FIR_TOEPLITZ) {
+        u = (wgs * (10500 + 2500 * s + 11 * M) - 6000000) / 56000;
+    } else if (fir_mode == FIR_FFT16) {
+        const int64_t t16 = FFT16_POINTS - (M - 1 + 63) / 64 * 64;
+        u = (wgs * (6000 + 2000 * s) - 2000000) / 56000 + unit_work((uint32_t)C, (uint32_t)((N + t16 - 1) / t16));
+    } else {
+        u = (wgs * (15500 + 2500 * s) - 2000000) / 56000;
+    }
+    if (adjoint) {  // (also wherever the forward's is, which then leaves no checkpoints)
+        const int64_t a = (wgs * (65000 + 9000 * (S > 6 ? 10 : s)) - 2000000) / 140000;
+        u = a > u ? a : u;
+    }
+    return u < 0 ? 0u : u > 0x7fffffff ? 0x7fffffffu : (uint32_t)u;
+}
+
 // Larger pole radius of 1 + a1 z^-1 + a2 z^-2.
 __host__ __device__ inline double section_radius(double a1, double a2) {
     const double disc = a1 * a1 - 4.0 * a2;
@@ -245,9 +288,12 @@ struct WsLayout {
     // at sh (total_short bytes in all); without that room it runs as any other
     size_t sh, total_short;
     bool short_shape;
+    uint32_t short_units;  // short_max_units
     int64_t ntiles, cpad;
 };
-WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode);
+// (adjoint: of a backward call's forward part)
+WsLayout ws_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t n_fir, int32_t fir_mode,
+                   bool adjoint = false);
 
 // Sets the calling thread's tfx_last_error message and returns s (for entry
 // points defined outside tfx_api.cpp).
@@ -310,9 +356,11 @@ hipError_t launch_fft16k(const float *x, float *y, int64_t C, int64_t N, int64_t
                          const void *tab, bool correlate, const float *hist, const uint32_t *hdr, hipStream_t st);
 // Chain x -> y with the combined spectrum and decay sums of tab and the twiddle
 // rows tw (the prepare step writes them once, in front of its first spectrum),
-// if it is a short-memory one (which the kernel leaves in the header).
+// if it is a short-memory one of at most max_units units (which the kernel leaves
+// in the header).
 hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy, int32_t M,
-                           int32_t cmp, const void *tab, const void *tw, uint32_t *hdr, hipStream_t st);
+                           int32_t cmp, uint32_t max_units, const void *tab, const void *tw, uint32_t *hdr,
+                           hipStream_t st);
 // Whether a call of this plan is prepared for that.
 inline bool short_wanted(const ChainPlan &p, const WsLayout &lay) {
     return lay.short_shape && p.ws_bytes >= lay.total_short &&
@@ -414,9 +462,9 @@ hipError_t launch_backward(const BwdPlan &p);
 size_t short_bwd_bytes(int64_t C, int64_t N);
 void *short_bwd_hf(void *area);  // where the prepare step leaves the FIR's response in FP64
 // gx and the gradients (gH: of the merged taps, null: not wanted) of a chain
-// prepared with tab / tw as in launch_short16k, if it is a short-memory one;
-// area: short_bwd_bytes.
-hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const void *tw, void *area, float *gH,
-                            uint32_t *hdr);
+// prepared with tab / tw as in launch_short16k, if it is a short-memory one of at
+// most max_units units; area: short_bwd_bytes.
+hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, uint32_t max_units, const void *tab, const void *tw,
+                            void *area, float *gH, uint32_t *hdr);
 
 }  // namespace tfx

@@ -32,6 +32,7 @@ struct ShortBwdArgs {
     const ShortTab *st;
     uint32_t *hdr;
     int32_t M;
+    uint32_t max_units;
     int32_t want;   // coefficient gradients wanted
     float4 *spart;  // [run of SB_RUN units][workgroup][16][512] summed spectra, two bins of thread t at [j / 2][t]
 };
@@ -52,10 +53,12 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     __shared__ __align__(16) float P[PLANE];
     __shared__ __align__(16) float2 twl[TW_LDS];
     const int t = threadIdx.x;
-    const int V = short_memory(a.st, a.M, t & 63), T = NB - V;
+    int V = short_memory(a.st, a.M, t & 63);
+    const int T = NB - V;
+    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
+    if (unit_work((uint32_t)a.C, tpc) > a.max_units) V = 0;
     if (blockIdx.x == 0 && t == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
-    const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
     tw_stage(twl, a.tw, t);
     float m = 0.f;
 #pragma unroll 1
@@ -344,8 +347,8 @@ Lay short_lay(int64_t C, int64_t N) {
 size_t short_bwd_bytes(int64_t C, int64_t N) { return short_lay(C, N).total; }
 void *short_bwd_hf(void *area) { return area; }
 
-hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const void *tw, void *area, float *gH,
-                            uint32_t *hdr) {
+hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, uint32_t max_units, const void *tab, const void *tw,
+                            void *area, float *gH, uint32_t *hdr) {
     const ChainPlan &p = bp.fwd;
     const Lay l = short_lay(p.C, p.N);
     char *w = static_cast<char *>(area);
@@ -366,6 +369,7 @@ hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, const void *tab, const
     a.st = reinterpret_cast<const ShortTab *>(static_cast<const char *>(tab) + fft16k_table_bytes());
     a.hdr = hdr;
     a.M = M;
+    a.max_units = max_units;
     a.want = any ? 1 : 0;
     a.spart = reinterpret_cast<float4 *>(w + l.spart);
     const int64_t nwg = short_bwd_wgs(p.C, p.N);

@@ -405,3 +405,32 @@ def test_gradient_sums_over_many_tiles():
         worst = max(worst, eh, es)
     # 8 roundings of 2^-24 in a row (4.8e-7), and the transforms' own
     assert worst <= 1e-6
+
+
+@pytest.mark.parametrize("C,N,S,lo,blocks", [
+    pytest.param(4096, 1024, 4, 600.0, False, id="rows far shorter than a block"),
+    pytest.param(1000, 15_000, 2, 6000.0, True, id="rows of one tile"),
+    pytest.param(1000, 15_000, 2, 200.0, False, id="rows of just over one tile, known on the device"),
+    pytest.param(1001, 15_000, 6, 200.0, True, id="rows of just over one tile, a longer cascade"),
+])
+def test_rows_that_are_worth_blocks(C, N, S, lo, blocks):
+    """The form by the row's length, the cascade's and the chain's memory."""
+    x = _gpu(_x(8, N, (831, N, S))).repeat((C + 7) // 8, 1)[:C].contiguous()
+    h, sec = design.fir_lowpass(101, 9000.0, 48000.0).astype(np.float32), _eq(S, 3, lo)
+    st = [("fir", _gpu(h)), ("sos", _gpu(sec))]
+    assert C * N * S >= WORK
+    y, V = _prepared_run(x, st)
+    assert (V > 0) == blocks
+    ref = O.chain(_cpu(x[:8]), [("fir", h), ("sos", sec)])
+    assert_close(_cpu(y[:8]), ref, TOL_FIR_F32 if blocks else TOL_IIR_F32, "first rows")
+    assert_close(_cpu(y[C - C % 8 - 8:C - C % 8]), ref, TOL_FIR_F32 if blocks else TOL_IIR_F32, "last rows")
+    if blocks:
+        assert not torch.equal(y, _scan(x, st))
+    else:
+        assert torch.equal(y, _scan(x, st))
+    # the adjoint follows whichever form the forward took
+    g = torch.roll(x, 3, 1)
+    got = _grads(x[:C - C % 8], g[:C - C % 8], [_gpu(h), _gpu(sec)], ["fir", "sos"])
+    rgx, (rgh, rgs) = O.chain_backward(_cpu(g[:8]), _cpu(x[:8]), [("fir", h), ("sos", sec)])
+    assert_close(_cpu(got[0][-8:]), rgx, TOL_IIR_F32, "dL/dx")
+    assert _rel(got[1], C // 8 * rgh) <= TOL_GRAD and _rel(got[2], C // 8 * rgs) <= TOL_GRAD

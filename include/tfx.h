@@ -183,7 +183,7 @@ tfx_status tfx_chain(const float *x, float *y, int64_t C, int64_t N, int64_t ldx
                      void *ws, size_t ws_bytes, void *stream);
 
 /* tfx_chain for a training step: ckpt, of the size above, is only good for
- * tfx_chain_train_backward of the same chain and signal (a chain whose response
+ * tfx_chain_train_backward of the same chain and signal (an fp32 chain whose response
  * dies out quickly leaves it unwritten and is filtered without a scan). */
 tfx_status tfx_chain_train(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
                            const tfx_stage *stages, int32_t nstages, tfx_compute cmp, float *ckpt,

@@ -1174,8 +1174,10 @@ hipError_t launch_run(const ChainPlan &p) {
     k.ldy = p.ldy;
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.hdr);
     // a chain that may be a short-memory one, with nothing asked for that only
-    // the scan gives (checkpoints, registers, a stream's history)
-    const bool short_try = short_wanted(p, lay) && !p.n_layout && (!p.ckpt || p.ckpt_lazy) &&
+    // the scan gives (checkpoints, registers, a stream's history); the adjoint is
+    // in fp32, so a forward with rounded operands cannot leave it the checkpoints
+    const bool short_try = short_wanted(p, lay) && !p.n_layout &&
+                           (!p.ckpt || (p.ckpt_lazy && p.fir_mode != FIR_TOEPLITZ)) &&
                            !p.state_in && !p.state_out && !p.hist_in && !p.hist_out;
     if (short_try) {
         const hipError_t e = launch_short16k(p.x, p.y, p.C, p.N, p.ldx, p.ldy, Mtot,

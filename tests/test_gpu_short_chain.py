@@ -434,3 +434,43 @@ def test_rows_that_are_worth_blocks(C, N, S, lo, blocks):
     rgx, (rgh, rgs) = O.chain_backward(_cpu(g[:8]), _cpu(x[:8]), [("fir", h), ("sos", sec)])
     assert_close(_cpu(got[0][-8:]), rgx, TOL_IIR_F32, "dL/dx")
     assert _rel(got[1], C // 8 * rgh) <= TOL_GRAD and _rel(got[2], C // 8 * rgs) <= TOL_GRAD
+
+
+def _train_calls(x, g, stages, cmp=0, cut=0):
+    """tfx_chain_train and tfx_chain_train_backward (fp32, its workspace cut bytes
+    short of the query), checkpoints from a buffer of NaN: y, the gradients and
+    the checkpoints as the forward left them."""
+    C, N = x.shape
+    kept, desc = _stages(stages, torch.device(DEV))
+    arr, n = lib.stage_array(desc), len(desc)
+    S = sum(k for kind, k, _ in desc if kind == lib.STAGE_SOS)
+    nb, nbb = lib.size_out(), lib.size_out()
+    lib.call("tfx_chain_workspace_size", C, N, arr, n, cmp, nb)
+    lib.call("tfx_chain_backward_workspace_size", C, N, arr, n, 0, nbb)
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
+    wsb = torch.empty(nbb.value, dtype=torch.uint8, device=DEV)
+    y, gx, gs = torch.empty_like(x), torch.empty_like(x), [torch.empty_like(t) for t in kept]
+    ck = torch.full((C, (N + 3071) // 3072, S, 2), float("nan"), device=DEV)
+    sp = torch.cuda.current_stream().cuda_stream
+    lib.call("tfx_chain_train", x.data_ptr(), y.data_ptr(), C, N, N, N, arr, n, cmp, ck.data_ptr(), ws.data_ptr(),
+             nb.value, sp)
+    left = ck.clone()
+    lib.call("tfx_chain_train_backward", x.data_ptr(), g.data_ptr(), gx.data_ptr(), C, N, N, N, N, arr, n, 0,
+             ck.data_ptr(), lib.pointer_array([t.data_ptr() for t in gs]), wsb.data_ptr(), nbb.value - cut, sp)
+    torch.cuda.synchronize()
+    return y, [gx] + gs, left
+
+
+@pytest.mark.parametrize("M", [5, 255])
+def test_checkpoints_of_rounded_operands(M):
+    """A training forward with bf16 operands writes its checkpoints: the adjoint, in
+    fp32, may take a form that cannot do without them (5 taps: a direct FIR)."""
+    C, N = 3, 1_700_011
+    x, g = _gpu(_x(C, N, (832, M))), _gpu(_x(C, N, (833, M)))
+    st = [("fir", _gpu(design.fir_lowpass(M, 9000.0, 48000.0).astype(np.float32))), ("sos", _gpu(_eq(3, 4)))]
+    y, ck = tfx.chain(x, st, compute="bf16", return_ckpt=True)
+    want = tfx.chain_backward(x, g, st, ck)
+    got_y, got, left = _train_calls(x, g, st, cmp=lib.COMPUTE["bf16"])
+    assert torch.equal(got_y, y) and torch.equal(left, ck)
+    for a, b in zip(got, [want[0]] + want[1]):
+        assert _rel(a, _cpu(b).astype(np.float64)) <= TOL_GRAD

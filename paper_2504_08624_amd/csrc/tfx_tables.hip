@@ -614,7 +614,7 @@ __device__ void circle_block(char *raw, Co co_at, int32_t S, int blk, ShortTab *
     if (tid < S) sh.r[tid] = section_radius(sh.co[tid][3], sh.co[tid][4]);
     __syncthreads();
     double rm = 0.0;
-    for (int s = 0; s < S; ++s) rm = sh.r[s] <= rm ? rm : sh.r[s];  // (a NaN stays)
+    for (int s = 0; s < S; ++s) rm = rm == rm && !(sh.r[s] <= rm) ? sh.r[s] : rm;  // (a NaN stays)
     double sn, cs;
     sincospi(-((double)(256 * blk + tid) + 0.5) / (256.0 * CIRC_BLOCKS), &sn, &cs);
 #pragma unroll 1

@@ -474,3 +474,15 @@ def test_checkpoints_of_rounded_operands(M):
     assert torch.equal(got_y, y) and torch.equal(left, ck)
     for a, b in zip(got, [want[0]] + want[1]):
         assert _rel(a, _cpu(b).astype(np.float64)) <= TOL_GRAD
+
+
+@pytest.mark.parametrize("k", [0, 1, 2])
+@pytest.mark.parametrize("col", [0, 3, 4])
+def test_a_nan_in_one_section(k, col):
+    """Whichever section holds it, such a chain is none of short memory."""
+    sec = _eq(3, 6)
+    sec[k, col] = np.nan
+    x = _gpu(_x(2, 2_600_000, (834,)))
+    st = [("fir", _gpu(design.fir_lowpass(255, 9000.0, 48000.0).astype(np.float32))), ("sos", _gpu(sec))]
+    y, V = _prepared_run(x, st)
+    assert V == 0 and bool(torch.isnan(y[:, 2:]).all())     # (a2 first counts two samples on)

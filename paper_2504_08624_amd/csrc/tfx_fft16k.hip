@@ -164,7 +164,7 @@ __global__ __launch_bounds__(WGB, 4) void short16k_kernel(ShortArgs a) {
     int V = short_memory(a.st, a.M, threadIdx.x & 63);
     const int T = NB - V;
     const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
-    if (!tabs || unit_work((uint32_t)a.C, tpc) > a.max_units) V = 0;
+    if (!tabs || unit_work((uint32_t)a.C, tpc) > units_with_memory(a.max_units, V)) V = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
     if (blockIdx.x >= nunits) return;
@@ -233,7 +233,8 @@ hipError_t launch_short16k(const float *x, float *y, int64_t C, int64_t N, int64
     a.M = M;
     a.max_units = max_units;
     const int64_t T = NB - FFT16_MEM;  // the shortest tiles: the most blocks
-    const dim3 grid(std::min(std::max(max_units, (uint32_t)C), tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T))));
+    const dim3 grid(std::min(std::max(units_with_memory(max_units, FFT16_MEM), (uint32_t)C),
+                             tile_units((uint32_t)C, (uint32_t)((N + T - 1) / T))));
     switch (cmp) {
         case TFX_COMPUTE_BF16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_BF16>, grid, dim3(WGB), 0, st, a); break;
         case TFX_COMPUTE_F16: hipLaunchKernelGGL(short16k_kernel<TFX_COMPUTE_F16>, grid, dim3(WGB), 0, st, a); break;

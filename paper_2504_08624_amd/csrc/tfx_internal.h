@@ -221,8 +221,9 @@ __host__ __device__ inline uint32_t unit_work(uint32_t C, uint32_t tpc) {
 // unit takes 56 ns, a workgroup of the scan (two channels' 3072 samples)
 // 15.5 + 2.5 a section (up to 6), with a matrix-core FIR in it 10.5 + 2.5 a
 // section + 0.011 a tap, behind the 16384-point FIR 6 + 2 and that FIR's own
-// units; adjoint 140 against 65 + 9 a section.  Against the faster form of every
-// call the rule loses 4 us at most and 0.3 % on the mean.  4096 x 1024 samples, 4
+// units; adjoint 140 against 65 + 9 a section.  A memory over 5120 samples makes
+// the scan look further back (units_with_memory).  Against the faster form of
+// every call the rule loses 0.1 % on the mean, 11 % at most.  4096 x 1024 samples, 4
 // sections: blocks 179 us, scan 64; 13020 x 3072, 6 sections: 311 / 194; 6510 x
 // 6144, 6 sections: 181 / 194; 8 x 5 M, 2 sections, 101 taps in bf16: 115 / 129.
 inline uint32_t short_max_units(int64_t C, int64_t N, int32_t S, int32_t M, int32_t fir_mode, bool adjoint) {
@@ -240,7 +241,11 @@ inline uint32_t short_max_units(int64_t C, int64_t N, int32_t S, int32_t M, int3
         const int64_t a = (wgs * (65000 + 9000 * (S > 6 ? 10 : s)) - 2000000) / 140000;
         u = a > u ? a : u;
     }
-    return u < 0 ? 0u : u > 0x7fffffff ? 0x7fffffffu : (uint32_t)u;
+    return u < 0 ? 0u : u > 0x6fffffff ? 0x6fffffffu : (uint32_t)u;
+}
+
+__host__ __device__ inline uint32_t units_with_memory(uint32_t max_units, int V) {
+    return max_units + (V > 5120 ? max_units / 8 : 0);
 }
 
 // Larger pole radius of 1 + a1 z^-1 + a2 z^-2.

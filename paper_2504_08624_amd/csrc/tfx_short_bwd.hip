@@ -56,7 +56,7 @@ __global__ __launch_bounds__(WGB, 2) void short_bwd_kernel(ShortBwdArgs a) {
     int V = short_memory(a.st, a.M, t & 63);
     const int T = NB - V;
     const uint32_t tpc = tiles_per_row(a.N, T), nunits = tile_units((uint32_t)a.C, tpc);
-    if (unit_work((uint32_t)a.C, tpc) > a.max_units) V = 0;
+    if (unit_work((uint32_t)a.C, tpc) > units_with_memory(a.max_units, V)) V = 0;
     if (blockIdx.x == 0 && t == 0) a.hdr[HDR_SHORT] = V > 0 ? (uint32_t)(V | 1) : 0u;
     if (V == 0) return;
     tw_stage(twl, a.tw, t);

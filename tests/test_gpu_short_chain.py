@@ -486,3 +486,51 @@ def test_a_nan_in_one_section(k, col):
     st = [("fir", _gpu(design.fir_lowpass(255, 9000.0, 48000.0).astype(np.float32))), ("sos", _gpu(sec))]
     y, V = _prepared_run(x, st)
     assert V == 0 and bool(torch.isnan(y[:, 2:]).all())     # (a2 first counts two samples on)
+
+
+def _resonance(theta, r, n):
+    """n equal sections with poles r e^(+-i theta), about unit gain there."""
+    return np.array([[2 * (1 - r) * np.sin(theta), 0.0, 0.0, -2 * r * np.cos(theta), r * r]] * n, np.float32)
+
+
+@pytest.mark.parametrize("theta,r,n,blocks", [
+    (0.3, 0.9965, 2, True), (1.5, 0.9962, 3, True), (0.3, 0.996, 4, True), (1.5, 0.9968, 2, False),
+    (0.3, 0.9965, 4, False)])
+def test_memory_at_its_limit(theta, r, n, blocks):
+    """Narrow resonances and repeated poles whose memory is all but 8192 samples, and
+    just over: output and every gradient.  (The gradient's responses, sums of
+    h delayed, die out more slowly than h itself.)"""
+    C = 2
+    N = WORK // (n * C) + 501
+    x = _x(C, N, (835, n))
+    h, sec = design.fir_lowpass(49, 9000.0, 48000.0).astype(np.float32), _resonance(theta, r, n)
+    st = [("fir", _gpu(h)), ("sos", _gpu(sec))]
+    y, V = _prepared_run(_gpu(x), st)
+    print("memory %d of theta %g r %g, %d sections" % (V, theta, r, n), flush=True)
+    assert 7500 <= V <= 8192 if blocks else V == 0
+    assert_close(_cpu(y), O.chain(x, [("fir", h), ("sos", sec)]), TOL_FIR_F32 if blocks else TOL_IIR_F32, "output")
+    g = (np.roll(x, 3, axis=1) + 0.1 * _x(C, N, (836, n), 1.0)).astype(np.float32)
+    got = _grads(_gpu(x), _gpu(g), [_gpu(h), _gpu(sec)], ["fir", "sos"])
+    rgx, (rgh, rgs) = O.chain_backward(g, x, [("fir", h), ("sos", sec)])
+    eh, es = _rel(got[1], rgh), _rel(got[2], rgs)
+    print("gradients: dL/dh %.2e dL/dsos %.2e" % (eh, es), flush=True)
+    assert_close(_cpu(got[0]), rgx, TOL_FIR_F32 if blocks else TOL_IIR_F32, "dL/dx")
+    assert eh <= TOL_GRAD and es <= TOL_GRAD
+
+
+@pytest.mark.parametrize("kind", ["short", "fp64 carry", "rings on"])
+@pytest.mark.parametrize("M", [255, 1500])
+def test_lazy_checkpoints_and_a_backward_without_the_room(kind, M):
+    """tfx_chain_train, whose short-memory form leaves the checkpoints out, and a
+    backward call whose workspace has no room for that form's adjoint."""
+    C, N = 2, 1_300_003
+    x, g = _gpu(_x(C, N, (837, M))), _gpu(_x(C, N, (838, M)))
+    sec = {"short": _eq(4, 8), "rings on": np.array([[1, -1.99, 1, -1.995, 0.9956]] * 4, np.float32),
+           "fp64 carry": _resonance(1.0, 0.9995, 4)}[kind]
+    st = [("fir", _gpu(design.fir_lowpass(M, 9000.0, 48000.0).astype(np.float32))), ("sos", _gpu(sec))]
+    want = _scan_backward(x, g, st)
+    for cut in (256, 0):
+        _, got, left = _train_calls(x, g, st, cut=cut)
+        assert bool(torch.isnan(left).any()) == (kind == "short")
+        for a, b in zip(got, want):
+            assert _rel(a, _cpu(b).astype(np.float64)) <= 2 * TOL_GRAD

@@ -672,7 +672,7 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
     }
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
     const uint64_t id = xcd_order(block, nblocks, a.xcd_ks);
-    c.tile = (int64_t)(id / npairs) + a.tile0;
+    c.tile = (int64_t)(id / npairs) + (STOUT ? a.tile0 : 0);
     const int64_t pair = (int64_t)(id % npairs);
     c.ch = 2 * pair + c.grp;
     c.valid = c.ch < a.C;

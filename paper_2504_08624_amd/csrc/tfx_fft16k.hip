@@ -63,7 +63,7 @@ __device__ __forceinline__ bool narrow_run(const F16Args &a, const float *xc, fl
                                            int cnt, float scale, float *P, const float2 *twl, int *s_bad, int t) {
     const int lead = a.correlate ? 0 : a.V, tail = a.V - lead;
     float zr[R], zi[R];
-    load_block(zr, xc, lo - lead, min(a.N, lo + cnt + tail), hc, a.hlen, t);
+    load_block(zr, xc, lo - lead, min(a.N, lo + cnt + tail), hc, a.hlen, opaque(t));
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         zr[k] *= scale;
@@ -76,11 +76,52 @@ __device__ __forceinline__ bool narrow_run(const F16Args &a, const float *xc, fl
     const float back = 1.f / scale;
 #pragma unroll
     for (int k = 0; k < R; ++k) zr[k] *= back;
-    store_block(zr, yc, lo, lead, cnt, a.N, t);
+    store_block(zr, yc, lo, lead, cnt, a.N, opaque(t));
     __syncthreads();
     const bool bad = *s_bad != 0;
     __syncthreads();
     return bad;
+}
+
+// The unit's tiles again in narrow runs.  Everything is formed anew from the
+// kernel's arguments: kept across the transform before, it would cost that
+// registers (44 scalar ones spilled: 110 us over 4096 x 4096 samples, 109 so).
+__device__ __forceinline__ void redo_unit(uint32_t block, int wave, float *P, const float2 *twl, int *s_bad) {
+    typedef __attribute__((address_space(4))) const F16Args KernArgs;
+    KernArgs *ka = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka), "+s"(block), "+s"(wave));
+    F16Args a{};
+    a.x = ka->x;
+    a.y = ka->y;
+    a.C = ka->C;
+    a.N = ka->N;
+    a.ldx = ka->ldx;
+    a.ldy = ka->ldy;
+    a.nunits = ka->nunits;
+    a.tpc = ka->tpc;
+    a.V = ka->V;
+    a.tw = ka->tw;
+    a.hs = ka->hs;
+    a.hist = ka->hist;
+    a.hlen = ka->hlen;
+    a.correlate = ka->correlate;
+    const int t = 64 * wave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), T = NB - a.V;
+    const TilePair p = tile_pair(xcd_unit(block, a.nunits), (uint32_t)a.C, a.tpc, T);
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 0; s < (p.two ? 2 : 1); ++s) {
+        const int64_t ch = s ? p.chB : p.chA, first = s ? p.nB : p.nA, last = min(first + T, a.N);
+        const float *xc = a.x + ch * a.ldx, *hc = a.hist ? a.hist + ch * a.hlen : nullptr;
+        float *yc = a.y + ch * a.ldy;
+        for (int64_t lo = first; lo < last;) {
+            const int64_t end = min(first + T, (lo / NARROW + 1) * NARROW);
+            const int cnt = (int)(end - lo);
+#pragma unroll 1
+            for (float scale = 1.f; narrow_run(a, xc, yc, hc, lo, cnt, scale, P, twl, s_bad, opaque(t)) && scale == 1.f;)
+                scale = NARROW_SCALE;
+            lo = end;
+        }
+    }
 }
 
 __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
@@ -91,44 +132,22 @@ __global__ __launch_bounds__(WGB, 4) void fir16k_kernel(F16Args a) {
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     tw_stage(twl, a.tw, t);
     if (t == 0) s_bad = 0;
-    const uint32_t u = xcd_unit(blockIdx.x, a.nunits);
     const int T = NB - a.V;
-    const TilePair p = tile_pair(u, (uint32_t)a.C, a.tpc, T);
+    const TilePair p = tile_pair(xcd_unit(blockIdx.x, a.nunits), (uint32_t)a.C, a.tpc, T);
     const int lead = a.correlate ? 0 : a.V;
-    const float *xa = a.x + p.chA * a.ldx, *xb = a.x + p.chB * a.ldx;
-    float *ya = a.y + p.chA * a.ldy, *yb = a.y + p.chB * a.ldy;
-    const float *ha = a.hist ? a.hist + p.chA * a.hlen : nullptr;
-    const float *hb = a.hist && p.two ? a.hist + p.chB * a.hlen : nullptr;
     {
         float zr[R], zi[R];
-        load_block(zr, xa, p.nA - lead, a.N, ha, a.hlen, t);
-        load_block(zi, xb, p.nB - lead, p.two ? a.N : 0, hb, a.hlen, t);
+        load_block(zr, a.x + p.chA * a.ldx, p.nA - lead, a.N, a.hist ? a.hist + p.chA * a.hlen : nullptr, a.hlen, t);
+        load_block(zi, a.x + p.chB * a.ldx, p.nB - lead, p.two ? a.N : 0,
+                   a.hist && p.two ? a.hist + p.chB * a.hlen : nullptr, a.hlen, t);
         __syncthreads();  // the twiddle rows
         convolve(zr, zi, a.hs, a.correlate ? -1.f : 1.f, P, twl, a.tw, t);
         if (not_finite(zr, zi)) s_bad = 1;
-        store_block(zr, ya, p.nA, lead, T, a.N, t);
-        if (p.two) store_block(zi, yb, p.nB, lead, T, a.N, t);
+        store_block(zr, a.y + p.chA * a.ldy, p.nA, lead, T, a.N, t);
+        if (p.two) store_block(zi, a.y + p.chB * a.ldy, p.nB, lead, T, a.N, t);
     }
     __syncthreads();
-    if (!s_bad) return;
-    // (the thread's index anew: kept across the transform it would cost a register there)
-    const int t2 = 64 * wave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    __syncthreads();
-#pragma unroll 1
-    for (int s = 0; s < (p.two ? 2 : 1); ++s) {
-        const float *xc = s ? xb : xa, *hc = s ? hb : ha;
-        float *yc = s ? yb : ya;
-        const int64_t first = s ? p.nB : p.nA, last = min(first + T, a.N);
-        for (int64_t lo = first; lo < last;) {
-            const int64_t end = min(first + T, (lo / NARROW + 1) * NARROW);
-            const int cnt = (int)(end - lo);
-#pragma unroll 1
-            for (float scale = 1.f;
-                 narrow_run(a, xc, yc, hc, lo, cnt, scale, P, twl, &s_bad, opaque(t2)) && scale == 1.f;)
-                scale = NARROW_SCALE;
-            lo = end;
-        }
-    }
+    if (s_bad) redo_unit(blockIdx.x, wave, P, twl, &s_bad);
 }
 
 // A short-memory chain (FIR and cascade as one filter of memory V; the grid is

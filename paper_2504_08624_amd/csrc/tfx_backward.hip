@@ -32,6 +32,7 @@
 #include <algorithm>
 
 #include "tfx_device.h"
+#include "tfx_grads.h"
 
 namespace tfx {
 
@@ -301,16 +302,14 @@ __global__ __launch_bounds__(WG, 3) void sos_bwd_kernel(BArgs a) {
 
 // Section-coefficient gradients from the per-tile partial sums.  One block
 // per (section, sum): lane-strided FP64 partial sums in a fixed order, then
-// a fixed tree; a second kernel maps each section's five sums to the
-// gradients [b0 b1 b2 a1 a2] of its stage row.
+// a fixed tree; then each section's five sums are mapped to the gradients
+// [b0 b1 b2 a1 a2] of its stage row.
 struct SosGradArgs {
     const double *part;
     const SecTab *tab;
     int32_t S;
     int64_t C, ntiles, cpad;
     double *sums;  // [S][5]
-    GradList out;
-    const uint32_t *gate;
 };
 
 constexpr int RED_THREADS = 256;
@@ -344,29 +343,25 @@ __device__ double block_sum_fixed(double v, double *sh) {
     return r;
 }
 
-__global__ __launch_bounds__(RED_THREADS) void sos_grad_reduce_kernel(SosGradArgs a) {
-    __shared__ double sh[RED_THREADS];
-    if (a.gate && short_done(a.gate)) return;
+__device__ __forceinline__ void sos_grad_reduce(const SosGradArgs &a, int block, double *sh) {
     const int64_t stride = a.cpad * a.ntiles;
     const int64_t n = a.C * a.ntiles;  // entries ch * ntiles + tile, ch < C
-    const double *p = a.part + (int64_t)blockIdx.x * stride;  // block = 5 s + k
+    const double *p = a.part + (int64_t)block * stride;  // block = 5 s + k
     const double t = block_sum_fixed(strided_sum(p, n, threadIdx.x, RED_THREADS), sh);
-    if (threadIdx.x == 0) a.sums[blockIdx.x] = t;
+    if (threadIdx.x == 0) a.sums[block] = t;
 }
 
-__global__ void sos_grad_map_kernel(SosGradArgs a) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.S || (a.gate && short_done(a.gate))) return;
+__device__ __forceinline__ void sos_grad_map(const SosGradArgs &a, const GradList &out, int s) {
     double d[5];
     for (int k = 0; k < 5; ++k) d[k] = a.sums[5 * s + k];
     const double b0 = a.tab[s].coef[0], a1 = a.tab[s].coef[3], a2 = a.tab[s].coef[4];
     const double dA00 = d[0], dA10 = d[1], dB0 = d[2], dB1 = d[3], dD = d[4];
     int st = 0, j = s;
-    while (j >= a.out.len[st]) {
-        j -= a.out.len[st];
+    while (j >= out.len[st]) {
+        j -= out.len[st];
         ++st;
     }
-    float *o = a.out.ptr[st];
+    float *o = out.ptr[st];
     if (!o) return;
     o[5 * j + 0] = (float)(dD - a1 * dB0 - a2 * dB1);  // b0 enters D and both entries of B
     o[5 * j + 1] = (float)dB0;
@@ -519,11 +514,8 @@ __global__ __launch_bounds__(WG) void fir_bwd_kernel(FirBwdArgs a) {
 constexpr int SPEC_SPLIT = 64;
 constexpr int FIR_BWD_WGS = 512;  // two per CU fit (about 230 VGPRs)
 
-__global__ void fir_spec_reduce1_kernel(const float2 *spart, int64_t nwg, double2 *sum1,
-                                        const uint32_t *gate) {
-    if (gate && short_done(gate)) return;
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t w0 = (int64_t)blockIdx.y * SPEC_SPLIT;
+__device__ __forceinline__ void fir_spec_reduce1(const float2 *spart, int64_t nwg, double2 *sum1, int split, int f) {
+    const int64_t w0 = (int64_t)split * SPEC_SPLIT;
     const int64_t w1 = min(nwg, w0 + SPEC_SPLIT);
     double sr = 0.0, si = 0.0;
 #pragma unroll 8
@@ -532,13 +524,10 @@ __global__ void fir_spec_reduce1_kernel(const float2 *spart, int64_t nwg, double
         sr += (double)v.x;
         si += (double)v.y;
     }
-    sum1[(int64_t)blockIdx.y * NFFT + f] = make_double2(sr, si);
+    sum1[(int64_t)split * NFFT + f] = make_double2(sr, si);
 }
 
-__global__ void fir_spec_reduce2_kernel(const double2 *sum1, int32_t nsplit, double2 *spec,
-                                        const uint32_t *gate) {
-    if (gate && short_done(gate)) return;
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void fir_spec_reduce2(const double2 *sum1, int32_t nsplit, double2 *spec, int f) {
     double sr = 0.0, si = 0.0;
     for (int k = 0; k < nsplit; ++k) {
         const double2 v = sum1[(int64_t)k * NFFT + f];
@@ -549,14 +538,12 @@ __global__ void fir_spec_reduce2_kernel(const double2 *sum1, int32_t nsplit, dou
 }
 
 // dL/dh[k] = Re(sum_f P[f] e^{+2 pi i f k / 4096}) / 4096 for the lags
-// k = 4 blockIdx.x + u, u < 4: thread t takes bins f = t + 256 j for all four
+// k = 4 block + u, u < 4: thread t takes bins f = t + 256 j for all four
 // lags, then a fixed-order block sum per lag.
 constexpr int GH_DFT_LAGS = 4;
-__global__ void fir_gh_dft_kernel(const double2 *spec, const double2 *tw64, int32_t M, float *gh,
-                                  const uint32_t *gate) {
+__device__ __forceinline__ void fir_gh_dft(const double2 *spec, const double2 *tw64, int32_t M, float *gh, int block) {
     __shared__ double wsum[GH_DFT_LAGS][WG / 64];
-    if (gate && short_done(gate)) return;
-    const int k0 = blockIdx.x * GH_DFT_LAGS, t = threadIdx.x;
+    const int k0 = block * GH_DFT_LAGS, t = threadIdx.x;
     double acc[GH_DFT_LAGS] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int j = 0; j < 16; ++j) {
@@ -585,24 +572,84 @@ __global__ void fir_gh_dft_kernel(const double2 *spec, const double2 *tw64, int3
 // (sum1[split][k]), level 2 the splits in order.
 constexpr int GH_SPLIT = 128;
 
-__global__ void fir_gh_reduce1_kernel(const float *part, int32_t M, int64_t nparts, double *sum1,
-                                      const uint32_t *gate) {
-    if (gate && short_done(gate)) return;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void fir_gh_reduce1(const float *part, int32_t M, int64_t nparts, double *sum1, int split,
+                                               int k) {
     if (k >= M) return;
-    const int64_t i0 = (int64_t)blockIdx.y * GH_SPLIT;
+    const int64_t i0 = (int64_t)split * GH_SPLIT;
     const int64_t i1 = min(nparts, i0 + GH_SPLIT);
     const int kb = k / FFT_PART, kk = k % FFT_PART;
     const float *p = part + ((int64_t)kb * nparts + i0) * FFT_PART + kk;
-    sum1[(int64_t)blockIdx.y * M + k] = strided_sum(p, (i1 - i0) * FFT_PART, 0, FFT_PART);
+    sum1[(int64_t)split * M + k] = strided_sum(p, (i1 - i0) * FFT_PART, 0, FFT_PART);
 }
 
-__global__ void fir_gh_reduce2_kernel(const double *sum1, int32_t M, int32_t nsplit, float *dst,
-                                      const uint32_t *gate) {
-    if (gate && short_done(gate)) return;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void fir_gh_reduce2(const double *sum1, int32_t M, int32_t nsplit, float *dst, int k) {
     if (k >= M) return;
     dst[k] = (float)strided_sum(sum1 + k, (int64_t)nsplit * M, 0, M);
+}
+
+// The coefficient gradients in three launches, each with the parts of one level:
+// of the scan's adjoint (section sums; the FIR's spectra, or its partials by lag)
+// or, where the short-memory form has done the work, of that.  A launch that finds
+// nothing to do takes 4.6 us and the host 3.5: as launches of their own the
+// short-memory form's three made a training step of any other chain 20 us longer
+// (8 x 5.76 M, 1023 taps, two sections that ring on: 745 us a step, 735 so; steps
+// bound by the host 220 and 207).
+struct GradArgs {
+    const uint32_t *gate;  // workspace header if the short-memory adjoint ran before, or null
+    ShortGradArgs sh;
+    SosGradArgs sos;
+    GradList gsos;
+    int32_t nsos;          // 5 S, or 0
+    int32_t fir;           // 0: no tap gradient, 1: from spectra, 2: from partials
+    const float2 *spart;
+    int64_t nparts;        // workgroups of spart, or blocks of part
+    const float *part;
+    double2 *spec1, *spec;
+    double *gh1;
+    int32_t nsplit, M, lagblocks;  // lagblocks: ceil(M / 256)
+    const double2 *tw64;
+    float *gh;
+};
+
+__global__ __launch_bounds__(RED_THREADS) void grad_level1_kernel(GradArgs a) {
+    __shared__ double sh[RED_THREADS];
+    int b = blockIdx.x;
+    if (a.gate && short_done(a.gate)) {
+        if (b < SB_SUM_BLOCKS) short_spec_sum(a.sh, b);
+        return;
+    }
+    if (b < a.nsos) {
+        sos_grad_reduce(a.sos, b, sh);
+        return;
+    }
+    b -= a.nsos;
+    const int per = a.fir == 1 ? NFFT / RED_THREADS : a.lagblocks;
+    if (a.fir == 0 || b >= per * a.nsplit) return;
+    const int split = b / per, i = b % per * RED_THREADS + threadIdx.x;
+    if (a.fir == 1) fir_spec_reduce1(a.spart, a.nparts, a.spec1, split, i);
+    else fir_gh_reduce1(a.part, a.M, a.nparts, a.gh1, split, i);
+}
+
+constexpr int LEVEL2_THREADS = 512;
+__global__ __launch_bounds__(LEVEL2_THREADS) void grad_level2_kernel(GradArgs a) {
+    const int b = blockIdx.x;
+    if (a.gate && short_done(a.gate)) {
+        if (b < SB_GRAD_BLOCKS) short_grad(a.sh, b);
+        return;
+    }
+    if (b == 0) {
+        if ((int)threadIdx.x < a.nsos / 5) sos_grad_map(a.sos, a.gsos, threadIdx.x);
+        return;
+    }
+    const int i = (b - 1) * LEVEL2_THREADS + threadIdx.x;
+    if (a.fir == 1 && i < NFFT) fir_spec_reduce2(a.spec1, a.nsplit, a.spec, i);
+    else if (a.fir == 2) fir_gh_reduce2(a.gh1, a.M, a.nsplit, a.gh, i);
+}
+
+__global__ __launch_bounds__(WG) void grad_level3_kernel(GradArgs a) {
+    const int b = blockIdx.x;
+    if (a.gate && short_done(a.gate)) short_grad_out(a.sh, a.gsos, b, a.sh.gh ? short_out_blocks(a.M) : 0);
+    else if (a.fir == 1 && b * GH_DFT_LAGS < a.M) fir_gh_dft(a.spec, a.tw64, a.M, a.gh, b);
 }
 
 // out = a (*) b, FP64 (a == null stands for the unit impulse).
@@ -693,6 +740,21 @@ BwdLayout bwd_layout(int64_t C, int64_t N, int32_t S, int32_t M_merged, int32_t 
     return b;
 }
 
+// (every launch sized for whichever form has done the work)
+static hipError_t launch_grads(const GradArgs &a, hipStream_t st) {
+    const int n1 = a.nsos + (a.fir == 1 ? NFFT / RED_THREADS : a.fir == 2 ? a.lagblocks : 0) * a.nsplit;
+    const int n2 = 1 + (a.fir == 1 ? NFFT / LEVEL2_THREADS : a.fir == 2 ? (a.M + LEVEL2_THREADS - 1) / LEVEL2_THREADS : 0);
+    const int n3 = a.fir == 1 ? (a.M + GH_DFT_LAGS - 1) / GH_DFT_LAGS : 0;
+    const int out = a.gate ? (a.sh.gh ? short_out_blocks(a.M) : 0) + 1 : 0;
+    hipLaunchKernelGGL(grad_level1_kernel, dim3((unsigned)std::max(n1, a.gate ? SB_SUM_BLOCKS : 0)), dim3(RED_THREADS), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(grad_level2_kernel, dim3((unsigned)std::max(n2, a.gate ? SB_GRAD_BLOCKS : 0)), dim3(LEVEL2_THREADS), 0, st, a);
+    if ((e = hipGetLastError()) != hipSuccess || std::max(n3, out) == 0) return e;
+    hipLaunchKernelGGL(grad_level3_kernel, dim3((unsigned)std::max(n3, out)), dim3(WG), 0, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_backward(const BwdPlan &bp) {
     const ChainPlan &p = bp.fwd;
     const int32_t M = merged_taps(p.firs);
@@ -722,10 +784,21 @@ hipError_t launch_backward(const BwdPlan &bp) {
     float *gH = !any ? nullptr : p.firs.n == 1 ? bp.gfir.ptr[0] : reinterpret_cast<float *>(ws + lay.gH);
     uint32_t *hdr = reinterpret_cast<uint32_t *>(ws + lay.fwd.hdr);
     const uint32_t *gate = short_try ? hdr : nullptr;
-    if (short_try &&
-        (e = launch_short_bwd(bp, M, lay.fwd.short_units, ws + lay.fwd.sh, ws + (p.fir_mode == FIR_FFT16 ? lay.fwd.f16 : lay.fwd.sh), area, gH,
-                              hdr)) != hipSuccess)
-        return e;
+    bool want = any;  // a coefficient's gradient
+    for (int i = 0; i < bp.gsos.n; ++i) want = want || bp.gsos.ptr[i] != nullptr;
+    GradArgs ga{};
+    ga.gate = gate;
+    ga.gsos = bp.gsos;
+    ga.M = M;
+    ga.lagblocks = (M + RED_THREADS - 1) / RED_THREADS;
+    ga.gh = gH;
+    if (short_try) {
+        if ((e = launch_short_bwd(bp, M, lay.fwd.short_units, ws + lay.fwd.sh,
+                                  ws + (p.fir_mode == FIR_FFT16 ? lay.fwd.f16 : lay.fwd.sh), area, want, hdr)) !=
+            hipSuccess)
+            return e;
+        ga.sh = short_grad_args(bp, M, area, gH, hdr);
+    }
     // the cascade input f and the gradient of the cascade input gf
     const float *f = p.x;
     int64_t ldf = p.ldx;
@@ -787,22 +860,17 @@ hipError_t launch_backward(const BwdPlan &bp) {
             hipLaunchKernelGGL((sos_bwd_kernel<true, false>), grid, block, dyn, st, b);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        SosGradArgs r{};
-        r.gate = gate;
+        SosGradArgs &r = ga.sos;
         r.part = b.part;
         r.tab = b.tab;
         r.S = p.S;
         r.C = p.C;
         r.ntiles = ntiles;
         r.cpad = cpad;
-        r.out = bp.gsos;
         r.sums = reinterpret_cast<double *>(ws + lay.sos_sum);
-        hipLaunchKernelGGL(sos_grad_reduce_kernel, dim3((unsigned)(5 * p.S)), dim3(RED_THREADS), 0, st, r);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(sos_grad_map_kernel, dim3((unsigned)((p.S + 63) / 64)), dim3(64), 0, st, r);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        ga.nsos = 5 * p.S;
     }
-    if (!has_fir) return hipSuccess;
+    if (!has_fir) return want ? launch_grads(ga, st) : hipSuccess;
     const float *gfc = has_sos ? gf : bp.gy;
     const int64_t ldgfc = has_sos ? ldgf : bp.ldg;
     if (lay.spec_path) {
@@ -827,23 +895,18 @@ hipError_t launch_backward(const BwdPlan &bp) {
         fb.xcd_ks = lay.spec_wg % 8 == 0 ? xcd_window(npairs) : 0;  // item ip runs on XCD ip % 8
         hipLaunchKernelGGL(fir_bwd_kernel, dim3((unsigned)lay.spec_wg), dim3(WG), 0, st, fb);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (!any) return hipSuccess;
-        double2 *sum1 = reinterpret_cast<double2 *>(ws + lay.gh1);
-        double2 *spec = reinterpret_cast<double2 *>(ws + lay.spec);
-        hipLaunchKernelGGL(fir_spec_reduce1_kernel, dim3(NFFT / 256, (unsigned)lay.spec_nsplit), dim3(256), 0, st,
-                           static_cast<const float2 *>(fb.spart), lay.spec_wg, sum1, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(fir_spec_reduce2_kernel, dim3(NFFT / 256), dim3(256), 0, st,
-                           static_cast<const double2 *>(sum1), (int32_t)lay.spec_nsplit, spec, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(fir_gh_dft_kernel, dim3((unsigned)((M + GH_DFT_LAGS - 1) / GH_DFT_LAGS)), dim3(WG), 0, st,
-                           static_cast<const double2 *>(spec), reinterpret_cast<const double2 *>(ws + lay.fwd.tw64),
-                           M, gH, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        ga.fir = any ? 1 : 0;
+        ga.spart = fb.spart;
+        ga.nparts = lay.spec_wg;
+        ga.nsplit = (int32_t)lay.spec_nsplit;
+        ga.spec1 = reinterpret_cast<double2 *>(ws + lay.gh1);
+        ga.spec = reinterpret_cast<double2 *>(ws + lay.spec);
+        ga.tw64 = reinterpret_cast<const double2 *>(ws + lay.fwd.tw64);
     } else {
         // input gradient: correlation of the cascade-input gradient with the taps
         if ((e = launch_fir_pass(p, lay.fwd, gfc, ldgfc, bp.gx, bp.ldgx, true, gate)) != hipSuccess) return e;
-        if (!any) return hipSuccess;
+    }
+    if (!lay.spec_path && any) {
         GhArgs g{};
         g.gate = gate;
         g.x = p.x;
@@ -865,16 +928,14 @@ hipError_t launch_backward(const BwdPlan &bp) {
         hipLaunchKernelGGL(fir_gh_part_kernel, dim3((unsigned)(npairs * ntiles), (unsigned)lay.nlag), dim3(WG), 0,
                            st, g);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const int64_t nbx = npairs * ntiles;
-        const int32_t nsplit = (int32_t)((nbx + GH_SPLIT - 1) / GH_SPLIT);
-        double *sum1 = reinterpret_cast<double *>(ws + lay.gh1);
-        hipLaunchKernelGGL(fir_gh_reduce1_kernel, dim3((unsigned)((M + 255) / 256), (unsigned)nsplit), dim3(256), 0,
-                           st, static_cast<const float *>(g.part), M, nbx, sum1, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(fir_gh_reduce2_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const double *>(sum1), M, nsplit, gH, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        ga.fir = 2;
+        ga.part = g.part;
+        ga.nparts = npairs * ntiles;
+        ga.nsplit = (int32_t)((ga.nparts + GH_SPLIT - 1) / GH_SPLIT);
+        ga.gh1 = reinterpret_cast<double *>(ws + lay.gh1);
     }
+    if (want && (e = launch_grads(ga, st)) != hipSuccess) return e;
+    if (!any) return hipSuccess;
     if (p.firs.n == 1) return hipSuccess;
     // several FIR stages: chain rule through the tap convolution
     double *o0 = reinterpret_cast<double *>(ws + lay.obuf), *o1 = o0 + M;

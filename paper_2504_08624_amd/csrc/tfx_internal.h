@@ -466,10 +466,10 @@ hipError_t launch_backward(const BwdPlan &p);
 // ---- adjoint of a short-memory chain (tfx_short_bwd.hip) ------------------------
 size_t short_bwd_bytes(int64_t C, int64_t N);
 void *short_bwd_hf(void *area);  // where the prepare step leaves the FIR's response in FP64
-// gx and the gradients (gH: of the merged taps, null: not wanted) of a chain
-// prepared with tab / tw as in launch_short16k, if it is a short-memory one of at
-// most max_units units; area: short_bwd_bytes.
+// gx of a chain prepared with tab / tw as in launch_short16k, if it is a short-
+// memory one of at most max_units units, and (want) the cross-spectra from which
+// the reductions make the coefficients' gradients; area: short_bwd_bytes.
 hipError_t launch_short_bwd(const BwdPlan &bp, int32_t M, uint32_t max_units, const void *tab, const void *tw,
-                            void *area, float *gH, uint32_t *hdr);
+                            void *area, bool want, uint32_t *hdr);
 
 }  // namespace tfx

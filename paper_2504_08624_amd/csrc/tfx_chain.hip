@@ -1029,13 +1029,17 @@ hipError_t launch_state_passthrough(const float *in, float *out, int64_t n, hipS
 // workgroups the counting makes it 58 against 48).  Then: the second pass of every
 // section in every tile, and the FP64 variant behind it.  Large calls
 // (stout_split): the tiles before the last as without registers, and the last one
-// behind them, which costs its tile's latency once and saves the second pass:
-// 8 sections, 2048 / 3600 / 15000 workgroups 84 / 113 / 338 us split, 90 / 141 /
-// 476 not; 6 sections, 3600 / 7200 / 15000: 110 / 176 / 310 and 101 / 176 / 333; 4
-// sections, 7200 / 10338 / 30000: 145 / 191 / 481 and 140 / 188 / 496; 2 sections,
-// 30000: 428 and 417.
+// behind them, which costs its tile's latency once and saves the second pass.  us
+// split / not: 8 sections, 2048 / 3600 / 15000 workgroups 84 / 114 / 338 and 90 /
+// 141 / 477; 7 sections, 2048 / 3600 / 15000: 81 / 110 / 331 and 76 / 115 / 378; 6
+// sections, 3600 / 7200 / 15000: 110 / 177 / 311 and 102 / 178 / 335; 5 sections,
+// 7200 / 10400: 163 / 212 and 160 / 214; 4 sections, 10400 / 15000 / 40000: 190 /
+// 257 / 626 and 189 / 262 / 663; 3 sections, 30000 / 40000: 436 / 602 and 437 /
+// 584; fewer never.
 constexpr int64_t STOUT_ONE = 64;
-inline bool stout_split(int64_t wgs, int32_t S) { return S >= MC_MIN_SECTIONS ? wgs >= 2048 : wgs * (S - 2) >= 28000; }
+inline bool stout_split(int64_t wgs, int32_t S) {
+    return S >= 8 ? wgs >= 2048 : S == 7 ? wgs >= 2800 : S >= 4 && wgs * (S - 2) >= 28000;
+}
 
 // (hiq: also the FP64-carry variant)
 template <int F, bool S, bool STOUT>

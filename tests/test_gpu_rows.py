@@ -125,3 +125,20 @@ def test_stream_of_mixed_blocks(taps, q):
             n0 += b
         assert_close(np.concatenate(out, axis=1), O.chain(x, stages), TOL_IIR_F32, "taps %d q %g" % (taps, q))
         stream.reset()
+
+
+@pytest.mark.parametrize("S,tiles", [(7, 933), (7, 934), (3, 9340)])
+def test_final_registers_by_size_of_seven_and_three(S, tiles):
+    """Either side of the rule at 7 sections (2800 workgroups), and 3, which keep to
+    one launch, with registers coming in."""
+    C, N = 6, tiles * T - 9
+    x = _gpu(_x(C, 6 * T + 1, (907, S))).repeat(1, tiles // 6 + 1)[:, :N].contiguous()
+    sec = _eq(S, 4)
+    s0 = (0.05 * signals.rng(908, S).standard_normal((C, S, 2))).astype(np.float32)
+    y, so = tfx.sos(x, _gpu(sec), state_in=_gpu(s0), return_state=True)
+    tail = 25 * T + 11
+    ref, rs = O.sos(_cpu(x[:, -tail:]), sec, return_state=True)      # the registers decay within a tile
+    assert_close(_cpu(y[:, -3 * T:]), ref[:, -3 * T:], TOL_IIR_F32, "tail S=%d tiles=%d" % (S, tiles))
+    assert np.max(np.abs(_cpu(so) - rs)) <= TOL_IIR_F32 * 0.1
+    head = O.sos(_cpu(x[:, :4 * T]), sec, state_in=s0)
+    assert_close(_cpu(y[:, :4 * T]), head, TOL_IIR_F32, "head S=%d tiles=%d" % (S, tiles))

@@ -102,7 +102,7 @@ def istft(spec: torch.Tensor, n_fft: int, hop_length=None, win_length=None, wind
     # that runs (waiting for it first left the device idle for a third of the call)
     wsrc = None if window is None else torch.as_tensor(window).detach()
     fetched = None
-    if wsrc is not None and wsrc.device.type == "cuda":
+    if wsrc is not None and wsrc.device.type == "cuda" and L > 0:
         host = torch.empty(wsrc.shape, dtype=wsrc.dtype, pin_memory=True)
         with torch.cuda.device(wsrc.device):
             host.copy_(wsrc, non_blocking=True)
@@ -113,6 +113,8 @@ def istft(spec: torch.Tensor, n_fft: int, hop_length=None, win_length=None, wind
     y = torch.empty((C, L), dtype=torch.float32, device=spec.device)
     lib.call("tfx_istft", fm.data_ptr(), C, T, n_fft, hop, _ptr(w), wl, int(bool(center)), int(bool(normalized)),
              y.data_ptr() if L else None, L, max(L, 1), _stream(spec.device))
+    if L == 0:
+        return y[0] if squeeze else y
     if fetched is not None:
         fetched.synchronize()
     full = np.zeros(n_fft)

@@ -75,3 +75,16 @@ def test_checkpoint_and_registers_of_one_tile(C, N, S, hiq):
                  torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert torch.equal(ck[:, 0], torch.zeros_like(s0) if si is None else si)
+
+
+def test_inverse_stft_of_no_samples():
+    """One centred frame has no output: nothing is fetched or looked at, and what was
+    refused still is."""
+    spec = torch.randn(2, 513, 1, dtype=torch.complex64, device=DEV)
+    for w in (None, torch.ones(1024, device=DEV), torch.zeros(1024, device=DEV)):
+        assert tuple(tfx.istft(spec, 1024, 256, window=w).shape) == (2, 0)
+    with pytest.raises(ValueError):
+        tfx.istft(spec, 1024, 256, window=torch.ones(1000, device=DEV))
+    with pytest.raises(ValueError):                          # the window's sum vanishes inside the output
+        tfx.istft(torch.randn(2, 513, 9, dtype=torch.complex64, device=DEV), 1024, 256,
+                  window=torch.zeros(1024, device=DEV))

@@ -56,13 +56,17 @@ MFMA_BF16_PEAK_TFS = 2500.0  # dense bf16 / fp16 matrix peak
 VALU_F32_PEAK_TFS = 78.6
 
 
-def chain_flops_per_sample():
+def chain_flops_per_sample(C, N, V):
     """Vector-unit flops per channel-sample of the short-memory form of the
     chain (FIR and cascade as one FIR on 16384-point blocks): one forward and one
-    inverse complex transform (5 N log2 N each) and a spectrum product (6 a bin)
-    per block of two tiles of at least 8192 samples."""
+    inverse complex transform (5 n log2 n each) and a spectrum product (6 a bin)
+    per block, two tiles of 16384 - V samples of a channel, V the chain's memory
+    (None: the chain ran as a scan)."""
+    if not V:
+        return None
     n = 16384
-    return (2 * 5 * n * 14 + 6 * n) / (2 * 8192.0)
+    blocks = C * -(-(-(-N // (n - V))) // 2)
+    return blocks * (2 * 5 * n * 14 + 6 * n) / (C * N)
 
 
 def measured_traffic():
@@ -522,10 +526,11 @@ def main():
     ms_step = wall / K * 1e3
     value = samples / (wall / K) / 1e6
     alg_bytes = 8.0 * samples
-    fps = chain_flops_per_sample()
+    memory = max(int(ws[:32].view(torch.int32)[4]) - 1, 0)   # header word: memory | 1, 0 for a scan
+    fps = chain_flops_per_sample(C, N, memory)
     kern_s = float(kern_ms.mean()) / 1e3
     achieved_gbs = alg_bytes / kern_s / 1e9
-    achieved_tfs = fps * samples / kern_s / 1e12
+    achieved_tfs = fps * samples / kern_s / 1e12 if fps else None
     out = y.cpu().numpy()
 
     # achievable copy bandwidth: a plain device copy of the input (also the
@@ -622,9 +627,9 @@ def main():
                      "copy_GBps": copy["GBps"], "frac_of_copy": round(achieved_gbs / copy["GBps"], 4),
                      "valu": {"what": "the block kernel's algorithmic flops (two 16384-point transforms and a "
                                       "spectrum product per two tiles) on the vector units, without packed fp32",
-                              "flops_per_sample": round(fps, 2), "achieved_TFLOP_per_s": round(achieved_tfs, 3),
-                              "peak_TFLOP_per_s": VALU_F32_PEAK_TFS,
-                              "frac": round(achieved_tfs / VALU_F32_PEAK_TFS, 4)}},
+                              "memory": memory, "flops_per_sample": round(fps, 2),
+                              "achieved_TFLOP_per_s": round(achieved_tfs, 3), "peak_TFLOP_per_s": VALU_F32_PEAK_TFS,
+                              "frac": round(achieved_tfs / VALU_F32_PEAK_TFS, 4)} if fps else None},
         "step_stats_ms": {"median": round(float(np.median(step_ms)), 4), "mean": round(float(step_ms.mean()), 4),
                           "sd": round(float(step_ms.std(ddof=1)) if K > 1 else 0.0, 4),
                           "cold_median": round(float(np.median(cold)), 4),

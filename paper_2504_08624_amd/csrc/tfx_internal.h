@@ -226,7 +226,12 @@ __host__ __device__ inline uint32_t unit_work(uint32_t C, uint32_t tpc) {
 // every call the rule loses 0.1 % on the mean, 11 % at most.  4096 x 1024 samples, 4
 // sections: blocks 179 us, scan 64; 13020 x 3072, 6 sections: 311 / 194; 6510 x
 // 6144, 6 sections: 181 / 194; 8 x 5 M, 2 sections, 101 taps in bf16: 115 / 129.
+// Rows of SHORT_ROW samples and more take blocks in any case: the two forms' times
+// are near each other there (matrix-core FIR of 101 taps, 8 x 1.3 M, 1 section: scan 38,
+// blocks 44; 2 sections 43 / 45; fp32 never slower) and the blocks' error is a tenth.
+constexpr int64_t SHORT_ROW = 65536;
 inline uint32_t short_max_units(int64_t C, int64_t N, int32_t S, int32_t M, int32_t fir_mode, bool adjoint) {
+    if (N >= SHORT_ROW) return 0x6fffffffu;
     const int64_t wgs = (C + 1) / 2 * ((N + T - 1) / T), s = S < 6 ? S : 6;
     int64_t u;
     if (fir_mode == FIR_TOEPLITZ) {

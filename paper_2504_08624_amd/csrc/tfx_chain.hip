@@ -657,18 +657,18 @@ __device__ __forceinline__ void chain_tile(const KArgs &a, ChainLds<FIRM> &sh, u
         // the section tables are staged once the FIR is done: its twiddles
         // hold their LDS area until then
         twl_stage(s_twl, a.twid, c.tid, WG);
-        if (HAS_SOS && c.tid == 0) s_epoch = load_epoch(a.hdr, HDR_EPOCH);
+        if (HAS_SOS && c.tid == 0) s_epoch = tag_epoch(a.hdr, ahead);
         __syncthreads();
-        if (HAS_SOS) c.epoch = ahead ? epoch_after(s_epoch) : s_epoch;
+        if (HAS_SOS) c.epoch = s_epoch;
     } else if (HAS_SOS) {
-        if (c.tid == 0) s_epoch = load_epoch(a.hdr, HDR_EPOCH);
+        if (c.tid == 0) s_epoch = tag_epoch(a.hdr, ahead);
         // the tables' loads overlap the FIR part of the tile
         if (CASC)
             stage_tables(s_tabc, a.tab, 0, a.S, c.tid, WG);
         else
             stage_tables(s_tab, a.tab, 0, min(a.S, LDS_SECTIONS), c.tid, WG);
         __syncthreads();
-        c.epoch = ahead ? epoch_after(s_epoch) : s_epoch;
+        c.epoch = s_epoch;
     }
     const uint64_t npairs = (uint64_t)(a.cpad / 2);
     const uint64_t id = xcd_order(block, nblocks, a.xcd_ks);

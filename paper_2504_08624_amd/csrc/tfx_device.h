@@ -41,6 +41,11 @@ __device__ __forceinline__ uint32_t epoch_after(uint32_t e) {
     const uint32_t ne = (e + 1u) & EPOCH_MASK;
     return ne == 0u ? 1u : ne;
 }
+// the epoch of a run's records: the header's, or (ahead) the one that follows it
+__device__ __forceinline__ uint32_t tag_epoch(const uint32_t *hdr, bool ahead) {
+    const uint32_t e = load_epoch(hdr, HDR_EPOCH);
+    return ahead ? epoch_after(e) : e;
+}
 __device__ __forceinline__ void next_epoch(uint32_t *hdr) { hdr[HDR_EPOCH] = epoch_after(hdr[HDR_EPOCH]); }
 // Run by the filter-kernel variant that does not match the high-Q word
 // before it exits: its block 0 advances the look-back epoch for the next run.

@@ -194,10 +194,13 @@ tfx_status tfx_chain_train(const float *x, float *y, int64_t C, int64_t N, int64
  * per-section device tables (and the merged taps) into ws and initialises
  * it; tfx_chain_run then filters with them, any number of times.  Both take
  * the same C, N, stages and cmp; the stage coefficients must not change in
- * between (call prepare again if they do).  tfx_chain_run launches one kernel,
- * writes no memset and re-arms the workspace for the next run itself, so it
- * may be captured into a hipGraph and replayed; runs sharing one ws must not
- * overlap in time.  tfx_chain == prepare + run on the same stream. */
+ * between (call prepare again if they do).  tfx_chain_run launches kernels only
+ * (up to four: every form the device may choose, each of which leaves at once if
+ * another does the work), writes no memset and re-arms the workspace for the next
+ * run itself, so it may be captured into a hipGraph and replayed; runs sharing one
+ * ws must not overlap in time.  tfx_chain == prepare + run on the same stream.
+ * The two calls may be given workspaces of different sizes, each of which its
+ * query accepts: a form whose tables the prepare had no room for is not taken. */
 tfx_status tfx_chain_prepare(int64_t C, int64_t N, const tfx_stage *stages, int32_t nstages,
                              tfx_compute cmp, void *ws, size_t ws_bytes, void *stream);
 tfx_status tfx_chain_run(const float *x, float *y, int64_t C, int64_t N, int64_t ldx, int64_t ldy,
@@ -209,9 +212,10 @@ tfx_status tfx_chain_run(const float *x, float *y, int64_t C, int64_t N, int64_t
  * same computation and arguments as tfx_chain, with the workspace taken from
  * a scratch array the library holds on each device (TFX_NOALLOC_SCRATCH_BYTES,
  * kept until the process ends) instead of a caller-owned one.  The call
- * allocates nothing, frees nothing and does not synchronise.  A call whose
- * workspace (tfx_chain_workspace_size) exceeds the array returns
- * TFX_E_WORKSPACE before anything is enqueued.  Every call on a device
+ * allocates nothing, frees nothing and does not synchronise.  A call that cannot
+ * do with the array (tfx_chain_workspace_size, without the part that only speeds
+ * up a chain whose response dies out quickly) returns TFX_E_WORKSPACE before
+ * anything is enqueued.  Every call on a device
  * shares that device's array: calls that may overlap in time on one device
  * (two streams, two host threads) race and give wrong results; calls on one
  * stream are ordered and safe.  The array keeps the last call's contents;
@@ -228,8 +232,9 @@ tfx_status tfx_chain_noalloc(const float *x, float *y, int64_t C, int64_t N, int
  * processing the paper's Sec. 5 names on its roadmap): y is the chain applied
  * to the block x[C][N] as the continuation of everything filtered before it.
  * The workspace is prepared once with tfx_chain_prepare(C, n_max, ...) for
- * the longest block; every block is then one call (one filter launch, plus a
- * small copy kernel for the history), N <= n_max, any N >= 0.
+ * the longest block; every block is then one call (one launch for blocks of up
+ * to 64 workgroups of two channels' 3072 samples; else the filter's and, for the
+ * history, in some forms a small copy), N <= n_max, any N >= 0.
  *   hist_in   FIR history: the M - 1 inputs just before the block, [C][M - 1]
  *             row-major (M = the merged tap count); NULL = zeros (start of
  *             the stream).  Ignored without FIR stages or when M == 1.

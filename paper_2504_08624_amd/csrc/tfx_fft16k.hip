@@ -2,10 +2,10 @@
 // 8193 taps).
 //
 // With V the filter's memory (M - 1 rounded up to a multiple of 64) a block of
-// 16384 samples gives T = 16384 - V outputs.  A workgroup filters two
-// tiles, neighbours in one channel or rows of one tile each, one in the real and
-// one in the imaginary part of the transform (the taps are real, so the two
-// outputs separate).  Convolution: a tile's block starts V
+// 16384 samples gives T = 16384 - V outputs.  A workgroup filters two tiles,
+// neighbours in one channel or, of many short rows, two rows of one tile each,
+// one in the real and one in the imaginary part of the transform (the taps are
+// real, so the two outputs separate).  Convolution: a tile's block starts V
 // samples before it, and the last T outputs of the circular convolution are
 // the tile.  Correlation (the FIR adjoint, gx[n] = sum_k h[k] g[n + k]): the
 // block starts at the tile, the spectrum is conjugated, and the first T

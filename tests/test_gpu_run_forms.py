@@ -88,3 +88,18 @@ def test_inverse_stft_of_no_samples():
     with pytest.raises(ValueError):                          # the window's sum vanishes inside the output
         tfx.istft(torch.randn(2, 513, 9, dtype=torch.complex64, device=DEV), 1024, 256,
                   window=torch.zeros(1024, device=DEV))
+
+
+@pytest.mark.parametrize("taps", [0, 201])
+def test_low_frequency_stream_of_mixed_blocks(taps):
+    """Slow registers (peaks from 250 Hz) through blocks of one tile and of several."""
+    C, sizes = 3, (512, 4 * T + 3, 512, 1, 2 * T, 700, 230_000, 512)
+    x = _x(C, sum(sizes), (954, taps))
+    sec = np.concatenate([design.peaking(f, 1.0, 6.0, 48000.0) for f in (250.0, 700.0, 2000.0)]).astype(np.float32)
+    stages = [("sos", sec)]
+    if taps:
+        stages.insert(0, ("fir", design.fir_lowpass(taps, 9000.0, 48000.0).astype(np.float32)))
+    st = tfx.ChainStream([(k, _gpu(c)) for k, c in stages], C, max(sizes))
+    ends = np.cumsum(sizes)
+    out = [_cpu(st.process(_gpu(x[:, e - b:e]))) for e, b in zip(ends, sizes)]
+    assert_close(np.concatenate(out, axis=1), O.chain(x, stages), TOL_IIR_F32, "taps %d" % taps)

@@ -34,13 +34,13 @@ constexpr int SB_SPLITS = 16;
 
 // sum1[split][pos] = sum of the spectra q = split, split + SPLITS, ... of spart in
 // that order, in FP64.  Only the first of them are written: by the workgroups of
-// the whole rounds, and in the last round by those that have a unit left.
+// the whole runs, and in the last run by those that have a unit left.
 constexpr int SB_SUM_BLOCKS = FFT16_POINTS / 256 * SB_SPLITS;  // of 256 threads
 __device__ __forceinline__ void short_spec_sum(const ShortGradArgs &a, int block) {
     const int T = FFT16_POINTS - (int)(a.hdr[HDR_SHORT] & ~1u), split = block / (FFT16_POINTS / 256);
-    const uint32_t nwg = a.nwg, round = SB_RUN * nwg;
+    const uint32_t nwg = a.nwg, run = SB_RUN * nwg;
     const uint32_t nunits = tile_units((uint32_t)a.C, f16k::tiles_per_row(a.N, T));
-    const uint32_t full = (nunits - 1) / round, nq = full * nwg + min(nwg, nunits - full * round);
+    const uint32_t full = (nunits - 1) / run, nq = full * nwg + min(nwg, nunits - full * run);
     const int pos = block % (FFT16_POINTS / 256) * 256 + threadIdx.x;
     double sr = 0.0, si = 0.0;
 #pragma unroll 8
